@@ -1,0 +1,350 @@
+"""Timed workloads of the library, through its Python entry points.
+
+Four kinds of call make up a program that uses the library, and each has its cases here:
+
+* ``sample``    one launch of the generative sampler on a batch of cell transmissions
+                (``binding.gmc_sample`` / ``gmc_sample_internal``), for every network the package
+                ships weights of, each operand precision and both integrators;
+* ``walk``      one launch of the analog random walk (``binding.mc_transmit`` /
+                ``mc_transmit_internal``);
+* ``transport`` a whole transport problem, births to tallies (``transport.run_problem``).
+
+The sizes are those of the benchmark, the studies and the tests: batches from a few hundred
+transmissions (a request, the last steps of a transport run) to 2^20, tau = 0.1 .. 100 (walks up to
+300), 10^4 .. 10^6 histories.
+"""
+from __future__ import annotations
+
+import functools
+import math
+import os
+
+import numpy as np
+import torch
+
+from paper_2512_13965_amd import binding, inputs, transport
+
+WEIGHTS = os.path.join(os.path.dirname(os.path.abspath(inputs.__file__)), "weights")
+
+# network: weights file (None: random initialisation), hidden width
+NETS = {
+    "h512": ("gmc_h512.bin", 512),                    # the headline boundary model
+    "h512_rect": ("gmc_h512_rect.bin", 512),          # rectangular cells
+    "h512_xy": ("gmc_h512_xy.bin", 512),              # XY geometry
+    "h512_internal": ("gmc_h512_internal.bin", 512),  # births inside a cell
+    "h512_collided": ("gmc_h512_collided.bin", 512),
+    "h128": ("gmc_h128.bin", 128),                    # fitted up to tau = 1000
+    "h128_internal": ("gmc_h128_internal.bin", 128),
+    "h128_collided": ("gmc_h128_collided.bin", 128),
+    "film_h512": ("gmc_film_h512.bin", 512),          # residual network
+    "h256": (None, 256),                              # the FP32 configuration (no fitted weights)
+}
+
+
+def listed():
+    S = dict(kind="sample")
+    W = dict(kind="walk", inside=False, ncoll=False)
+    T = dict(kind="transport")
+    return [
+        # a small request: one call decides the latency a caller sees
+        dict(S, name="request", net="h512", precision="bf16", integrator="euler", K=16, n=777),
+        # the headline batch: a full launch of mixed cells
+        dict(S, name="batch", net="h512", precision="bf16", integrator="euler", K=16, n=1 << 20),
+        # the paper's integrator on an ordinary, ragged batch (a transport step in mid-run)
+        dict(S, name="rk4", net="h512", precision="bf16", integrator="rk4", K=12, n=50_003),
+        # the FP32 configuration of the benchmark
+        dict(S, name="fp32", net="h256", precision="fp32", integrator="euler", K=16, n=65_536),
+        # the FP8 sampler
+        dict(S, name="fp8", net="h512", precision="fp8", integrator="euler", K=16, n=300_007),
+        # the small network of thick media and of the fastest transport
+        dict(S, name="narrow", net="h128", precision="bf16", integrator="rk4", K=12, n=1 << 18),
+        # the residual network with adaptive modulation
+        dict(S, name="film", net="film_h512", precision="bf16", integrator="euler", K=16, n=20_001),
+        # births inside source cells: a chunk of a transport run's source
+        dict(S, name="births", net="h512_internal", precision="bf16", integrator="rk4", K=12, n=10_000),
+        # the analog walk the sampler replaces: mixed cells, and a thick cell, whose longest walks
+        # take thousands of flights
+        dict(W, name="walk", tau=0.0, c=0.0, mode="continuous", n=1 << 20),
+        dict(W, name="walk_thick", tau=100.0, c=0.99, mode="continuous", n=1_000_003),
+        # the full method on the lattice: internal births, collided model, first-flight split
+        dict(T, name="lattice", problem="lattice", method="split_h128", integrator="rk4", K=12,
+             histories=200_000),
+        # analog transport on the checkerboard, the reference solution of every comparison
+        dict(T, name="checkerboard", problem="checkerboard", method="analog", integrator="euler", K=16,
+             histories=1_000_000),
+    ]
+
+
+def _log_int(rng, lo, hi):
+    return int(round(math.exp(rng.uniform(math.log(lo), math.log(hi)))))
+
+
+def draw(rng):
+    kind = rng.choice(["sample", "sample", "sample", "walk", "walk", "transport"])
+    if kind == "sample":
+        net = rng.choice(["h512", "h512", "h512_rect", "h512_xy", "h512_internal", "h128", "h128_internal",
+                          "film_h512", "h256"])
+        precision = {"h256": rng.choice(["fp32", "bf16", "fp8"]), "film_h512": "bf16"}.get(
+            net, rng.choice(["bf16", "bf16", "fp8"]))
+        if net.startswith("h128"):
+            precision = rng.choice(["bf16", "fp8", "fp32"])
+        integrator = rng.choice(["euler", "rk4"])
+        K = rng.choice([8, 12, 16, 16, 24]) if integrator == "euler" else rng.choice([6, 12, 12])
+        case = dict(kind=kind, net=net, precision=precision, integrator=integrator, K=K, n=1)
+        # at most half the headline launch's operations (FP32 runs at a sixteenth of the rate)
+        top = 13e12 / (16 if precision == "fp32" else 1)
+        most = top / work(case)["flops"]
+        case["n"] = _log_int(rng, 100, min(most, 1 << 20))
+        return case
+    if kind == "walk":
+        # one material, or mixed cells (tau = 0)
+        tau = rng.choice([0.0, round(math.exp(rng.uniform(math.log(0.1), math.log(300.0))), 3)])
+        return dict(kind=kind, inside=rng.random() < 0.3, ncoll=rng.random() < 0.3, tau=tau,
+                    c=round(rng.uniform(0.8, 1.0), 3), mode=rng.choice(["continuous", "continuous", "analog"]),
+                    n=_log_int(rng, 1000, (1 << 20) if tau < 150 else (1 << 17)))
+    problem = rng.choice(["lattice", "checkerboard", "hohlraum"])
+    method = rng.choice(["analog", "split_h128", "split_h512"]) if problem != "checkerboard" else "analog"
+    most = {"analog": 1_000_000, "split_h128": 200_000, "split_h512": 30_000}[method]
+    if problem == "hohlraum":
+        most = min(most, 100_000)
+    integrator = rng.choice(["euler", "rk4"])
+    return dict(kind=kind, problem=problem, method=method, integrator=integrator,
+                K=16 if integrator == "euler" else 12, histories=_log_int(rng, 3000, most))
+
+
+# ------------------------------------------------------------------------------------------
+
+
+@functools.lru_cache(maxsize=None)
+def _weights(net):
+    file, hidden = NETS[net]
+    return inputs.random_weights(hidden, 1) if file is None else inputs.load_blob(os.path.join(WEIGHTS, file))
+
+
+def _model(net, precision):
+    return binding.Model(inputs.pack_blob(_weights(net)), precision)
+
+
+def _conditions(case, seed):
+    """Host conditions of a sample or walk case (the package's seeded input laws)."""
+    n = case["n"]
+    if case["kind"] == "walk":
+        if case["inside"]:
+            if case["tau"]:
+                return inputs.fixed_internal_conditions(n, case["tau"], case["c"], seed)
+            return inputs.internal_conditions(n, seed)
+        if case["tau"]:
+            return inputs.fixed_cell_conditions(n, case["tau"], case["c"], seed)
+        return inputs.transmission_conditions(n, seed)
+    net = case["net"]
+    if net.endswith("_internal"):
+        return inputs.internal_conditions(n, seed)
+    if net.endswith("_xy"):
+        return inputs.xy_conditions(n, seed)
+    if net.endswith("_rect"):
+        return inputs.transmission_conditions(n, seed, log_aspect_range=(-math.log(4.0), math.log(4.0)))
+    return inputs.transmission_conditions(n, seed)
+
+
+def _problem(case):
+    if case["problem"] == "lattice":
+        return inputs.lattice_problem(16)
+    if case["problem"] == "hohlraum":
+        return inputs.hohlraum_problem(112)
+    return inputs.checkerboard_problem(32)
+
+
+def prepare(case, seed):
+    if case["kind"] == "transport":
+        st = dict(case=case, seed=seed, problem=_problem(case), model=None, source=None,
+                  world=binding.World(1 << 20, 2, 1 << 14))
+        if case["method"] != "analog":
+            width = case["method"].split("_")[1]
+            st["model"] = _model(width + "_collided", "bf16")
+            if case["problem"] == "lattice":          # volumetric source; the hohlraum has a surface source
+                st["source"] = _model(width + "_internal", "bf16")
+        return st
+    host = _conditions(case, seed)
+    inside = isinstance(host, inputs.InternalConditions)
+    cond = (binding.DeviceCondInternal if inside else binding.DeviceCond).from_host(host)
+    st = dict(case=case, seed=seed, cond=cond, inside=inside, out=binding.DeviceExit.empty(case["n"]))
+    if case["kind"] == "sample":
+        st["model"] = _model(case["net"], case["precision"])
+    else:
+        st["ncoll"] = torch.empty(case["n"], dtype=torch.int32, device="cuda") if case["ncoll"] else None
+    return st
+
+
+def _record(e):
+    return dict(face=e.face, pos=e.pos, dir_cos=e.dir_cos, dir_sin=e.dir_sin, path=e.path)
+
+
+def run(state):
+    case, seed = state["case"], state["seed"]
+    if case["kind"] == "sample":
+        call = binding.gmc_sample_internal if state["inside"] else binding.gmc_sample
+        return _record(call(state["model"], state["cond"], case["integrator"], case["K"], seed, 0,
+                            out=state["out"]))
+    if case["kind"] == "walk":
+        call = binding.mc_transmit_internal if state["inside"] else binding.mc_transmit
+        mode = binding.MODE_ANALOG if case["mode"] == "analog" else binding.MODE_CONTINUOUS
+        rec = _record(call(state["cond"], mode, seed, 0, ncoll=state["ncoll"], out=state["out"]))
+        return rec if state["ncoll"] is None else dict(rec, ncoll=state["ncoll"])
+    analog = case["method"] == "analog"
+    return transport.run_problem(state["world"], state["problem"], case["histories"], seed,
+                                 binding.SAMPLER_MC if analog else binding.SAMPLER_GMC, state["model"],
+                                 case["K"], integrator=case["integrator"], source_model=state["source"],
+                                 source_K=case["K"])
+
+
+# ------------------------------------------------------------------------------------------
+
+# Operations of one flight of a walk: ten Philox rounds (two wide multiplies and four exclusive
+# ors each) and about fifty for the boundary distance, the flight length and the new direction.
+FLIGHT_OPS = 110
+
+# Cell transmissions a history takes, and the sampled (collided) ones among them.
+PER_HISTORY = {"lattice": (96.0, 6.5), "hohlraum": (112.0, 22.0), "checkerboard": (18.0, 18.0)}
+
+
+def _eval_flops(net):
+    w = _weights(net)
+    return 2.0 * sum(m.size for m in w.W)
+
+
+def _evals(case):
+    return case["K"] * (4 if case["integrator"] == "rk4" else 1)
+
+
+def work(case):
+    if case["kind"] == "sample":
+        n_c = 6 if case["net"].endswith("_internal") else 5 if case["net"].endswith(("_xy", "_rect")) else 4
+        params = _weights(case["net"]).n_params()
+        size = {"fp32": 4, "bf16": 2, "fp8": 1}[case["precision"]]
+        return dict(bytes=case["n"] * (4 * n_c + 20) + params * size,
+                    flops=case["n"] * _evals(case) * _eval_flops(case["net"]))
+    if case["kind"] == "walk":
+        # mean flights of a walk: 1 + pi tau_s / 4 in the mean over entries
+        if case["tau"]:
+            tau_s = case["tau"] * case["c"]
+        else:
+            tau_s = 0.5 * (100.0 - 0.1) / math.log(1000.0)
+        flights = 1.0 + 0.25 * math.pi * tau_s
+        return dict(bytes=case["n"] * ((24 if case["inside"] else 16) + 20 + (4 if case["ncoll"] else 0)),
+                    flops=case["n"] * flights * FLIGHT_OPS)
+    p = _problem(case)
+    visits, sampled = PER_HISTORY[case["problem"]]
+    if case["method"] == "analog":
+        tau_s = float(np.mean(p.tau * p.c))
+        flops = case["histories"] * visits * (1.0 + 0.25 * math.pi * tau_s) * FLIGHT_OPS
+    else:
+        flops = case["histories"] * (sampled + 1.0) * _evals(case) * _eval_flops(
+            case["method"].split("_")[1] + "_collided")
+    return dict(bytes=p.n_cells * (16 + 9 * 8), flops=flops)
+
+
+# ------------------------------------------------------------------------------------------
+
+
+def _philox(c0, c1, c2, c3, seed):
+    """Philox4x32-10 words (uint64 arrays holding 32-bit values) of the given counters."""
+    m = np.uint64(0xFFFFFFFF)
+    k0, k1 = seed & 0xFFFFFFFF, (seed >> 32) & 0xFFFFFFFF
+    s = np.uint64(32)
+    for _ in range(10):
+        p0, p1 = np.uint64(0xD2511F53) * c0, np.uint64(0xCD9E8D57) * c2
+        c0, c1, c2, c3 = (p1 >> s) ^ c1 ^ np.uint64(k0), p1 & m, (p0 >> s) ^ c3 ^ np.uint64(k1), p0 & m
+        k0, k1 = (k0 + 0x9E3779B9) & 0xFFFFFFFF, (k1 + 0xBB67AE85) & 0xFFFFFFFF
+    return c0, c1, c2, c3
+
+
+def _noise(seed, n):
+    """z ~ N(0, I_5) of particles 0 .. n-1 in 64 bits: Box-Muller on the Philox words."""
+    i = np.arange(n, dtype=np.uint64)
+    z = np.zeros_like(i)
+    a = _philox(i & np.uint64(0xFFFFFFFF), i >> np.uint64(32), z, z + np.uint64(1), seed)
+    b = _philox(i & np.uint64(0xFFFFFFFF), i >> np.uint64(32), z + np.uint64(1), z + np.uint64(1), seed)
+    u = [((w >> np.uint64(8)).astype(np.float64) + 1.0) * 2.0 ** -24 for w in (*a, *b[:2])]
+    out = []
+    for p in range(3):
+        r, t = np.sqrt(-2.0 * np.log(u[2 * p])), 2.0 * math.pi * u[2 * p + 1]
+        out += [r * np.cos(t), r * np.sin(t)]
+    return np.stack(out[:5], 1)
+
+
+def _silu(a):
+    return a * torch.sigmoid(a)
+
+
+def _velocity(w, W, b, x, t, f):
+    n = x.shape[0]
+    if not isinstance(w, inputs.FilmWeights):
+        h = torch.cat([x, torch.full((n, 1), t, dtype=x.dtype, device=x.device), f], 1)
+        for l in range(4):
+            h = _silu(torch.addmm(b[l], h, W[l]))
+        return torch.addmm(b[4], h, W[4])
+    phi = [g(math.pi * 2.0 ** j * t) for j in range(4) for g in (math.sin, math.cos)]
+    tf = torch.tensor(phi, dtype=x.dtype, device=x.device).expand(n, 8)
+    h = torch.addmm(b[0], torch.cat([x, tf, f], 1), W[0])
+    e = _silu(torch.addmm(b[1], torch.cat([tf, f], 1), W[1]))
+    for j in range(w.blocks):
+        l = 2 + 3 * j
+        scale, shift = torch.addmm(b[l + 1], e, W[l + 1]), torch.addmm(b[l + 2], e, W[l + 2])
+        h = h + _silu((1.0 + scale) * torch.addmm(b[l], h, W[l]) + shift)
+    return torch.addmm(b[-1], h, W[-1])
+
+
+def _exact_sample(case, seed):
+    """The sampler's exit records in 64 bits (the ODE of the same network, noise and steps)."""
+    w = _weights(case["net"])
+    W = [torch.from_numpy(m.astype(np.float64)).t().contiguous().cuda() for m in w.W]
+    b = [torch.from_numpy(v.astype(np.float64)).cuda() for v in w.b]
+    h = _conditions(case, seed)
+    d = lambda a: np.asarray(a, np.float64)
+    if case["net"].endswith("_internal"):
+        f = [d(h.log_tau), d(h.c), 2 * d(h.x) - 1, 2 * d(h.y) - 1, d(h.cos_phi), d(h.sin_phi)]
+    else:
+        f = [d(h.log_tau), d(h.c), 2 * d(h.y_in) - 1, d(h.sin_th)]
+        f += [d(a) for a in (h.log_aspect, h.omega_x) if a is not None]
+    F, Z = torch.from_numpy(np.stack(f, 1)), torch.from_numpy(_noise(seed, case["n"]))
+    K = case["K"]
+    dt = 1.0 / K
+    xs = []
+    for i in range(0, case["n"], 1 << 16):
+        x, c = Z[i:i + (1 << 16)].cuda(), F[i:i + (1 << 16)].cuda()
+        v = functools.partial(_velocity, w, W, b, f=c)
+        for k in range(K):
+            t = k * dt
+            k1 = v(x, t)
+            if case["integrator"] == "euler":
+                x = x + dt * k1
+                continue
+            k2 = v(x + 0.5 * dt * k1, t + 0.5 * dt)
+            k3 = v(x + 0.5 * dt * k2, t + 0.5 * dt)
+            k4 = v(x + dt * k3, t + dt)
+            x = x + (dt / 6.0) * (k1 + 2 * k2 + 2 * k3 + k4)
+        xs.append(x)
+    x = torch.cat(xs)
+    a0, a1, a2, a3, a4 = x.unbind(1)
+    face = (a4 >= -1).int() + (a4 >= 0).int() + (a4 >= 1).int()
+    nx = (face == 1).double() - (face == 3).double()
+    ny = (face == 2).double() - (face == 0).double()
+    r = torch.sqrt(a1 * a1 + a2 * a2)
+    keep = (r <= 1.0) if case["net"].endswith("_xy") else torch.zeros_like(r, dtype=torch.bool)
+    s = torch.where(keep, torch.ones_like(r), 1.0 / r)
+    u, v = a1 * s, a2 * s
+    dn = torch.minimum(u * nx + v * ny, torch.zeros_like(u))
+    u, v = u - 2 * dn * nx, v - 2 * dn * ny
+    bad = x.abs().amax(1) > 32.0
+    zero = lambda q: torch.where(bad, torch.zeros_like(q), q)
+    # the face is a whole number; with FP8 operands a direction near zero norm, or of a sample at a
+    # face's threshold, may turn round, so its direction is left out
+    fp8 = case["precision"] == "fp8"
+    return dict(face=None, pos=zero(((a0 + 1) / 2).clamp(0, 1)), dir_cos=None if fp8 else zero(u),
+                dir_sin=None if fp8 else zero(v), path=zero(torch.exp(a3)))
+
+
+def exact(case, seed):
+    # walks and transport runs are chains of random decisions: a rounding anywhere may send a
+    # particle another way, so they have no values in 64 bits
+    return _exact_sample(case, seed) if case["kind"] == "sample" else None
