@@ -204,7 +204,7 @@ def run(state):
 FLIGHT_OPS = 110
 
 # Cell transmissions a history takes, and the sampled (collided) ones among them.
-PER_HISTORY = {"lattice": (96.0, 6.5), "hohlraum": (112.0, 22.0), "checkerboard": (18.0, 18.0)}
+PER_HISTORY = {"lattice": (96.3, 6.5), "hohlraum": (112.3, 10.0), "checkerboard": (48.9, 48.9)}
 
 
 def _eval_flops(net):
