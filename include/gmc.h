@@ -106,12 +106,10 @@ typedef struct {
 
 typedef struct gmc_model gmc_model;
 
-/* Per-device set-up of the current device: queries its compute units and allocates the ring of
- * 4096 work counters (32 KiB) that mc_transmit and mc_transmit_internal launches take in turn
- * (kept until the process ends).  Needed once per device before those calls, which allocate
- * nothing themselves (GMC_EINVAL if the device was not set up); gmc_model_create and
- * gmc_world_create do it for their device.  Idempotent and thread-safe.  Errors: GMC_EDEVICE,
- * GMC_ENOMEM, GMC_EUNSUPPORTED (device index beyond 63). */
+/* Per-device set-up of the current device: queries its compute units.  Needed once per device
+ * before mc_transmit and mc_transmit_internal (GMC_EINVAL if the device was not set up), which
+ * allocate nothing themselves; gmc_model_create and gmc_world_create do it for their device.
+ * Idempotent and thread-safe.  Errors: GMC_EDEVICE, GMC_EUNSUPPORTED (device index beyond 63). */
 int gmc_device_init(void);
 
 /* Parses a weights blob and uploads it to the current device in the layout the kernels read.
@@ -222,19 +220,14 @@ int gmc_uncollided_split(gmc_cond cond, int64_t n, uint64_t seed, uint64_t id_ba
  *   2 -> absorption test.
  *   ncoll_opt  NULL, or device uint32 [n] receiving the number of collisions in the cell.
  * Errors: GMC_EINVAL, GMC_EDEVICE. */
-/* The walk's lanes take particles from a work counter of the ring gmc_device_init allocates
- * (GMC_EINVAL if the current device was not set up); the call allocates nothing. */
+/* GMC_EINVAL too if the current device was not set up (gmc_device_init).  The call is one kernel:
+ * it allocates nothing and keeps no state, so calls on any streams and threads may overlap. */
 int mc_transmit(gmc_cond cond, int64_t n, int mode, uint64_t seed, uint64_t id_base,
                 gmc_exit out, uint32_t *ncoll_opt, void *stream);
-/* mc_transmit for callers that cannot allocate device memory (code under HIP graph capture,
- * tight serving loops, harnesses that forbid allocation): the same walk, arguments, random
- * streams and outputs, bit for bit, but its work counter is one of 64 counters of a fixed
- * 512-byte device array that the library holds on each GPU until the process ends (its address
- * looked up by gmc_device_init, which must have run on the current device: GMC_EINVAL
- * otherwise).  The call allocates nothing, calls no allocating routine and records no memset:
- * it zeroes its counter with a kernel on `stream`.  Calls take the 64 counters in turn; calls
- * that overlap on one GPU (other streams, or more than 64 in flight) may share a counter and
- * then race.  Errors as mc_transmit, plus GMC_EINVAL for n beyond 2^62 (the counter's range). */
+/* mc_transmit by another name, kept for callers that cannot allocate device memory (code under HIP
+ * graph capture, tight serving loops, harnesses that forbid allocation), to whom it promised first
+ * what mc_transmit promises too: no allocation, no memset recorded, no allocating routine called.
+ * Errors as mc_transmit, plus GMC_EINVAL for n beyond 2^62. */
 int mc_transmit_noalloc(gmc_cond cond, int64_t n, int mode, uint64_t seed, uint64_t id_base,
                         gmc_exit out, uint32_t *ncoll_opt, void *stream);
 /* The analog walk of mc_transmit started inside the cell at (x, y) with direction

@@ -85,15 +85,18 @@ bool is_pow2(float s)
 
 std::mutex g_dev_mu;
 int g_cu[64] = {0};
-unsigned long long *g_queue[64] = {nullptr};
-unsigned g_queue_next[64] = {0};
-constexpr int kQueueRing = 4096;
-unsigned long long *g_noalloc[64] = {nullptr};   // address of the allocation-free walk's counters
-unsigned g_noalloc_next[64] = {0};
-// Largest n of mc_transmit_noalloc: its work counter (64 bits) runs up to n plus one chunk
-// per wave.
+bool g_ready[64] = {false};              // gmc_device_init has run on the device
+// Largest n of mc_transmit_noalloc.
 constexpr int64_t kNoAllocMaxN = (int64_t)1 << 62;
 
+// Whether gmc_device_init has run on the current device.
+bool device_ready()
+{
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return false;
+    std::lock_guard<std::mutex> lk(g_dev_mu);
+    return g_ready[dev];
+}
 
 }  // namespace
 
@@ -110,31 +113,6 @@ int device_cu_count()
         g_cu[dev] = cu;
     }
     return g_cu[dev];
-}
-
-// A ring of per-call work counters on the current device (allocated by gmc_device_init, kept
-// until the process ends).  Each launch takes the next slot and zeroes it on its own stream
-// first.
-unsigned long long *device_queue_counter()
-{
-    int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return nullptr;
-    std::lock_guard<std::mutex> lk(g_dev_mu);
-    if (!g_queue[dev]) return nullptr;
-    unsigned slot = g_queue_next[dev]++ % kQueueRing;
-    return g_queue[dev] + slot;
-}
-
-// The next counter of the allocation-free walk on the current device, or nullptr if the device
-// has not been set up.
-unsigned long long *noalloc_counter()
-{
-    int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return nullptr;
-    std::lock_guard<std::mutex> lk(g_dev_mu);
-    if (!g_noalloc[dev]) return nullptr;
-    unsigned slot = g_noalloc_next[dev]++ % gmc::kNoAllocCounters;
-    return g_noalloc[dev] + slot;
 }
 
 }  // namespace gmc
@@ -156,18 +134,7 @@ int gmc_device_init(void)
     if (dev < 0 || dev >= 64) return fail(GMC_EUNSUPPORTED, "gmc_device_init: device index beyond 63");
     if (gmc::device_cu_count() <= 0) return fail(GMC_EDEVICE, "gmc_device_init: cannot query the device");
     std::lock_guard<std::mutex> lk(g_dev_mu);
-    if (!g_queue[dev]) {
-        void *p = nullptr;
-        e = hipMalloc(&p, sizeof(unsigned long long) * kQueueRing);
-        if (e != hipSuccess) return fail(GMC_ENOMEM, "gmc_device_init: cannot allocate the walk's work counters");
-        g_queue[dev] = (unsigned long long *)p;
-    }
-    if (!g_noalloc[dev]) {     // once per device, with that device current
-        unsigned long long *base = nullptr;
-        e = gmc::lookup_noalloc_counters(&base);
-        if (e != hipSuccess) return hip_fail(e, "gmc_device_init: looking up the allocation-free walk's counters");
-        g_noalloc[dev] = base;
-    }
+    g_ready[dev] = true;
     return GMC_OK;
 }
 
@@ -439,7 +406,7 @@ int launch_sampler(const gmc_model *m, gmc::MlpParams p, int64_t n, int integrat
 }
 
 int launch_walk_api(gmc::WalkParams p, int64_t n, int mode, uint64_t seed, uint64_t id_base, gmc_exit out,
-                    uint32_t *ncoll_opt, void *stream, const char *who, bool noalloc = false)
+                    uint32_t *ncoll_opt, void *stream, const char *who)
 {
     const std::string w(who);
     if (mode != GMC_MODE_CONTINUOUS && mode != GMC_MODE_ANALOG)
@@ -457,8 +424,7 @@ int launch_walk_api(gmc::WalkParams p, int64_t n, int mode, uint64_t seed, uint6
     p.mode = mode;
     p.seed = seed;
     p.id_base = id_base;
-    p.queue = noalloc ? gmc::noalloc_counter() : gmc::device_queue_counter();
-    if (!p.queue) return fail(GMC_EINVAL, w + ": gmc_device_init has not been called on this device");
+    if (!device_ready()) return fail(GMC_EINVAL, w + ": gmc_device_init has not been called on this device");
     const int cu = gmc::device_cu_count();
     if (cu <= 0) return fail(GMC_EDEVICE, w + ": cannot query the device");
     const int grid = gmc::walk_grid(n, cu);
@@ -536,7 +502,7 @@ int mc_transmit_noalloc(gmc_cond cond, int64_t n, int mode, uint64_t seed, uint6
 {
     if (n < 0) return fail(GMC_EINVAL, "mc_transmit_noalloc: negative n");
     if (n > kNoAllocMaxN)
-        return fail(GMC_EINVAL, "mc_transmit_noalloc: n beyond 2^62, the range of its work counter");
+        return fail(GMC_EINVAL, "mc_transmit_noalloc: n beyond 2^62");
     if (n > 0 && !cond_ok(cond)) return fail(GMC_EINVAL, "mc_transmit_noalloc: null condition array");
     gmc::WalkParams p{};
     p.log_tau = cond.log_tau;
@@ -545,7 +511,7 @@ int mc_transmit_noalloc(gmc_cond cond, int64_t n, int mode, uint64_t seed, uint6
     p.sin_th = cond.sin_th;
     p.log_aspect = cond.log_aspect;
     p.omega_x = cond.omega_x;
-    return launch_walk_api(p, n, mode, seed, id_base, out, ncoll_opt, stream, "mc_transmit_noalloc", true);
+    return launch_walk_api(p, n, mode, seed, id_base, out, ncoll_opt, stream, "mc_transmit_noalloc");
 }
 
 int mc_transmit_internal(gmc_cond_internal cond, int64_t n, int mode, uint64_t seed, uint64_t id_base,

@@ -81,94 +81,6 @@ __device__ __forceinline__ void normal5(uint64_t seed, uint64_t id, float z[5])
     }
 }
 
-// State of one analog walk inside the unit cell (paper section "Monte Carlo Method", eq. 4),
-// advanced one flight at a time so a persistent kernel can refill lanes between flights.
-struct Walker {
-    float x, y, u, v, len, inv_sig, cs;
-    float wa;                            // cell width in units of its height (1: square)
-    bool xy;                             // XY geometry: (u, v) projects a direction on the sphere
-    uint32_t flight, ncoll;
-    bool scatter, analog;
-};
-
-// mode 0 (continuous absorption): flights ~ Exp(c tau); mode 1 (analog): flights ~ Exp(tau)
-// and a collision absorbs when xi > c.  Start at (x, y) with direction (u, v) in the cell
-// [0, wa] x [0, 1]; lengths and tau are in units of the cell height.
-__device__ __forceinline__ void walker_init(Walker &w, float tau, float c, int mode, float x, float y,
-                                            float u, float v, float wa = 1.0f, bool xy = false)
-{
-    w.wa = wa;
-    w.xy = xy;
-    w.analog = (mode == 1);
-    const float sig = w.analog ? tau : c * tau;
-    w.scatter = sig > 1e-30f;            // below this 1/sig would overflow
-    w.inv_sig = w.scatter ? 1.0f / sig : 0.0f;
-    w.cs = c;
-    w.x = x;
-    w.y = y;
-    w.u = u;
-    w.v = v;
-    w.len = 0.0f;
-    w.flight = 0;
-    w.ncoll = 0;
-}
-
-constexpr int kInside = -3;
-
-// One flight: distance to the boundary, sampled flight length, then scatter or leave.
-// Flight j draws Philox(key, counter (stream lo, stream hi, j, walk tag)): word 0 -> length,
-// word 1 -> new direction, word 2 -> absorption test.  Returns kInside while the particle is
-// still in the cell, else the exit face 0..3 (pos = counter-clockwise position along it, as a
-// fraction of that face's length), -1 absorbed, -2 capped.
-__device__ __forceinline__ int walker_flight(Walker &w, uint64_t key, uint64_t stream, float &pos)
-{
-    const float kInf = __builtin_inff();
-    float tx = kInf, ty = kInf;
-    if (w.u > 0.0f) tx = (w.wa - w.x) * fast_rcp(w.u);
-    else if (w.u < 0.0f) tx = -w.x * fast_rcp(w.u);
-    if (w.v > 0.0f) ty = (1.0f - w.y) * fast_rcp(w.v);
-    else if (w.v < 0.0f) ty = -w.y * fast_rcp(w.v);
-    const bool xface = tx <= ty;
-    const float db = fmaxf(xface ? tx : ty, 0.0f);
-    const U4 r = draw4(key, stream, w.flight, kTagWalk);
-    const float ds = w.scatter ? neg_log(u01(r.a)) * w.inv_sig : kInf;
-    int face = kInside;
-    if (ds >= db) {
-        w.len += db;
-        if (xface) {
-            const float ye = fminf(fmaxf(w.y + db * w.v, 0.0f), 1.0f);
-            face = w.u > 0.0f ? 1 : 3;
-            pos = w.u > 0.0f ? ye : 1.0f - ye;
-        } else {
-            const float xe = fminf(fmaxf(w.x + db * w.u, 0.0f), w.wa);
-            face = w.v > 0.0f ? 2 : 0;
-            pos = w.v > 0.0f ? (w.wa - xe) / w.wa : xe / w.wa;
-        }
-    } else {
-        w.x += ds * w.u;
-        w.y += ds * w.v;
-        w.len += ds;
-        w.ncoll += 1;
-        if (w.analog && u01(r.c) > w.cs) {
-            face = -1;
-        } else {
-            const float ph = u01(r.b);
-            w.u = cos_turns(ph);
-            w.v = sin_turns(ph);
-            if (w.xy) {                  // on the sphere: mu = 2 xi - 1 from word 3, projected
-                const float mu = 2.0f * u01(r.d) - 1.0f;
-                const float st = sqrtf(fmaxf(1.0f - mu * mu, 0.0f));
-                w.u *= st;
-                w.v *= st;
-            }
-        }
-    }
-    w.flight += 1;
-    if (face == kInside && w.flight >= kMaxFlights) face = -2;
-    if (face < 0 && face != kInside) pos = 0.0f;
-    return face;
-}
-
 // Rotation of a direction by k quarter turns counter-clockwise.
 __device__ __forceinline__ void rot_quarter(int k, float a, float b, float &ra, float &rb)
 {

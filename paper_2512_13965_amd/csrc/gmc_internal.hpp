@@ -131,18 +131,18 @@ struct WalkParams {
     const unsigned long long *n_dev;   // optional: particle count read on the device (<= n)
     int mode;
     uint64_t seed, id_base;
-    unsigned long long *queue;  // device work counter, zeroed by the launcher
 };
 
 hipError_t launch_walk(const WalkParams &p, int grid, hipStream_t s);
-#ifndef GMC_WALK_BLOCKS_PER_CU
-#define GMC_WALK_BLOCKS_PER_CU 8
-#endif
-// Grid of the persistent walk for n particles: at most GMC_WALK_BLOCKS_PER_CU blocks of 256
-// lanes per compute unit.
+// Blocks of 256 lanes per compute unit of the walk kernels, all resident at once.  8 (64 registers
+// a lane) / 6 / 5 / 4: 2^20 mixed walks 172 / 157 / 157 / 154 us, at tau = 100 706 / 661 / 723 /
+// 740 us.
+constexpr int kWalkBlocksPerCu = 6;
+// Grid of the walk for n particles: at least one particle to a wave (few walks are spread over
+// all waves, since a wave with few walks shares its lanes out among them).
 inline int walk_grid(int64_t n, int cu)
 {
-    const int64_t want = (n + 255) / 256, cap = (int64_t)cu * GMC_WALK_BLOCKS_PER_CU;
+    const int64_t want = (n + 3) / 4, cap = (int64_t)cu * kWalkBlocksPerCu;
     return (int)(want < cap ? want : cap);
 }
 hipError_t launch_split(const WalkParams &p, int32_t *flag, hipStream_t s);
@@ -150,15 +150,6 @@ hipError_t launch_decode(const float *raw, int64_t n, int32_t *face, float *pos,
                          float *dsin, float *path, int32_t *flags, hipStream_t s);
 
 int device_cu_count();
-// The next work counter of the analog walk's ring on the current device (allocated by
-// gmc_device_init), or nullptr if the device has not been set up.
-unsigned long long *device_queue_counter();
-// Work counters of the allocation-free walk (mc_transmit_noalloc): a file-scope device array of
-// kNoAllocCounters counters in gmc_walk.hip.  lookup_noalloc_counters gives its address on the
-// current device (a host-side lookup, no allocation).
-constexpr int kNoAllocCounters = 64;
-hipError_t lookup_noalloc_counters(unsigned long long **base);
-
 // Record a thread-local error message (returned by gmc_last_error) and return `code`.
 int set_error(int code, const char *msg);
 int set_hip_error(hipError_t e, const char *what);

@@ -27,6 +27,7 @@
 #include "../../include/gmc.h"
 #include "gmc_device.hpp"
 #include "gmc_internal.hpp"
+#include "gmc_walk.hpp"
 
 namespace gmc {
 namespace {
@@ -61,12 +62,6 @@ struct CellsDev {
     double *wpath, *path, *visits, *rej_w, *rej_n;
     const ProblemDev *prob;
 };
-
-__device__ __forceinline__ int lane_rank(uint64_t mask)
-{
-    return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32),
-                                          __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
-}
 
 // Per-workgroup tally staging: the flux, deposit and path tallies of a workgroup's particles are
 // summed per cell in an LDS hash table of SLOTS slots and flushed with one FP64 global atomic
@@ -249,7 +244,7 @@ __device__ __forceinline__ void append(bool alive, const Next &nx, int32_t pid, 
     if (lane == leader) b = atomicAdd(counter, (unsigned long long)__popcll(mask));
     const unsigned long long base = (unsigned long long)__shfl((long long)b, leader);
     if (alive) {
-        const int64_t j = (int64_t)(base + (unsigned long long)lane_rank(mask));
+        const int64_t j = (int64_t)(base + (unsigned long long)rank_in(mask));
         out.cell[j] = nx.cell;
         out.pid[j] = pid;
         out.entry[j] = nx.entry;
@@ -271,53 +266,53 @@ __device__ __forceinline__ void append(bool alive, const Next &nx, int32_t pid, 
     }
 }
 
-// Births of histories [h0, h0 + count) of problem pid: source sampling, analog first leg in the
-// birth cell (global orientation), tally, move; survivors appended after the alive particles.
-__global__ __launch_bounds__(256) void birth_kernel(CellsDev cd, int32_t pid, uint32_t h0,
-                                                    int64_t count, BankDev out,
-                                                    unsigned long long *counter,
-                                                    unsigned long long *pcount)
+// Volumetric births of histories [h0, h0 + count) of problem pid, first leg by the analog walk in
+// the birth cell (global orientation): the source sample of history h0 + t and its walk's exit
+// record at index t.  A lane group's walk, not a lane's, bounds the launch (see gmc_walk.hpp).
+template <bool XY>
+__global__ __launch_bounds__(256, kWalkBlocksPerCu) void birth_walk_kernel(CellsDev cd, int32_t pid, uint32_t h0, int64_t count,
+                                                            int32_t *face, float *pos, float *dcos, float *dsin,
+                                                            float *path)
 {
-    __shared__ TallyLds tl;
-    tally_init(tl);
-    __syncthreads();
-    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    bool alive = false;
-    Next nx{};
-    double w_out = 0.0;
-    uint32_t h = 0;
-    if (t < count) {
-        const ProblemDev P = cd.prob[pid];
-        h = h0 + (uint32_t)t;
-        const U4 r = draw4(P.seed, (uint64_t)h, 0u, kTagSource);
-        const uint32_t nsrc = (uint32_t)(P.snx * P.sny);
-        const uint32_t pick = __umulhi(r.a, nsrc);
-        const int ci = P.sx0 + (int)(pick % (uint32_t)P.snx), cj = P.sy0 + (int)(pick / (uint32_t)P.snx);
-        const int cell = (int)(P.cell0 + (int64_t)cj * P.nx + ci);
-        const float ph = u01(r.d);
-        // the cell's own frame [0, L / Ly] x [0, 1], lengths in units of its height Ly
-        const float wa = (float)(P.L / P.Ly);
-        float st = 1.0f;
-        if (P.xy) {                      // isotropic on the sphere: mu from a second draw
-            const U4 r2 = draw4(P.seed, (uint64_t)h, 1u, kTagSource);
-            const float mu = 2.0f * u01(r2.a) - 1.0f;
-            st = sqrtf(fmaxf(1.0f - mu * mu, 0.0f));
-        }
-        Walker W;
-        walker_init(W, (float)(cd.tau[cell] * (P.Ly / P.L)), (float)cd.c[cell], 0, wa * u01_open(r.b),
-                    u01_open(r.c), st * cos_turns(ph), st * sin_turns(ph), wa, P.xy != 0);
-        float pos = 0.0f;
-        int face;
-        do {
-            face = walker_flight(W, P.seed, (uint64_t)h, pos);
-        } while (face == kInside);
-        w_out = visit_tally(cd, P, cell, 1.0, W.len, P.Ly, tl);
-        nx = move_on(cd, P, cell, face, pos, W.u, W.v, w_out);
-        alive = nx.alive;
-    }
-    append(alive, nx, pid, w_out, h, 1u, out, counter, pcount);
-    __syncthreads();
-    tally_flush(tl, cd);
+    __shared__ WalkGroups groups[4];
+    __shared__ uint32_t pool;
+    const ProblemDev P = cd.prob[pid];
+    run_walks<false, XY, false>(
+        count, P.seed, groups, &pool,
+        [&](int64_t t) {
+            const uint32_t h = h0 + (uint32_t)t;
+            const U4 r = draw4(P.seed, (uint64_t)h, 0u, kTagSource);
+            const uint32_t nsrc = (uint32_t)(P.snx * P.sny);
+            const uint32_t pick = __umulhi(r.a, nsrc);
+            const int ci = P.sx0 + (int)(pick % (uint32_t)P.snx), cj = P.sy0 + (int)(pick / (uint32_t)P.snx);
+            const int cell = (int)(P.cell0 + (int64_t)cj * P.nx + ci);
+            const float ph = u01(r.d);
+            // the cell's own frame [0, L / Ly] x [0, 1], lengths in units of its height Ly
+            float st = 1.0f;
+            if constexpr (XY) {              // isotropic on the sphere: mu from a second draw
+                const U4 r2 = draw4(P.seed, (uint64_t)h, 1u, kTagSource);
+                const float mu = 2.0f * u01(r2.a) - 1.0f;
+                st = sqrtf(fmaxf(1.0f - mu * mu, 0.0f));
+            }
+            WalkStart w;
+            w.wa = (float)(P.L / P.Ly);
+            w.x = w.wa * u01_open(r.b);
+            w.y = u01_open(r.c);
+            w.u = st * cos_turns(ph);
+            w.v = st * sin_turns(ph);
+            w.tau = (float)(cd.tau[cell] * (P.Ly / P.L));
+            w.c = (float)cd.c[cell];
+            w.stream = (uint64_t)h;
+            w.key = P.seed;
+            return w;
+        },
+        [&](int64_t t, int f, float ps, float u, float v, float len, uint32_t) {
+            face[t] = f;
+            pos[t] = ps;
+            dcos[t] = u;
+            dsin[t] = v;
+            path[t] = len;
+        });
 }
 
 // Surface-source births of histories [h0, h0 + count): a uniformly picked cell of the source
@@ -386,9 +381,9 @@ __global__ __launch_bounds__(256) void source_kernel(CellsDev cd, int32_t pid, u
     keys[t] = P.seed;
 }
 
-// Stages 3-4 of the births sampled by the internal model (exits in the cell's own frame, which
-// is the global orientation): tally, move, append.
-__global__ __launch_bounds__(256) void source_apply_kernel(CellsDev cd, int32_t pid, uint32_t h0,
+// Stages 3-4 of the volumetric births (exits in the cell's own frame, which is the global
+// orientation): tally, move, append.
+__global__ __launch_bounds__(256) void birth_apply_kernel(CellsDev cd, int32_t pid, uint32_t h0,
                                                            int64_t count, const int32_t *face_c,
                                                            const float *pos, const float *dcos,
                                                            const float *dsin, const float *path,
@@ -411,7 +406,7 @@ __global__ __launch_bounds__(256) void source_apply_kernel(CellsDev cd, int32_t 
         const uint32_t pick = __umulhi(r.a, nsrc);
         const int ci = P.sx0 + (int)(pick % (uint32_t)P.snx), cj = P.sy0 + (int)(pick / (uint32_t)P.snx);
         const int cell = (int)(P.cell0 + (int64_t)cj * P.nx + ci);
-        w_out = visit_tally(cd, P, cell, 1.0, path[t], P.L, tl);
+        w_out = visit_tally(cd, P, cell, 1.0, path[t], P.Ly, tl);
         nx = move_on(cd, P, cell, face_c[t], pos[t], dcos[t], dsin[t], w_out);
         alive = nx.alive;
     }
@@ -568,7 +563,7 @@ __global__ __launch_bounds__(256) void gather_split_kernel(BankDev b, int64_t n_
     if (lane == leader) base = atomicAdd(count, (unsigned long long)__popcll(mask));
     base = (unsigned long long)__shfl((long long)base, leader);
     if (collided) {
-        const int64_t j = (int64_t)(base + (unsigned long long)lane_rank(mask));
+        const int64_t j = (int64_t)(base + (unsigned long long)rank_in(mask));
         ltau[j] = lt;
         cc[j] = c;
         yin[j] = y;
@@ -694,7 +689,6 @@ struct gmc_world {
     ProblemDev *prob = nullptr;
     unsigned long long *counters = nullptr;   // [2][1 + max_problems]: n_alive, per-problem
     unsigned long long *host_counters = nullptr;
-    unsigned long long *queue = nullptr;      // the analog walk's work counter (this world's own)
     // captured transport steps, one per (sampler, model, K, integrator, bank parity, bucket)
     struct StepGraph {
         int sampler, K, integrator, cur, ff, xy;
@@ -790,7 +784,6 @@ void plan(gmc_world *w, Layout &L)
     L.add((void **)&w->rej_n, 8 * N);
     L.add((void **)&w->prob, sizeof(ProblemDev) * P);
     L.add((void **)&w->counters, 8 * 2 * (1 + P));
-    L.add((void **)&w->queue, 8);
 }
 
 int sync_counters(gmc_world *w, int which, hipStream_t s)
@@ -1017,8 +1010,15 @@ int gmc_world_inject(gmc_world *w, int32_t pid, uint64_t h_begin, int64_t count,
             hipLaunchKernelGGL(surface_birth_kernel, dim3(blocks_for(count)), dim3(256), 0, s, w->cells(),
                                pid, (uint32_t)h_begin, count, w->bank[which], ctr, ctr + 1);
         } else if (!w->src_model) {
-            hipLaunchKernelGGL(birth_kernel, dim3(blocks_for(count)), dim3(256), 0, s, w->cells(), pid,
-                               (uint32_t)h_begin, count, w->bank[which], ctr, ctr + 1);
+            const int cu = device_cu_count();
+            if (cu <= 0) return set_error(GMC_EDEVICE, "gmc_world_inject: cannot query the device");
+            const dim3 grid(walk_grid(count, cu));
+            if (w->xyg[pid])
+                hipLaunchKernelGGL(birth_walk_kernel<true>, grid, dim3(256), 0, s, w->cells(), pid, (uint32_t)h_begin,
+                                   count, w->e_face, w->e_pos, w->e_dcos, w->e_dsin, w->e_path);
+            else
+                hipLaunchKernelGGL(birth_walk_kernel<false>, grid, dim3(256), 0, s, w->cells(), pid, (uint32_t)h_begin,
+                                   count, w->e_face, w->e_pos, w->e_dcos, w->e_dsin, w->e_path);
         } else {
             hipLaunchKernelGGL(source_kernel, dim3(blocks_for(count)), dim3(256), 0, s, w->cells(), pid,
                                (uint32_t)h_begin, count, w->c_ltau, w->c_c, w->c_x, w->c_yin, w->c_cos,
@@ -1050,10 +1050,11 @@ int gmc_world_inject(gmc_world *w, int32_t pid, uint64_t h_begin, int64_t count,
             if (cu <= 0) return set_error(GMC_EDEVICE, "gmc_world_inject: cannot query the device");
             hipError_t e = launch_mlp_ode(m->precision, m->hidden, p, cu, s);
             if (e != hipSuccess) return set_hip_error(e, "gmc_world_inject: internal sampler");
-            hipLaunchKernelGGL(source_apply_kernel, dim3(blocks_for(count)), dim3(256), 0, s, w->cells(), pid,
+        }
+        if (w->src_face[pid] < 0)
+            hipLaunchKernelGGL(birth_apply_kernel, dim3(blocks_for(count)), dim3(256), 0, s, w->cells(), pid,
                                (uint32_t)h_begin, count, w->e_face, w->e_pos, w->e_dcos, w->e_dsin,
                                w->e_path, w->bank[which], ctr, ctr + 1);
-        }
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return set_hip_error(e, "gmc_world_inject: launch");
         const int rc = sync_counters(w, which, s);
@@ -1199,7 +1200,6 @@ int enqueue_step(gmc_world *w, int sampler, const gmc_model *m, int K, hipStream
         p.n = n_launch;
         p.n_dev = n_dev;
         p.mode = GMC_MODE_CONTINUOUS;
-        p.queue = w->queue;
         e = launch_walk(p, walk_grid(n_launch, cu), s);
     }
     if (e != hipSuccess) return set_hip_error(e, "gmc_transport_step: sampler");
