@@ -81,15 +81,14 @@ __device__ __forceinline__ void normal5(uint64_t seed, uint64_t id, float z[5])
     }
 }
 
-// Rotation of a direction by k quarter turns counter-clockwise.
+// Rotation of a direction by k quarter turns counter-clockwise: (a, b), (-b, a), (-a, -b), (b, -a);
+// selects and sign flips, as the lanes of a wave hold every k.
 __device__ __forceinline__ void rot_quarter(int k, float a, float b, float &ra, float &rb)
 {
-    switch (k & 3) {
-    case 0: ra = a; rb = b; break;
-    case 1: ra = -b; rb = a; break;
-    case 2: ra = -a; rb = -b; break;
-    default: ra = b; rb = -a; break;
-    }
+    const bool swap = (k & 1) != 0;
+    const uint32_t p = __builtin_bit_cast(uint32_t, swap ? b : a), q = __builtin_bit_cast(uint32_t, swap ? a : b);
+    ra = __builtin_bit_cast(float, p ^ ((uint32_t)((k + 1) & 2) << 30));
+    rb = __builtin_bit_cast(float, q ^ ((uint32_t)(k & 2) << 30));
 }
 
 // Exit record from x_K (paper eq. 11 in the 5-dim reading): face = number of the thresholds
@@ -161,33 +160,30 @@ __device__ __forceinline__ int decode_exit(float a0, float a1, float a2, float a
 // First-flight split of a canonical transmission: the entry ray from (0, y) along (u, v) meets
 // the boundary of [0, wa] x [0, 1] after d_b; with flights ~ Exp(c tau) (eq. 4, continuous
 // absorption) the particle crosses without a collision with probability exp(-c tau d_b).  The
-// decision compares that probability with xi = u01(word 0) of Philox(key, (id lo, id hi, 0,
-// split tag)); an uncollided particle leaves at the ray's end with its entry direction and path
+// decision compares that probability with xi, u01(word 0) of Philox(key, (id lo, id hi, 0,
+// split tag)) (split_draw); an uncollided particle leaves at the ray's end with its entry direction and path
 // d_b (written to e).  Returns true for an uncollided crossing.
+__device__ __forceinline__ float split_draw(uint64_t key, uint64_t id)
+{
+    return u01(draw4(key, id, 0u, kTagSplit).a);
+}
+
 __device__ __forceinline__ bool uncollided_exit(float tau, float c, float y, float u, float v, float wa,
-                                                uint64_t key, uint64_t id, Exit &e)
+                                                float xi, Exit &e)
 {
     const float kInf = __builtin_inff();
     const float tx = u > 0.0f ? wa / u : kInf;
-    float ty = kInf;
-    if (v > 0.0f) ty = (1.0f - y) / v;
-    else if (v < 0.0f) ty = -y / v;
+    const float ty = fabsf(v) > 0.0f ? (v > 0.0f ? 1.0f - y : -y) / v : kInf;
     const bool xface = tx <= ty;
     const float db = xface ? tx : ty;
     const float pu = expf(-c * tau * db);
-    const U4 r = draw4(key, id, 0u, kTagSplit);
-    if (!(u01(r.a) <= pu)) return false;
+    if (!(xi <= pu)) return false;
     e.u = u;
     e.v = v;
     e.path = db;
-    if (xface) {
-        e.face = 1;
-        e.pos = fminf(fmaxf(y + db * v, 0.0f), 1.0f);
-    } else {
-        const float xe = fminf(fmaxf(db * u, 0.0f), wa);
-        e.face = v > 0.0f ? 2 : 0;
-        e.pos = v > 0.0f ? (wa - xe) / wa : xe / wa;
-    }
+    const float xe = fminf(fmaxf(db * u, 0.0f), wa), xr = v > 0.0f ? wa - xe : xe;
+    e.face = xface ? 1 : (v > 0.0f ? 2 : 0);
+    e.pos = xface ? fminf(fmaxf(y + db * v, 0.0f), 1.0f) : (wa == 1.0f ? xr : xr / wa);
     return true;
 }
 

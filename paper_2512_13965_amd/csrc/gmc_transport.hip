@@ -60,10 +60,16 @@ struct BankDev {
 // or sum of w l / V where sigma_a = 0) and is formed when the tallies are read.
 constexpr int kVisitTallies = 4;
 
+// Material of a cell as a crossing needs it: the sampler's conditions ln tau and c in FP32, and
+// sigma_a = (1 - c) tau / L for the tallies.
+struct CellMat {
+    float lt, c;
+    double siga;
+};
+
 struct CellsDev {
     const double *tau, *c;         // per global cell (births)
-    const double *siga;            // per global cell: sigma_a = (1 - c) tau / L
-    const float *ltau, *cf;        // per global cell (FP32: sampler conditions)
+    const CellMat *mat;            // per global cell
     double *visit;                 // [cells][kVisitTallies]
     double *leak, *cutoff;
     // weight and number of generative samples rejected by the decoder (a part of the cutoff)
@@ -137,14 +143,29 @@ __device__ __forceinline__ void tally_flush(TallyTable<SLOTS> &tl, const CellsDe
 // with the physical path (path_units in units of `unit`, the length of the face the walk's frame
 // took as its height), plus the path tallies w l, l and one visit.
 template <int SLOTS>
-__device__ __forceinline__ double visit_tally(const CellsDev &cd, int cell, double w, float path_units, double unit,
-                                              TallyTable<SLOTS> &tl)
+__device__ __forceinline__ double visit_tally(const CellsDev &cd, int cell, double sig_a, double w, float path_units,
+                                              double unit, TallyTable<SLOTS> &tl)
 {
-    const double sig_a = cd.siga[cell];
     const double ls = (double)path_units * unit;
     const double dw = sig_a > 0.0 ? w * (-expm1(-sig_a * ls)) : 0.0;
     tally_add(tl, cd, cell, dw, w * ls, ls);
     return w - dw;
+}
+
+// The first-flight split's xi of one particle's cell visits (split_draw of stream hist + 2^32 visit):
+// only the second counter word, the visit, changes, so two Philox rounds' other halves are the
+// particle's own.
+__device__ __forceinline__ DrawPrefix split_prefix(uint32_t hist, uint32_t k0, uint32_t k1)
+{
+    const uint64_t p0 = (uint64_t)kPhiloxM0 * hist;
+    const uint64_t p1 = (uint64_t)kPhiloxM1 * ((uint32_t)(p0 >> 32) ^ kTagSplit ^ k1);
+    return DrawPrefix{k0, (uint32_t)(p1 >> 32) ^ (k0 + kPhiloxW0), (uint32_t)p1, (uint32_t)p0 ^ (k1 + kPhiloxW1)};
+}
+
+__device__ __forceinline__ float split_draw(const DrawPrefix &q, uint32_t k0, uint32_t k1, uint32_t visit)
+{
+    const uint64_t g = (uint64_t)kPhiloxM0 * (visit ^ q.a);
+    return u01(philox_rest(q.b, q.c, (uint32_t)(g >> 32) ^ q.d, (uint32_t)g, k0, k1).a);
 }
 
 struct Next {
@@ -157,7 +178,7 @@ struct Next {
 // with global direction (gx, gy) and weight w_out: cut off, leak, reflect or enter the
 // neighbour (whose entry face is the opposite one, entered at position 1 - pos in its own
 // counter-clockwise orientation, i.e. canonical height y = pos).
-__device__ __forceinline__ Next move_on(const CellsDev &cd, const ProblemDev &P, int cell, int face,
+__device__ __forceinline__ Next move_on(const CellsDev &cd, const ProblemDev &P, int cell, int &ci, int &cj, int face,
                                         float pos, float gx, float gy, double w_out)
 {
     Next nx{cell, 0, 0.0f, gx, gy, false};
@@ -173,13 +194,7 @@ __device__ __forceinline__ Next move_on(const CellsDev &cd, const ProblemDev &P,
         atomicAdd(&cd.cutoff[cell], w_out);
         return nx;
     }
-    const uint32_t local = (uint32_t)(cell - P.cell0);
-    const int cj = (int)(local / (uint32_t)P.nx), ci = (int)(local - (uint32_t)cj * (uint32_t)P.nx);
-    int ni = ci, nj = cj;
-    if (face == 0) nj -= 1;
-    else if (face == 1) ni += 1;
-    else if (face == 2) nj += 1;
-    else ni -= 1;
+    const int ni = ci + (face == 1) - (face == 3), nj = cj + (face == 2) - (face == 0);
     if (ni < 0 || nj < 0 || ni >= P.nx || nj >= P.ny) {
         if (!P.reflect) {
             atomicAdd(&cd.leak[cell], w_out);
@@ -193,9 +208,19 @@ __device__ __forceinline__ Next move_on(const CellsDev &cd, const ProblemDev &P,
         nx.cell = (int32_t)(P.cell0 + (int64_t)nj * P.nx + ni);
         nx.entry = (face + 2) & 3;
         nx.yin = pos;
+        ci = ni;
+        cj = nj;
     }
     nx.alive = true;
     return nx;
+}
+
+__device__ __forceinline__ Next move_on(const CellsDev &cd, const ProblemDev &P, int cell, int face, float pos,
+                                        float gx, float gy, double w_out)
+{
+    const uint32_t local = (uint32_t)(cell - P.cell0);
+    int cj = (int)(local / (uint32_t)P.nx), ci = (int)(local - (uint32_t)cj * (uint32_t)P.nx);
+    return move_on(cd, P, cell, ci, cj, face, pos, gx, gy, w_out);
 }
 
 // What a workgroup's append shares: survivors of each wave and their first index, and the
@@ -387,8 +412,9 @@ __global__ __launch_bounds__(256) void source_kernel(CellsDev cd, int32_t pid, u
     const int ci = P.sx0 + (int)(pick % (uint32_t)P.snx), cj = P.sy0 + (int)(pick / (uint32_t)P.snx);
     const int cell = (int)(P.cell0 + (int64_t)cj * P.nx + ci);
     const float ph = u01(r.d);
-    ltau[t] = cd.ltau[cell];
-    cc[t] = cd.cf[cell];
+    const CellMat m = cd.mat[cell];
+    ltau[t] = m.lt;
+    cc[t] = m.c;
     xb[t] = u01_open(r.b);
     yb[t] = u01_open(r.c);
     cosb[t] = cos_turns(ph);
@@ -425,7 +451,7 @@ __global__ __launch_bounds__(kTallyThreads) void birth_apply_kernel(CellsDev cd,
             const uint32_t pick = __umulhi(r.a, nsrc);
             const int ci = P.sx0 + (int)(pick % (uint32_t)P.snx), cj = P.sy0 + (int)(pick / (uint32_t)P.snx);
             const int cell = (int)(P.cell0 + (int64_t)cj * P.nx + ci);
-            w_out = visit_tally(cd, cell, 1.0, path[t], P.Ly, tl);
+            w_out = visit_tally(cd, cell, cd.mat[cell].siga, 1.0, path[t], P.Ly, tl);
             nx = move_on(cd, P, cell, face_c[t], pos[t], dcos[t], dsin[t], w_out);
             alive = nx.alive;
         }
@@ -435,184 +461,257 @@ __global__ __launch_bounds__(kTallyThreads) void birth_apply_kernel(CellsDev cd,
     tally_flush(tl, cd);
 }
 
-// Stage 1: canonical conditions of every alive particle.  Entry face e maps to the canonical
-// left face by the rotation of k = (e + 1) mod 4 quarter turns (canonical -> local).
+// Where stage 1 leaves the canonical conditions of the particles to sample.
+struct CondDev {
+    float *ltau, *cc, *yin, *sth, *laspect, *omx;
+    uint64_t *ids, *keys;
+};
+
+// Stage 1 of one particle: its canonical conditions.  Entry face e maps to the canonical left face
+// by the rotation of k = (e + 1) mod 4 quarter turns (canonical -> local).
 // The canonical cell takes the entry face as its height: left and right faces have length Ly,
 // bottom and top length L, so entries through a vertical face see tau * Ly / L and aspect
 // A = L / Ly, entries through a horizontal face tau and A = Ly / L.
-__global__ __launch_bounds__(256) void gather_kernel(BankDev b, int64_t n_arg,
-                                                     const unsigned long long *n_dev, CellsDev cd,
-                                                     float *ltau, float *cc, float *yin, float *sth,
-                                                     float *laspect, float *omx, uint64_t *ids,
-                                                     uint64_t *keys)
+struct Canonical {
+    float lt, la, c, s, ox;
+};
+
+__device__ __forceinline__ Canonical canonical(const CellMat &m, float lr, int e, float gx, float gy)
+{
+    const int k = (e + 1) & 3;
+    float U, V;
+    rot_quarter((4 - k) & 3, gx, gy, U, V);
+    return Canonical{(e & 1) ? m.lt + lr : m.lt, (e & 1) ? -lr : lr, m.c, fminf(fmaxf(V, -1.0f), 1.0f), U};
+}
+
+// Conditions of particle i of the bank to place j.
+__device__ __forceinline__ void put_conditions(const BankDev &b, int64_t i, const CellsDev &cd, const CondDev &o,
+                                               int64_t j)
+{
+    const ProblemDev &P = cd.prob[b.pid[i]];
+    const Canonical q = canonical(cd.mat[b.cell[i]], P.lr, b.entry[i], b.gx[i], b.gy[i]);
+    o.ltau[j] = q.lt;
+    o.laspect[j] = q.la;
+    o.omx[j] = q.ox;                     // read only in XY geometry
+    o.cc[j] = q.c;
+    o.yin[j] = b.yin[i];
+    o.sth[j] = q.s;
+    o.ids[j] = (uint64_t)b.hist[i] | ((uint64_t)b.event[i] << 32);
+    o.keys[j] = P.seed;
+}
+
+// Stage 1: canonical conditions of every alive particle.
+__global__ __launch_bounds__(256) void gather_kernel(BankDev b, int64_t n_arg, const unsigned long long *n_dev,
+                                                     CellsDev cd, CondDev o)
 {
     const int64_t n = n_dev ? (int64_t)*n_dev : n_arg;
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    const int cell = b.cell[i];
-    const int e = b.entry[i];
-    const int k = (e + 1) & 3;
-    float U, V;
-    rot_quarter((4 - k) & 3, b.gx[i], b.gy[i], U, V);
-    const float lr = cd.prob[b.pid[i]].lr;
-    ltau[i] = (e & 1) ? cd.ltau[cell] + lr : cd.ltau[cell];
-    laspect[i] = (e & 1) ? -lr : lr;
-    omx[i] = U;                          // read only in XY geometry
-    cc[i] = cd.cf[cell];
-    yin[i] = b.yin[i];
-    sth[i] = fminf(fmaxf(V, -1.0f), 1.0f);
-    ids[i] = (uint64_t)b.hist[i] | ((uint64_t)b.event[i] << 32);
-    keys[i] = cd.prob[b.pid[i]].seed;
+    if (i < n) put_conditions(b, i, cd, o, i);
 }
 
-// Exit-record face of a particle whose history ended inside the split gather: the apply stage
-// leaves it out.
-constexpr int32_t kFaceEnded = -1000;
+// Exit-record faces the split gather leaves for the apply stage: the particle's history ended in
+// it; its crossing is collided, the exit record is the sampler's at the particle's slot.
+constexpr int32_t kFaceEnded = -1000, kFaceCollided = -1001;
 
 // Stage 1 with the first-flight split (models fitted on collided exits, blob flag bit 1).  Each
 // particle draws its crossing's split (uncollided_exit, keyed by history and cell visit); while
 // the crossings stay uncollided it is streamed through up to ff_max cells inside this kernel:
 // stages 3-4 of each such crossing (FP64 attenuation and tallies, staged in the workgroup's LDS
-// table with bounded probing, and the move to the neighbour) exactly as the apply stage would
-// do them with the same random numbers, its bank slot then updated in place.  The crossing that ends the loop is
-//   * collided: canonical conditions compacted (one atomic per wave) into the sampler's staging
-//     with the bank index in sidx;
+// table, and the move to the neighbour) exactly as the apply stage would do them with the same
+// random numbers, its bank slot then updated in place.  The crossing that ends the loop is
+//   * collided: face kFaceCollided, canonical conditions compacted into the sampler's staging,
+//     their place in `slot`;
 //   * the ff_max-th uncollided one: its exit record written at the particle's own index, for
 //     the apply stage;
 //   * one that ended the history (leak, cutoff): face kFaceEnded.
 // ff_max = 1 is one crossing per particle per step.  `streamed` counts the crossings finished here.
-__global__ __launch_bounds__(256) void gather_split_kernel(BankDev b, int64_t n_arg,
-                                                           const unsigned long long *n_dev, CellsDev cd,
-                                                           float *ltau, float *cc, float *yin, float *sth,
-                                                           float *laspect, float *omx, uint64_t *ids,
-                                                           uint64_t *keys, int32_t *sidx,
-                                                           unsigned long long *count, int32_t *e_face,
-                                                           float *e_pos, float *e_dcos, float *e_dsin,
-                                                           float *e_path, int ff_max,
-                                                           unsigned long long *streamed)
+//
+// How many crossings a particle streams through varies (geometric: on the lattice 16 in the mean,
+// the longest of 64 lanes about 60), so lanes are not bound to particles: a workgroup takes its
+// share (BlockShare) through a counter in LDS, and a wave stops for new particles when
+// kStreamRefill of its lanes idle.  One workgroup per CU with a table of 4,096 cells (147 KB): what
+// spills over such a table goes out as scattered FP64 atomics (0.055 ns each on the whole
+// chip), which bounded the kernel with a table of 1,024 and three workgroups per CU.  A step then
+// takes as long as its longest streams, 64 crossings of 1.5 us (instructions in sequence).
+// Measured, 2 10^5 particles on the lattice: 549 us with one particle to a lane and the smaller
+// table, 240 us; the mean over a run's 30 steps 172 -> 104 us (1,024 threads 125, 256 threads 123,
+// two workgroups of half the table 139; idle lanes to refill 8 / 16 / 32 the same).
+// ONE: all particles belong to problem `only`, whose description then stays in scalar registers
+// (otherwise a lane holds its particle's).
+constexpr int kStreamThreads = 512;
+constexpr int kStreamBlocksPerCu = 1;
+constexpr int kStreamRefill = 16;
+using TallyStream = TallyTable<4096>;
+
+template <bool ONE>
+__global__ __launch_bounds__(kStreamThreads) void gather_split_kernel(BankDev b, int64_t n_arg,
+                                                                      const unsigned long long *n_dev, CellsDev cd,
+                                                                      CondDev o, int32_t *slot,
+                                                                      unsigned long long *count, int32_t *e_face,
+                                                                      float *e_pos, float *e_dcos, float *e_dsin,
+                                                                      float *e_path, int ff_max, int32_t only,
+                                                                      unsigned long long *streamed)
 {
-    __shared__ TallyTable<1024> tl;
+    __shared__ TallyStream tl;
+    __shared__ uint32_t pool, beyond, waves[kStreamThreads / 64];
+    __shared__ unsigned long long first;
     tally_init(tl);
-    __syncthreads();
-    const int64_t n = n_dev ? (int64_t)*n_dev : n_arg;
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const int lane = threadIdx.x & 63;
-    bool collided = false;
-    float lt = 0.f, c = 0.f, y = 0.f, s = 0.f, la = 0.f, ox = 0.f;
-    uint64_t id = 0, key = 0;
-    uint32_t nstream = 0;
-    bool ended = false;
-    if (i < n) {
-        int cell = b.cell[i];
-        int e = b.entry[i];
-        float gx = b.gx[i], gy = b.gy[i], yy = b.yin[i];
-        double w = b.w[i];
-        uint32_t ev = b.event[i];
-        const uint32_t hist = b.hist[i];
-        const ProblemDev P = cd.prob[b.pid[i]];
-        for (int it = 0;; ++it) {
-            const int k = (e + 1) & 3;
-            float U, V;
-            rot_quarter((4 - k) & 3, gx, gy, U, V);
-            lt = (e & 1) ? cd.ltau[cell] + P.lr : cd.ltau[cell];
-            la = (e & 1) ? -P.lr : P.lr;
-            c = cd.cf[cell];
-            y = yy;
-            s = fminf(fmaxf(V, -1.0f), 1.0f);
-            ox = U;
-            id = (uint64_t)hist | ((uint64_t)ev << 32);
-            key = P.seed;
-            const float u = P.xy ? U : sqrtf(fmaxf(1.0f - s * s, 0.0f));
-            Exit ex;
-            if (!uncollided_exit(expf(lt), c, y, u, s, la == 0.0f ? 1.0f : expf(la), key, id, ex)) {
-                collided = true;
-                break;
-            }
-            if (it + 1 >= ff_max) {
-                e_face[i] = ex.face;
-                e_pos[i] = ex.pos;
-                e_dcos[i] = ex.u;
-                e_dsin[i] = ex.v;
-                e_path[i] = ex.path;
-                break;
-            }
-            const double w_out = visit_tally(cd, cell, w, ex.path, (e & 1) ? P.Ly : P.L, tl);
-            float ngx, ngy;
-            rot_quarter(k, ex.u, ex.v, ngx, ngy);
-            Next nx = move_on(cd, P, cell, (ex.face + k) & 3, ex.pos, ngx, ngy, w_out);
-            if (nx.alive && ev + 1 >= P.max_visits) {
-                atomicAdd(&cd.cutoff[cell], w_out);
-                nx.alive = false;
-            }
-            ++nstream;
-            if (!nx.alive) {
-                e_face[i] = kFaceEnded;
-                ended = true;
-                break;
-            }
-            cell = nx.cell;
-            e = nx.entry;
-            yy = nx.yin;
-            gx = nx.gx;
-            gy = nx.gy;
-            w = w_out;
-            ++ev;
-        }
-        if (nstream > 0 && !ended) {
-            b.cell[i] = cell;
-            b.entry[i] = e;
-            b.yin[i] = yy;
-            b.gx[i] = gx;
-            b.gy[i] = gy;
-            b.w[i] = w;
-            b.event[i] = ev;
-        }
+    if (threadIdx.x == 0) {
+        pool = 0;
+        beyond = 0;
     }
     __syncthreads();
-    tally_flush(tl, cd);
-    // crossings beyond the one per particle that the step counts (a history that ended here
-    // finished its step's own crossing inside the loop)
-    uint32_t tot = ended ? nstream - 1 : nstream;
+    const int64_t n = n_dev ? (int64_t)*n_dev : n_arg;
+    const BlockShare mine(n);
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    // lanes of a wave that take a particle: where there are few, every wave gets its share
+    const uint32_t share = (mine.items + kStreamThreads / 64 - 1) / (kStreamThreads / 64);
+    const int lanes = share < 64 ? (int)share : 64;
+
+    bool active = false, held = false;
+    int64_t i = 0;
+    ProblemDev P = cd.prob[ONE ? only : 0];
+    int cell = 0, ci = 0, cj = 0, e = 0;
+    float gx = 0.0f, gy = 0.0f, yy = 0.0f;
+    double w = 0.0;
+    uint32_t ev = 0, hist = 0, passed = 0, tot = 0;
+    int32_t fate = 0;
+    DrawPrefix q{};
+    bool dry = mine.items == 0;
+    for (;;) {
+        if (held && !active) {               // the particle's streaming is over
+            if (fate != 0) e_face[i] = fate;
+            if (passed > 0 && fate != kFaceEnded) {
+                b.cell[i] = cell;
+                b.entry[i] = e;
+                b.yin[i] = yy;
+                b.gx[i] = gx;
+                b.gy[i] = gy;
+                b.w[i] = w;
+                b.event[i] = ev;
+            }
+            // crossings beyond the one per particle that the step counts (a history that ended
+            // here finished its step's own crossing in the loop)
+            tot += fate == kFaceEnded ? passed - 1 : passed;
+            held = false;
+        }
+        const uint64_t needs = __ballot(!active && lane < lanes);
+        if (!dry) {
+            const uint32_t cnt = (uint32_t)__popcll(needs);
+            uint32_t at = 0;
+            if (lane == 0) at = atomicAdd(&pool, cnt);
+            at = (uint32_t)__builtin_amdgcn_readfirstlane((int)at);
+            dry = at >= mine.items || mine.items - at <= cnt;
+            const uint32_t item = at + (uint32_t)rank_in(needs);
+            if (!active && lane < lanes && at < mine.items && item < mine.items) {
+                i = mine.index(item);
+                if (i < n) {
+                    if constexpr (!ONE) P = cd.prob[b.pid[i]];
+                    cell = b.cell[i];
+                    e = b.entry[i];
+                    gx = b.gx[i];
+                    gy = b.gy[i];
+                    yy = b.yin[i];
+                    w = b.w[i];
+                    ev = b.event[i];
+                    hist = b.hist[i];
+                    const uint32_t local = (uint32_t)(cell - P.cell0);
+                    cj = (int)(local / (uint32_t)P.nx);
+                    ci = (int)(local - (uint32_t)cj * (uint32_t)P.nx);
+                    q = split_prefix(hist, (uint32_t)P.seed, (uint32_t)(P.seed >> 32));
+                    passed = 0;
+                    active = held = true;
+                }
+            }
+        }
+        int live = __popcll(__ballot(active));
+        if (live == 0) {
+            if (dry) break;
+            continue;
+        }
+        const int stop = dry ? 0 : lanes - kStreamRefill;
+        for (int it = 0; live > 0 && (live > stop || it == 0); ++it) {
+            if (active) {
+                const CellMat m = cd.mat[cell];
+                const Canonical a = canonical(m, P.lr, e, gx, gy);
+                const float u = P.xy ? a.ox : sqrtf(fmaxf(1.0f - a.s * a.s, 0.0f));
+                const float xi = split_draw(q, (uint32_t)P.seed, (uint32_t)(P.seed >> 32), ev);
+                Exit ex;
+                const float wa = P.lr == 0.0f ? 1.0f : expf(a.la);
+                if (!uncollided_exit(expf(a.lt), a.c, yy, u, a.s, wa, xi, ex)) {
+                    active = false;
+                    fate = kFaceCollided;
+                } else if (passed + 1 >= (uint32_t)ff_max) {
+                    e_face[i] = ex.face;
+                    e_pos[i] = ex.pos;
+                    e_dcos[i] = ex.u;
+                    e_dsin[i] = ex.v;
+                    e_path[i] = ex.path;
+                    active = false;
+                    fate = 0;
+                } else {
+                    const int k = (e + 1) & 3;
+                    const double w_out = visit_tally(cd, cell, m.siga, w, ex.path, (e & 1) ? P.Ly : P.L, tl);
+                    float ngx, ngy;
+                    rot_quarter(k, ex.u, ex.v, ngx, ngy);
+                    const Next nx = move_on(cd, P, cell, ci, cj, (ex.face + k) & 3, ex.pos, ngx, ngy, w_out);
+                    ++passed;
+                    if (nx.alive && ev + 1 >= P.max_visits) {
+                        atomicAdd(&cd.cutoff[cell], w_out);
+                        active = false;
+                    }
+                    if (!nx.alive) active = false;
+                    if (!active) fate = kFaceEnded;
+                    cell = nx.cell;
+                    e = nx.entry;
+                    yy = nx.yin;
+                    gx = nx.gx;
+                    gy = nx.gy;
+                    w = w_out;
+                    ++ev;
+                }
+            }
+            live = __popcll(__ballot(active));
+        }
+    }
 #pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) tot += (uint32_t)__shfl_xor((int)tot, o);
-    if (lane == 0 && tot > 0) atomicAdd(streamed, (unsigned long long)tot);
-    const uint64_t mask = __ballot(collided);
-    if (!mask) return;
-    const int leader = __ffsll((unsigned long long)mask) - 1;
-    unsigned long long base = 0;
-    if (lane == leader) base = atomicAdd(count, (unsigned long long)__popcll(mask));
-    base = (unsigned long long)__shfl((long long)base, leader);
-    if (collided) {
-        const int64_t j = (int64_t)(base + (unsigned long long)rank_in(mask));
-        ltau[j] = lt;
-        cc[j] = c;
-        yin[j] = y;
-        sth[j] = s;
-        laspect[j] = la;
-        omx[j] = ox;
-        ids[j] = id;
-        keys[j] = key;
-        sidx[j] = (int32_t)i;
+    for (int m = 32; m >= 1; m >>= 1) tot += (uint32_t)__shfl_xor((int)tot, m);
+    if (lane == 0 && tot > 0) atomicAdd(&beyond, tot);
+    __syncthreads();                         // also: the bank's and e_face's new values
+    if (threadIdx.x == 0 && beyond > 0) atomicAdd(streamed, (unsigned long long)beyond);
+    tally_flush(tl, cd);
+    // the collided particles of this share to the sampler's staging, one atomic per workgroup tile
+    for (uint32_t v0 = 0; v0 < mine.items; v0 += kStreamThreads) {
+        const uint32_t v = v0 + threadIdx.x;
+        const int64_t p = v < mine.items ? mine.index(v) : n;
+        const bool take = p < n && e_face[p] == kFaceCollided;
+        const uint64_t mask = __ballot(take);
+        if (lane == 0) waves[wave] = (uint32_t)__popcll(mask);
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            uint32_t total = 0;
+            for (int k = 0; k < kStreamThreads / 64; ++k) {
+                const uint32_t c = waves[k];
+                waves[k] = total;
+                total += c;
+            }
+            first = total ? atomicAdd(count, (unsigned long long)total) : 0ull;
+        }
+        __syncthreads();
+        if (take) {
+            const int64_t j = (int64_t)(first + waves[wave]) + rank_in(mask);
+            put_conditions(b, p, cd, o, j);
+            slot[p] = (int32_t)j;
+        }
+        __syncthreads();
     }
 }
 
-// The sampler's exits of the compacted collided particles back to their bank indices.
-__global__ __launch_bounds__(256) void scatter_kernel(int64_t n_arg, const unsigned long long *count,
-                                                      const int32_t *sidx, const int32_t *f2, const float *p2,
-                                                      const float *c2, const float *s2, const float *l2,
-                                                      int32_t *face, float *pos, float *dcos, float *dsin,
-                                                      float *path)
-{
-    const int64_t n = (int64_t)*count;
-    const int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (j >= n || j >= n_arg) return;
-    const int32_t i = sidx[j];
-    face[i] = f2[j];
-    pos[i] = p2[j];
-    dcos[i] = c2[j];
-    dsin[i] = s2[j];
-    path[i] = l2[j];
-}
+// Exit records of the split's collided particles, at their slots.
+struct ExitDev {
+    const int32_t *face;
+    const float *pos, *dcos, *dsin, *path;
+};
 
 // Stages 3-4 for every alive particle, survivors compacted into `out`.  Bound by its global atomics
 // (5 a cell of a workgroup's table and 2 a wave of survivors in an earlier form): 10^6 particles on
@@ -621,8 +720,8 @@ __global__ __launch_bounds__(kTallyThreads) void apply_kernel(BankDev in, int64_
                                                               const unsigned long long *n_dev,
                                                               const int32_t *face_c, const float *pos,
                                                               const float *dcos, const float *dsin,
-                                                              const float *path, CellsDev cd, BankDev out,
-                                                              unsigned long long *counter,
+                                                              const float *path, const int32_t *slot, ExitDev split,
+                                                              CellsDev cd, BankDev out, unsigned long long *counter,
                                                               unsigned long long *pcount)
 {
     __shared__ TallyLds tl;
@@ -638,18 +737,32 @@ __global__ __launch_bounds__(kTallyThreads) void apply_kernel(BankDev in, int64_
         double w_out = 0.0;
         int32_t pid = 0;
         uint32_t hist = 0, event = 0;
-        if (i < n && face_c[i] != kFaceEnded) {
+        int fc = i < n ? face_c[i] : kFaceEnded;
+        if (fc != kFaceEnded) {
+            float ps, dc, ds, pl;
+            if (fc == kFaceCollided) {       // the sampler's exit of the particle's slot
+                const int64_t j = slot[i];
+                fc = split.face[j];
+                ps = split.pos[j];
+                dc = split.dcos[j];
+                ds = split.dsin[j];
+                pl = split.path[j];
+            } else {
+                ps = pos[i];
+                dc = dcos[i];
+                ds = dsin[i];
+                pl = path[i];
+            }
             pid = in.pid[i];
             const ProblemDev P = cd.prob[pid];
             const int cell = in.cell[i];
             const int k = (in.entry[i] + 1) & 3;
             hist = in.hist[i];
             event = in.event[i] + 1;
-            w_out = visit_tally(cd, cell, in.w[i], path[i], (in.entry[i] & 1) ? P.Ly : P.L, tl);
-            const int fc = face_c[i];
+            w_out = visit_tally(cd, cell, cd.mat[cell].siga, in.w[i], pl, (in.entry[i] & 1) ? P.Ly : P.L, tl);
             float gx, gy;
-            rot_quarter(k, dcos[i], dsin[i], gx, gy);
-            nx = move_on(cd, P, cell, fc >= 0 ? (fc + k) & 3 : fc, pos[i], gx, gy, w_out);
+            rot_quarter(k, dc, ds, gx, gy);
+            nx = move_on(cd, P, cell, fc >= 0 ? (fc + k) & 3 : fc, ps, gx, gy, w_out);
             if (nx.alive && event >= P.max_visits) {
                 atomicAdd(&cd.cutoff[cell], w_out);
                 nx.alive = false;
@@ -710,8 +823,8 @@ struct gmc_world {
     float *c_x = nullptr, *c_cos = nullptr;      // internal-model births
     float *c_la = nullptr;                       // canonical ln aspect (rectangular cells)
     float *c_ox = nullptr;                       // canonical in-plane x direction (XY geometry)
-    // first-flight split: bank index of each compacted collided particle, their exits, count
-    int32_t *s_idx = nullptr, *s_face = nullptr;
+    // first-flight split: place of each collided particle among the compacted ones, their exits, count
+    int32_t *s_slot = nullptr, *s_face = nullptr;
     float *s_pos = nullptr, *s_dcos = nullptr, *s_dsin = nullptr, *s_path = nullptr;
     unsigned long long *s_count = nullptr;
     unsigned long long *n_large = nullptr;       // sampler's device-side tile choice (two count handoffs)
@@ -723,8 +836,8 @@ struct gmc_world {
     float *e_pos = nullptr, *e_dcos = nullptr, *e_dsin = nullptr, *e_path = nullptr;
     // cells and tallies
     double *tau = nullptr, *c = nullptr;
-    float *ltau = nullptr, *cf = nullptr;
-    double *siga = nullptr, *visit = nullptr, *leak = nullptr, *cutoff = nullptr, *rej_w = nullptr, *rej_n = nullptr;
+    CellMat *mat = nullptr;
+    double *visit = nullptr, *leak = nullptr, *cutoff = nullptr, *rej_w = nullptr, *rej_n = nullptr;
     ProblemDev *prob = nullptr;
     unsigned long long *counters = nullptr;   // [2][1 + max_problems]: n_alive, per-problem
     unsigned long long *host_counters = nullptr;
@@ -752,7 +865,7 @@ struct gmc_world {
     std::mutex mu;
 
     unsigned long long *cnt(int which) { return counters + (size_t)which * (1 + max_problems); }
-    CellsDev cells() const { return CellsDev{tau, c, siga, ltau, cf, visit, leak, cutoff, rej_w, rej_n, prob}; }
+    CellsDev cells() const { return CellsDev{tau, c, mat, visit, leak, cutoff, rej_w, rej_n, prob}; }
 };
 
 namespace {
@@ -788,7 +901,7 @@ void plan(gmc_world *w, Layout &L)
     L.add((void **)&w->c_x, 4 * C);
     L.add((void **)&w->c_la, 4 * C);
     L.add((void **)&w->c_ox, 4 * C);
-    L.add((void **)&w->s_idx, 4 * C);
+    L.add((void **)&w->s_slot, 4 * C);
     L.add((void **)&w->s_face, 4 * C);
     L.add((void **)&w->s_pos, 4 * C);
     L.add((void **)&w->s_dcos, 4 * C);
@@ -807,9 +920,7 @@ void plan(gmc_world *w, Layout &L)
     L.add((void **)&w->e_path, 4 * C);
     L.add((void **)&w->tau, 8 * N);
     L.add((void **)&w->c, 8 * N);
-    L.add((void **)&w->ltau, 4 * N);
-    L.add((void **)&w->cf, 4 * N);
-    L.add((void **)&w->siga, 8 * N);
+    L.add((void **)&w->mat, sizeof(CellMat) * N);
     L.add((void **)&w->visit, 8 * kVisitTallies * N);
     L.add((void **)&w->leak, 8 * N);
     L.add((void **)&w->cutoff, 8 * N);
@@ -954,19 +1065,17 @@ int gmc_problem_add(gmc_world *w, const gmc_problem_desc *d, int32_t *pid_out, v
     for (int p = 0; p < w->max_problems; ++p)
         if (!w->in_use[p]) { pid = p; break; }
     if (pid < 0) return set_error(GMC_ENOMEM, "gmc_problem_add: no free problem slot");
-    std::vector<float> lt, cf;
+    std::vector<CellMat> mat;
     std::vector<double> sa;
     try {
-        lt.resize(n);
-        cf.resize(n);
+        mat.resize(n);
         sa.resize(n);
     } catch (const std::bad_alloc &) {
         return set_error(GMC_ENOMEM, "gmc_problem_add: host staging");
     }
     for (int64_t i = 0; i < n; ++i) {
-        lt[i] = d->tau[i] > 0.0 ? (float)std::log(d->tau[i]) : -1.0e4f;
-        cf[i] = (float)d->c[i];
         sa[i] = (1.0 - d->c[i]) * d->tau[i] / d->L;
+        mat[i] = CellMat{d->tau[i] > 0.0 ? (float)std::log(d->tau[i]) : -1.0e4f, (float)d->c[i], sa[i]};
     }
     int64_t cell0 = -1;
     for (auto &r : w->free_cells)
@@ -986,10 +1095,8 @@ int gmc_problem_add(gmc_world *w, const gmc_problem_desc *d, int32_t *pid_out, v
     hipStream_t s = (hipStream_t)stream;
     hipError_t e = hipMemcpyAsync(w->tau + cell0, d->tau, 8 * n, hipMemcpyHostToDevice, s);
     if (e == hipSuccess) e = hipMemcpyAsync(w->c + cell0, d->c, 8 * n, hipMemcpyHostToDevice, s);
-    if (e == hipSuccess) e = hipMemcpyAsync(w->ltau + cell0, lt.data(), 4 * n, hipMemcpyHostToDevice, s);
-    if (e == hipSuccess) e = hipMemcpyAsync(w->cf + cell0, cf.data(), 4 * n, hipMemcpyHostToDevice, s);
+    if (e == hipSuccess) e = hipMemcpyAsync(w->mat + cell0, mat.data(), sizeof(CellMat) * n, hipMemcpyHostToDevice, s);
     if (e == hipSuccess) e = hipMemcpyAsync(w->prob + pid, &P, sizeof P, hipMemcpyHostToDevice, s);
-    if (e == hipSuccess) e = hipMemcpyAsync(w->siga + cell0, sa.data(), 8 * n, hipMemcpyHostToDevice, s);
     if (e == hipSuccess) {
         hipLaunchKernelGGL(zero_tallies_kernel, dim3(blocks_for(n)), dim3(256), 0, s, w->cells(), cell0, n);
         e = hipGetLastError();
@@ -1169,6 +1276,18 @@ bool world_xy(const gmc_world *w)
     return false;
 }
 
+// The one problem the world holds, -1 if it holds several.
+int32_t only_problem(const gmc_world *w)
+{
+    int32_t only = -1;
+    for (int p = 0; p < w->max_problems; ++p)
+        if (w->in_use[p]) {
+            if (only >= 0) return -1;
+            only = p;
+        }
+    return only;
+}
+
 // Enqueue one transport step on `s`: gather, sampler, counter reset, apply.  Grids are sized for
 // `n_launch` particles; the kernels process n_dev[0] of them when n_dev is given (a captured step
 // serves every count up to its bucket), else n_launch.
@@ -1177,21 +1296,27 @@ int enqueue_step(gmc_world *w, int sampler, const gmc_model *m, int K, hipStream
 {
     const int cur = w->cur, nxt = 1 - cur;
     const bool split = sampler == GMC_SAMPLER_GMC && m->collided;
+    const int cu = device_cu_count();
+    if (cu <= 0) return set_error(GMC_EDEVICE, "gmc_transport_step: cannot query the device");
+    const CondDev o{w->c_ltau, w->c_c, w->c_yin, w->c_sth, w->c_la, w->c_ox, w->ids, w->keys};
     if (split) {
         hipLaunchKernelGGL(set_u64_kernel, dim3(1), dim3(1), 0, s, w->s_count, 0ull, 1);
-        hipLaunchKernelGGL(gather_split_kernel, dim3(blocks_for(n_launch)), dim3(256), 0, s, w->bank[cur],
-                           n_launch, n_dev, w->cells(), w->c_ltau, w->c_c, w->c_yin, w->c_sth, w->c_la,
-                           w->c_ox, w->ids, w->keys, w->s_idx, w->s_count, w->e_face, w->e_pos, w->e_dcos,
-                           w->e_dsin, w->e_path, w->ff_max, w->streamed);
+        const dim3 grid((unsigned)std::min<int64_t>((n_launch + 63) / 64, (int64_t)cu * kStreamBlocksPerCu));
+        const int32_t only = w->graphs ? -1 : only_problem(w);
+        if (only >= 0)
+            hipLaunchKernelGGL(gather_split_kernel<true>, grid, dim3(kStreamThreads), 0, s, w->bank[cur], n_launch,
+                               n_dev, w->cells(), o, w->s_slot, w->s_count, w->e_face, w->e_pos, w->e_dcos, w->e_dsin,
+                               w->e_path, w->ff_max, only, w->streamed);
+        else
+            hipLaunchKernelGGL(gather_split_kernel<false>, grid, dim3(kStreamThreads), 0, s, w->bank[cur], n_launch,
+                               n_dev, w->cells(), o, w->s_slot, w->s_count, w->e_face, w->e_pos, w->e_dcos, w->e_dsin,
+                               w->e_path, w->ff_max, only, w->streamed);
     } else {
         hipLaunchKernelGGL(gather_kernel, dim3(blocks_for(n_launch)), dim3(256), 0, s, w->bank[cur], n_launch,
-                           n_dev, w->cells(), w->c_ltau, w->c_c, w->c_yin, w->c_sth, w->c_la, w->c_ox, w->ids,
-                           w->keys);
+                           n_dev, w->cells(), o);
     }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return set_hip_error(e, "gmc_transport_step: gather");
-    const int cu = device_cu_count();
-    if (cu <= 0) return set_error(GMC_EDEVICE, "gmc_transport_step: cannot query the device");
     if (sampler == GMC_SAMPLER_GMC) {
         MlpParams p = m->tmpl;
         p.log_tau = w->c_ltau;
@@ -1217,12 +1342,6 @@ int enqueue_step(gmc_world *w, int sampler, const gmc_model *m, int K, hipStream
         p.seed = 0;
         p.id_base = 0;
         e = launch_mlp_ode(m->precision, m->hidden, p, cu, s);
-        if (e == hipSuccess && split) {
-            hipLaunchKernelGGL(scatter_kernel, dim3(blocks_for(n_launch)), dim3(256), 0, s, n_launch, w->s_count,
-                               w->s_idx, w->s_face, w->s_pos, w->s_dcos, w->s_dsin, w->s_path, w->e_face,
-                               w->e_pos, w->e_dcos, w->e_dsin, w->e_path);
-            e = hipGetLastError();
-        }
     } else {
         WalkParams p{};
         p.log_tau = w->c_ltau;
@@ -1249,8 +1368,9 @@ int enqueue_step(gmc_world *w, int sampler, const gmc_model *m, int K, hipStream
     hipLaunchKernelGGL(set_u64_kernel, dim3(blocks_for(1 + w->max_problems)), dim3(256), 0, s,
                        ctr, 0ull, 1 + w->max_problems);
     hipLaunchKernelGGL(apply_kernel, dim3(tally_blocks(n_launch, cu)), dim3(kTallyThreads), 0, s, w->bank[cur], n_launch,
-                       n_dev, w->e_face, w->e_pos, w->e_dcos, w->e_dsin, w->e_path, w->cells(),
-                       w->bank[nxt], ctr, ctr + 1);
+                       n_dev, w->e_face, w->e_pos, w->e_dcos, w->e_dsin, w->e_path, w->s_slot,
+                       ExitDev{w->s_face, w->s_pos, w->s_dcos, w->s_dsin, w->s_path}, w->cells(), w->bank[nxt], ctr,
+                       ctr + 1);
     e = hipGetLastError();
     if (e != hipSuccess) return set_hip_error(e, "gmc_transport_step: apply");
     return GMC_OK;

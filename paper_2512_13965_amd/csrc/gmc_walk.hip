@@ -94,7 +94,7 @@ __global__ __launch_bounds__(256) void split_kernel(WalkParams p, int32_t *flag)
     const uint64_t id = p.ids ? p.ids[i] : p.id_base + (uint64_t)i;
     const uint64_t key = p.keys ? p.keys[i] : p.seed;
     Exit e;
-    const bool unc = uncollided_exit(expf(p.log_tau[i]), p.c[i], p.y_in[i], u, s, wa, key, id, e);
+    const bool unc = uncollided_exit(expf(p.log_tau[i]), p.c[i], p.y_in[i], u, s, wa, split_draw(key, id), e);
     flag[i] = unc ? 1 : 0;
     if (unc) {
         p.face[i] = e.face;

@@ -17,9 +17,8 @@
 //     fused multiply-add a flight; then each lane tests its own flight for the cell's boundary
 //     and the first one that ends the walk writes its record.  Every value is the one that the
 //     first regime computes, bit for bit.
-// The walks are dealt out in advance: block b of nb owns the granules b, b + nb, b + 2 nb, ... of
-// 64 consecutive walks (fewer where there are few walks), and its waves take from it through a
-// counter in LDS.  One counter for the whole launch costs more than the walks where they are
+// The walks are dealt out to blocks in advance (BlockShare), and the waves of a block take from
+// its share through a counter in LDS.  One counter for the whole launch costs more than the walks where they are
 // short: same-address atomics complete one in 13 ns (2^23 walks at tau = 1, 64 to an atomic:
 // 1.7 ms).
 // Measured, against one lane per walk throughout and a launch-wide counter: 2^20 walks of mixed
@@ -113,12 +112,9 @@ __device__ __forceinline__ uint32_t xor3(uint32_t a, uint32_t b, uint32_t c)
     return __builtin_amdgcn_bitop3_b32(a, b, c, 0x96);
 }
 
-// draw4(key, stream, flight, kTagWalk) from the prefix of (stream, key).
-__device__ __forceinline__ U4 draw_flight(const DrawPrefix &q, uint32_t k0, uint32_t k1, uint32_t flight)
+// Rounds 3 to 10 of a Philox block.
+__device__ __forceinline__ U4 philox_rest(uint32_t c0, uint32_t c1, uint32_t c2, uint32_t c3, uint32_t k0, uint32_t k1)
 {
-    const uint64_t f = (uint64_t)kPhiloxM1 * flight;
-    const uint64_t g = (uint64_t)kPhiloxM0 * ((uint32_t)(f >> 32) ^ q.a);
-    uint32_t c0 = q.b ^ (uint32_t)f, c1 = q.c, c2 = (uint32_t)(g >> 32) ^ q.d, c3 = (uint32_t)g;
 #pragma unroll
     for (uint32_t r = 2; r < 10; ++r) {
         const uint64_t p0 = (uint64_t)kPhiloxM0 * c0, p1 = (uint64_t)kPhiloxM1 * c2;
@@ -129,6 +125,32 @@ __device__ __forceinline__ U4 draw_flight(const DrawPrefix &q, uint32_t k0, uint
     }
     return U4{c0, c1, c2, c3};
 }
+
+// draw4(key, stream, flight, kTagWalk) from the prefix of (stream, key).
+__device__ __forceinline__ U4 draw_flight(const DrawPrefix &q, uint32_t k0, uint32_t k1, uint32_t flight)
+{
+    const uint64_t f = (uint64_t)kPhiloxM1 * flight;
+    const uint64_t g = (uint64_t)kPhiloxM0 * ((uint32_t)(f >> 32) ^ q.a);
+    return philox_rest(q.b ^ (uint32_t)f, q.c, (uint32_t)(g >> 32) ^ q.d, (uint32_t)g, k0, k1);
+}
+
+// The walks or particles 0 .. n-1 that a block of a launch takes: granules of consecutive ones,
+// block b the granules b, b + nb, b + 2 nb, ...; a granule halves from 64 until every block has
+// four.  Item v of the block is index(v), none if that lies beyond n.
+struct BlockShare {
+    int shift;
+    uint32_t items;
+    __device__ __forceinline__ explicit BlockShare(int64_t n) : shift(6)
+    {
+        while (shift > 0 && ((int64_t)gridDim.x << (shift + 2)) > n) --shift;
+        const int64_t nb = gridDim.x, granules = (n + (1 << shift) - 1) >> shift;
+        items = (uint32_t)(granules > blockIdx.x ? (granules - blockIdx.x + nb - 1) / nb : 0) << shift;
+    }
+    __device__ __forceinline__ int64_t index(uint32_t item) const
+    {
+        return (((int64_t)(item >> shift) * gridDim.x + blockIdx.x) << shift) + (item & ((1u << shift) - 1u));
+    }
+};
 
 // Distance to the cell's boundary along (u, v); xface: the ray leaves through a vertical face.
 __device__ __forceinline__ float walk_boundary(float x, float y, float u, float v, float wa, bool &xface)
@@ -192,12 +214,8 @@ __device__ __forceinline__ void run_walks(int64_t n, uint64_t seed, WalkGroups *
     if (threadIdx.x == 0) *pool = 0;
     __syncthreads();
 
-    // The block's walks: item v is walk ((v / gran) nb + b) gran + v % gran, none if beyond n; the
-    // granule halves from 64 until every block has four.
-    int shift = 6;
-    while (shift > 0 && ((int64_t)gridDim.x << (shift + 2)) > n) --shift;
-    const int64_t nb = gridDim.x, granules = (n + (1 << shift) - 1) >> shift;
-    const uint32_t items = (uint32_t)(granules > blockIdx.x ? (granules - blockIdx.x + nb - 1) / nb : 0) << shift;
+    const BlockShare mine(n);
+    const uint32_t items = mine.items;
     // lanes of a wave that start a walk: where there are few walks, every wave gets its share
     const uint32_t share = (items + waves - 1) / waves;
     const int lanes = share < 64 ? (int)share : 64;
@@ -236,7 +254,7 @@ __device__ __forceinline__ void run_walks(int64_t n, uint64_t seed, WalkGroups *
             dry = first >= items || items - first <= (uint32_t)cnt;
             const uint32_t item = first + (uint32_t)rank_in(needs);
             if (need && first < items && item < items) {
-                idx = (((int64_t)(item >> shift) * nb + blockIdx.x) << shift) + (item & ((1u << shift) - 1u));
+                idx = mine.index(item);
                 if (idx < n) {
                     const WalkStart w = fetch(idx);
                     const float sig = ANALOG ? w.tau : w.c * w.tau;
@@ -403,9 +421,9 @@ __device__ __forceinline__ void run_walks(int64_t n, uint64_t seed, WalkGroups *
         }
         const uint64_t all = __ballot(ends);
         if (alive) {
-            const uint64_t mine = (all >> base) & (g == 64 ? ~0ull : (1ull << g) - 1ull);
-            if (mine) {
-                if (j == __ffsll((unsigned long long)mine) - 1) {
+            const uint64_t ours = (all >> base) & (g == 64 ? ~0ull : (1ull << g) - 1ull);
+            if (ours) {
+                if (j == __ffsll((unsigned long long)ours) - 1) {
                     const uint32_t f = flight + (uint32_t)j;
                     if (ds >= db) {
                         float pos;

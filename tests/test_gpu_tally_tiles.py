@@ -53,3 +53,26 @@ def test_many_problems_share_workgroups():
         want = transport.run_problem(alone, prob, hist[i], 100 + i, binding.SAMPLER_MC)
         _same(got[i], want, f"problem {i}")
     alone.close()
+
+
+@pytest.mark.parametrize("n", [3, 700, 200_001])
+def test_streaming_refills_lanes(n):
+    # the first-flight split's streaming kernel: fewer particles than waves, than lanes, and more
+    # than its lanes at once (256 CUs of 512); with one crossing per step, with many, and with a
+    # second problem in the world (its kernel then reads each particle's problem)
+    binding = require_gpu()
+    prob = inputs.lattice_problem(4)
+    w = inputs.random_weights(128, 7, flags=2)
+    m = binding.Model(inputs.pack_blob(w), "bf16")
+    runs = {}
+    for label, streaming, second in (("one", 1, False), ("many", 64, False), ("two problems", 64, True)):
+        world = binding.World(1 << 18, 2, 1 << 12)
+        if second:
+            world.add_problem(inputs.checkerboard_problem(4, src=1), 1)
+        runs[label] = transport.run_problem(world, prob, n, 5, binding.SAMPLER_GMC, m, 2, streaming=streaming)
+        world.close()
+    m.close()
+    for label in ("many", "two problems"):
+        _same(runs["one"], runs[label], label)
+        assert runs[label]["transmissions"] == runs["one"]["transmissions"]
+    assert runs["many"]["steps"] < runs["one"]["steps"]
