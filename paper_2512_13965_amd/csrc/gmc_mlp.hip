@@ -1,8 +1,8 @@
 // Fused velocity-MLP + ODE sampler for gfx950 (paper: section "Conditional Flow
 // Matching", eq. 8; network of section "Network Architecture and Inputs"; decoding of eq. 11).
 //
-// Persistent workgroups (four waves, or eight in the two-group schedule of BF16 / FP8 models
-// of width 256 and more) each own a tile of samples at a time and carry it through all ODE
+// BF16 and FP8 models of width 128 run mlp_wave_kernel (below).  The others: persistent workgroups
+// (four waves for FP32, eight in the two-group schedule of BF16 / FP8 models) each own a tile of samples at a time and carry it through all ODE
 // steps (Euler x <- x + v(x, k/K | c) / K, or classic RK4):
 //   * the tile's activations live in LDS (128 x H), the ODE state x and the condition in LDS;
 //   * each hidden layer is a [H x H] x [H x 128] contraction on MFMA; each wave owns a set of
@@ -53,12 +53,6 @@
 #ifndef GMC_WIDE_WAVES
 #define GMC_WIDE_WAVES 8
 #endif
-// Largest number of persistent workgroups per compute unit for the four-wave kernels (FP32, and
-// BF16 / FP8 at width 128), as far as registers and LDS allow.
-#ifndef GMC_MAX_WG_PER_CU
-#define GMC_MAX_WG_PER_CU 4
-#endif
-
 namespace gmc {
 namespace {
 
@@ -174,8 +168,12 @@ __device__ __forceinline__ void epi_tile(const f32x16 &acc, float oscale, float 
 // in BF16 and FP8 models, whose accumulators carry the factor: the multiply drops out), and
 // with per-layer scales the output factor c2 = oscale * inv_next (a power of two) moves into
 // the reciprocal's argument, acc * rcp((1 + e) / c2) being exactly (acc * c2) * rcp(1 + e).
-template <int PO, bool SCALE, int NT, typename Val, typename Store>
-__device__ __forceinline__ void drain_pipe(Val &&val, float oscale, float inv_next, Store &&store)
+// hook(j) runs in iteration j (matrix work of the same wave, spread over the pipeline).
+struct NoHook {
+    template <typename J> __device__ __forceinline__ void operator()(J) const {}
+};
+template <int PO, bool SCALE, int NT, typename Val, typename Store, typename Hook = NoHook>
+__device__ __forceinline__ void drain_pipe(Val &&val, float oscale, float inv_next, Store &&store, Hook &&hook = Hook{})
 {
     constexpr int NV = NT * 16;
     constexpr int D = GMC_PIPE_D;
@@ -205,6 +203,7 @@ __device__ __forceinline__ void drain_pipe(Val &&val, float oscale, float inv_ne
             }
             if constexpr (v == 15) store(std::integral_constant<int, tt>{}, wd[tt]);
         }
+        hook(J);
         __builtin_amdgcn_sched_barrier(0);
     });
 }
@@ -821,40 +820,266 @@ __global__ __launch_bounds__((Cfg<MP, H, TM>::THREADS), 1) void mlp_ode_kernel(M
     }
 }
 
-// Persistent workgroups per compute unit of one kernel instance.  The two-group kernels fill
-// a CU's LDS and keep one.  A four-wave kernel has one wave per SIMD, which leaves the vector
-// units idle while it runs matrix work and the matrix core idle during its epilogue; where
-// registers and LDS leave room, several of its workgroups share a CU and their phases
-// interleave (the occupancy query, at most GMC_MAX_WG_PER_CU; queried once per instance).
-template <int MP, int H, int RK, int TM>
-int resident_per_cu()
+// Width 128 with BF16 or FP8 operands: a wave carries 32 samples through all evaluations by
+// itself.  The accumulator values lane (n, h) holds of a layer are the operand values lane (n, h)
+// reads for the next one (phys_to_feature), so with all of a layer's rows in one wave the
+// activations never leave its registers: no activation tile, no barrier, and the state of the ODE
+// stays in registers too.  The weights of all layers (BF16 108 KB) are copied into LDS once per
+// workgroup, of which a CU holds one with three waves to a SIMD.  Bound by the SiLU (two
+// transcendentals of 8 cycles an activation, 26 cycles with the rest: 6.7k cycles per 32 samples and
+// evaluation against 3.5k of matrix work; vector units busy 84 % of a full launch), so a layer's
+// two pairs of row tiles, X and Y, take turns: Y's products run in the iterations of X's SiLU, and
+// the next layer's X over the k-blocks that X gave in those of Y's.
+// Measured, against four waves to 128 samples with the activations in LDS (three such workgroups
+// to a CU): BF16 RK4 x 12, 2^20 samples 7.33 -> 6.27 ms, 2^18 1.77 -> 1.59 ms, 1,000 343 -> 224 us;
+// FP8 Euler K = 16, 2^20 samples 2.52 -> 2.01 ms.  (Two waves to a SIMD: 6.43 ms; without the
+// products in the SiLU's iterations: 6.87 ms; the biases read from memory: 6.45 ms.)
+template <int MP>
+struct WaveCfg {
+    static constexpr int H = 128;
+    static constexpr int PH = layer_prec(MP, 1), P5 = layer_prec(MP, 4);
+    static constexpr bool SCALE = (MP == kFP8);
+    static constexpr int NT = H / 32;
+    static constexpr int NKBH = H / kb_width(PH), NKB5 = H / kb_width(P5);
+    static constexpr int W = 12, THREADS = 64 * W;
+    static constexpr int TILE = 64 * 16;                       // one fragment line of 64 lanes
+    static constexpr int LDS_1 = NT * TILE;                    // layer 1: one BF16 k-block
+    static constexpr int LDS_H = NT * NKBH * 64 * frag_bytes(PH);
+    static constexpr int LDS_5 = NKB5 * TILE;
+    static constexpr int OFF_H = LDS_1, OFF_5 = LDS_1 + 3 * LDS_H, OFF_B = OFF_5 + LDS_5;
+    static constexpr int LDS_BYTES = OFF_B + (4 * H + 32) * 4;
+};
+
+// Four packed words as a BF16 operand fragment.
+template <typename F>
+__device__ __forceinline__ void put16(F &f, const uint32_t *w)
 {
-    if constexpr (Cfg<MP, H, TM>::GROUPS) {
-        return 1;
-    } else {
-        static const int n = [] {
-            int b = 1;
-            const hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(
-                &b, reinterpret_cast<const void *>(&mlp_ode_kernel<MP, H, RK, TM>), Cfg<MP, H, TM>::THREADS, 0);
-            if (e != hipSuccess) {
-                (void)hipGetLastError();   // fall back to one workgroup; keep the error off later launches
-                b = 1;
+    if constexpr (std::is_same_v<F, u32x4>) f = u32x4{w[0], w[1], w[2], w[3]};
+}
+
+template <int MP, int RK>
+__global__ __launch_bounds__((WaveCfg<MP>::THREADS), WaveCfg<MP>::W / 4) void mlp_wave_kernel(MlpParams p)
+{
+    using C = WaveCfg<MP>;
+    using M1 = Mma<kBF16>;
+    using MH = Mma<C::PH>;
+    constexpr bool rk4 = (RK == 1);
+    static_assert(C::LDS_BYTES <= 160 * 1024, "LDS budget");
+    __shared__ __attribute__((aligned(16))) char smem[C::LDS_BYTES];
+    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, half = lane >> 5;
+
+    // weights and biases to LDS; FP8 fragments (32 bytes a lane) as two lines of 16-byte halves
+    auto copy = [&](int off, const void *src, int bytes) {
+        for (int b = tid * 16; b < bytes; b += C::THREADS * 16) *(u32x4 *)(smem + off + b) = *(const u32x4 *)((const char *)src + b);
+    };
+    copy(0, p.wA[0], C::LDS_1);
+    for (int l = 0; l < 3; ++l) {
+        if constexpr (C::PH == kFP8) {
+            for (int q = tid; q < C::LDS_H / 16; q += C::THREADS) {
+                const int line = q >> 7, in = q & 127;         // source: lane in / 2, half in % 2
+                *(u32x4 *)(smem + C::OFF_H + l * C::LDS_H + line * 2048 + (in & 1) * 1024 + (in >> 1) * 16) =
+                    *(const u32x4 *)((const char *)p.wA[1 + l] + q * 16);
             }
-            return std::max(1, std::min(b, GMC_MAX_WG_PER_CU));
-        }();
-        return n;
+        } else {
+            copy(C::OFF_H + l * C::LDS_H, p.wA[1 + l], C::LDS_H);
+        }
+    }
+    copy(C::OFF_5, p.wA[4], C::LDS_5);
+    for (int l = 0; l < 4; ++l) copy(C::OFF_B + l * C::H * 4, p.bias[l], C::H * 4);
+    copy(C::OFF_B + 4 * C::H * 4, p.bias[4], 32 * 4);
+    __syncthreads();
+
+    const int64_t n_items = p.n_dev ? (int64_t)*p.n_dev : p.n;
+    const int64_t ntiles = (n_items + 31) / 32;
+    const float dt = 1.0f / (float)p.K;
+    const int nevals = rk4 ? 4 * p.K : p.K;
+    int at_lane = lane * 16, at_half = half * 16;     // offsets of this lane in a line, in a bias row
+    const char *frag = smem + at_lane;
+    auto load_h = [&](int l, int T, int kb) {
+        const char *f = frag + C::OFF_H + l * C::LDS_H + (T * C::NKBH + kb) * 64 * frag_bytes(C::PH);
+        if constexpr (C::PH == kFP8) return MH::cat(*(const u32x4 *)f, *(const u32x4 *)(f + 1024));
+        else return *(const u32x4 *)f;
+    };
+    auto load_bias = [&](int off) {          // the accumulator's start for one row tile
+        const float *b = (const float *)(smem + C::OFF_B + at_half) + off;
+        f32x16 v;
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+            const f32x4 q = *(const f32x4 *)(b + 8 * g);
+            v[4 * g + 0] = q.x;
+            v[4 * g + 1] = q.y;
+            v[4 * g + 2] = q.z;
+            v[4 * g + 3] = q.w;
+        }
+        return v;
+    };
+    auto upper = [](float x) {               // lane n's value in lane n + 32
+        const auto r = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(uint32_t, x),
+                                                        __builtin_bit_cast(uint32_t, x), false, false);
+        return __builtin_bit_cast(float, (uint32_t)r[1]);
+    };
+
+    for (int64_t tile = (int64_t)wave * gridDim.x + blockIdx.x; tile < ntiles; tile += (int64_t)gridDim.x * C::W) {
+        const int64_t i = tile * 32 + (lane & 31);
+        float z[5], cf[6];
+        sampler_inputs(p, i, n_items, z, cf);
+        // the input row [x0..x4, t, cf0..cf5, 0 x 4]: lanes 0-31 hold features 0-7, lanes 32-63 8-15;
+        // of the state lanes 0-31 hold x0..x3, lanes 32-63 x4 (as the output layer's rows fall)
+        const uint32_t c01 = pack_bf16(cf[0], cf[1]), c23 = pack_bf16(cf[2], cf[3]), c45 = pack_bf16(cf[4], cf[5]);
+        float x[4], ks[4], xi[4];
+#pragma unroll
+        for (int d = 0; d < 4; ++d) {
+            x[d] = half ? (d == 0 ? z[4] : 0.0f) : z[d];
+            xi[d] = x[d];
+            ks[d] = 0.0f;
+        }
+#pragma unroll 1
+        for (int e = 0; e < nevals; ++e) {
+            // the weights do not change from one evaluation to the next: keep the compiler from
+            // loading them ahead of the loop, for which there are no registers
+            asm volatile("" : "+v"(at_lane), "+v"(at_half));
+            frag = smem + at_lane;
+            const int stage = rk4 ? (e & 3) : 0;
+            const int k = rk4 ? (e >> 2) : e;
+            const float t = ((float)k + (stage == 0 ? 0.0f : (stage == 3 ? 1.0f : 0.5f))) * dt;
+            const uint32_t x4t = pack_bf16(upper(xi[0]), t);
+            const u32x4 in = half ? u32x4{c23, c45, 0u, 0u}
+                                  : u32x4{pack_bf16(xi[0], xi[1]), pack_bf16(xi[2], xi[3]), x4t, c01};
+            f32x16 X[2], Y[2], out;
+            typename MH::Frag B[2][C::NKBH];          // operands of the layer read, of the one written
+            u32x4 b5[C::NKB5];
+#pragma unroll
+            for (int r = 0; r < 2; ++r) {
+                X[r] = load_bias(32 * r);
+                Y[r] = load_bias(64 + 32 * r);
+                M1::run(X[r], *(const u32x4 *)(frag + r * C::TILE), in, 127);
+                M1::run(Y[r], *(const u32x4 *)(frag + (2 + r) * C::TILE), in, 127);
+            }
+            // packed words of row tile T to the operands of the layer that reads them
+            auto put = [&](auto PO, auto SLOT, auto TT, const uint32_t *w) {
+                constexpr int T = decltype(TT)::value, q = decltype(SLOT)::value;
+                if constexpr (decltype(PO)::value == kBF16 && C::PH == kBF16 && q < 2) {
+                    put16(B[q][2 * T], w);
+                    put16(B[q][2 * T + 1], w + 4);
+                } else if constexpr (decltype(PO)::value == kBF16) {
+                    put16(b5[2 * T], w);
+                    put16(b5[2 * T + 1], w + 4);
+                } else {
+#pragma unroll
+                    for (int m = 0; m < 4; ++m) B[q][T / 2][4 * (T % 2) + m] = (int)w[m];
+                }
+            };
+            // the products of hidden layer l, row tiles T0 and T0 + 1, over k-blocks K0 .. K1 - 1, as a
+            // list of 2 (K1 - K0): fragments are read PF places ahead
+            constexpr int PF = C::PH == kFP8 ? 2 : 4;
+            typename MH::Frag a[PF];
+            auto fetch = [&](auto L, auto T0, auto K0, auto M) {
+                constexpr int m = decltype(M)::value;
+                a[m % PF] = load_h(decltype(L)::value, decltype(T0)::value + m % 2, decltype(K0)::value + m / 2);
+            };
+            auto product = [&](f32x16 (&acc)[2], auto L, auto Q, auto T0, auto K0, auto K1, auto M) {
+                constexpr int m = decltype(M)::value, n = 2 * (decltype(K1)::value - decltype(K0)::value);
+                if constexpr (m < n) {
+                    const int sc = (C::PH == kFP8) ? p.mscale[1 + decltype(L)::value] : 127;
+                    MH::run(acc[m % 2], a[m % PF], B[decltype(Q)::value][decltype(K0)::value + m / 2], sc);
+                    if constexpr (m + PF < n) fetch(L, T0, K0, std::integral_constant<int, m + PF>{});
+                }
+            };
+            using I0 = std::integral_constant<int, 0>;
+            using I2 = std::integral_constant<int, 2>;
+            using KH = std::integral_constant<int, C::NKBH / 2>;
+            using KN = std::integral_constant<int, C::NKBH>;
+            constexpr int STEPS = 32 + 4 * GMC_PIPE_D, LEAD = 4;   // iterations of a pair's SiLU
+            // SiLU of the pair `src` (row tiles T0, T0 + 1) with a list of n products in its iterations
+            auto silu_pair = [&](f32x16 (&src)[2], auto PO, auto SLOT, auto T0, float osc, float inv, auto N, auto &&run) {
+                constexpr int n = decltype(N)::value, every = (STEPS - LEAD) / (n > 0 ? n : 1);
+                drain_pipe<decltype(PO)::value, C::SCALE, 2>(
+                    [&](auto I) { return src[decltype(I)::value / 16][decltype(I)::value % 16]; }, osc, inv,
+                    [&](auto TT, const uint32_t *w) {
+                        put(PO, SLOT, std::integral_constant<int, decltype(T0)::value + decltype(TT)::value>{}, w);
+                    },
+                    [&](auto J) {
+                        constexpr int j = decltype(J)::value - LEAD;
+                        if constexpr (n > 0 && j >= 0 && j % every == 0 && j / every < n)
+                            run(std::integral_constant<int, j / every>{});
+                    });
+            };
+            using PHC = std::integral_constant<int, C::PH>;
+            silu_pair(X, PHC{}, I0{}, I0{}, p.oscale[0], p.inv_in_scale[1], I0{}, [](auto) {});
+            sfor<3>([&](auto L) {
+                constexpr int l = decltype(L)::value;
+                using Q = std::integral_constant<int, l % 2>;                       // operands read
+                using R = std::integral_constant<int, l == 2 ? 2 : (l + 1) % 2>;    // and written
+                using PO = std::integral_constant<int, l == 2 ? C::P5 : C::PH>;
+                // the previous layer's Y, with X over the first half of the k-blocks
+#pragma unroll
+                for (int r = 0; r < 2; ++r) X[r] = load_bias(C::H * (1 + l) + 32 * r);
+                sfor<PF>([&](auto M) { if constexpr (decltype(M)::value < C::NKBH) fetch(L, I0{}, I0{}, M); });
+                silu_pair(Y, PHC{}, Q{}, I2{}, p.oscale[l], p.inv_in_scale[1 + l], KN{},
+                          [&](auto M) { product(X, L, Q{}, I0{}, I0{}, KH{}, M); });
+                sfor<PF>([&](auto M) { if constexpr (decltype(M)::value < C::NKBH) fetch(L, I0{}, KH{}, M); });
+#pragma unroll
+                for (int r = 0; r < 2; ++r) Y[r] = load_bias(C::H * (1 + l) + 64 + 32 * r);
+                sfor<C::NKBH>([&](auto M) {
+                    product(X, L, Q{}, I0{}, KH{}, KN{}, M);
+                    __builtin_amdgcn_sched_barrier(0);
+                });
+                // X, with Y over all k-blocks
+                sfor<PF>([&](auto M) { fetch(L, I2{}, I0{}, M); });
+                silu_pair(X, PO{}, R{}, I0{}, p.oscale[1 + l], l < 2 ? p.inv_in_scale[2 + l] : 1.0f,
+                          std::integral_constant<int, 2 * C::NKBH>{},
+                          [&](auto M) { product(Y, L, Q{}, I2{}, I0{}, KN{}, M); });
+            });
+            // the last Y, with the output layer over the first half
+            out = load_bias(4 * C::H);
+            auto last = [&](auto KB) {
+                constexpr int kb = decltype(KB)::value;
+                M1::run(out, *(const u32x4 *)(frag + C::OFF_5 + kb * C::TILE), b5[kb], 127);
+            };
+            silu_pair(Y, std::integral_constant<int, C::P5>{}, I2{}, I2{}, p.oscale[3], 1.0f,
+                      std::integral_constant<int, C::NKB5 / 2>{}, last);
+            sfor<C::NKB5 / 2>([&](auto M) { last(std::integral_constant<int, C::NKB5 / 2 + decltype(M)::value>{}); });
+            // x <- x + dt v, or the RK4 stage (as in mlp_ode_kernel)
+#pragma unroll
+            for (int d = 0; d < 4; ++d) {
+                const float v = out[d];
+                if constexpr (!rk4) {
+                    x[d] += v * dt;
+                    xi[d] = x[d];
+                } else if (stage < 3) {
+                    ks[d] = stage == 0 ? v : ks[d] + 2.0f * v;
+                    xi[d] = x[d] + (stage == 2 ? dt : 0.5f * dt) * v;
+                } else {
+                    xi[d] = x[d] = x[d] + (dt * (1.0f / 6.0f)) * (ks[d] + v);
+                }
+            }
+        }
+        const float x4 = upper(x[0]);
+        if (half == 0 && i < n_items) {
+            const float xk[5] = {x[0], x[1], x[2], x[3], x4};
+            sampler_outputs(p, i, xk);
+        }
     }
 }
 
-// grid: one persistent workgroup per tile of a launch of at most `bound` samples, at most
-// cu x resident_per_cu
+template <int MP>
+hipError_t launch_wave(const MlpParams &p, int cu, hipStream_t s)
+{
+    using C = WaveCfg<MP>;
+    const int grid = (int)std::max<int64_t>(1, std::min<int64_t>((p.n + 31) / 32, cu));
+    if (p.integrator == 1) hipLaunchKernelGGL((mlp_wave_kernel<MP, 1>), dim3(grid), dim3(C::THREADS), 0, s, p);
+    else hipLaunchKernelGGL((mlp_wave_kernel<MP, 0>), dim3(grid), dim3(C::THREADS), 0, s, p);
+    return hipGetLastError();
+}
+
+// grid: one persistent workgroup per tile of a launch of at most `bound` samples, at most one per
+// compute unit (whose LDS it fills)
 template <int MP, int H, int TM>
 hipError_t launch_tiles(const MlpParams &p, int64_t bound, int cu, hipStream_t s)
 {
     constexpr int threads = Cfg<MP, H, TM>::THREADS;
     const int64_t ntiles = (bound + TM - 1) / TM;
-    const int per_cu = p.integrator == 1 ? resident_per_cu<MP, H, 1, TM>() : resident_per_cu<MP, H, 0, TM>();
-    const int grid = (int)std::max<int64_t>(1, std::min<int64_t>(ntiles, (int64_t)cu * per_cu));
+    const int grid = (int)std::max<int64_t>(1, std::min<int64_t>(ntiles, cu));
     if (p.integrator == 1) hipLaunchKernelGGL((mlp_ode_kernel<MP, H, 1, TM>), dim3(grid), dim3(threads), 0, s, p);
     else hipLaunchKernelGGL((mlp_ode_kernel<MP, H, 0, TM>), dim3(grid), dim3(threads), 0, s, p);
     return hipGetLastError();
@@ -928,38 +1153,16 @@ bool mlp_supported(int prec, int hidden)
     return false;
 }
 
-template <int MP, int H>
-void prepare_one()
-{
-    (void)resident_per_cu<MP, H, 0, kTileM>();
-    (void)resident_per_cu<MP, H, 1, kTileM>();
-}
-
-void mlp_prepare(int prec, int hidden)
-{
-    switch (prec * 1000 + hidden) {
-    case kF32 * 1000 + 128: prepare_one<kF32, 128>(); break;
-    case kF32 * 1000 + 256: prepare_one<kF32, 256>(); break;
-    case kBF16 * 1000 + 128: prepare_one<kBF16, 128>(); break;
-    case kBF16 * 1000 + 256: prepare_one<kBF16, 256>(); break;
-    case kBF16 * 1000 + 512: prepare_one<kBF16, 512>(); break;
-    case kFP8 * 1000 + 128: prepare_one<kFP8, 128>(); break;
-    case kFP8 * 1000 + 256: prepare_one<kFP8, 256>(); break;
-    case kFP8 * 1000 + 512: prepare_one<kFP8, 512>(); break;
-    default: break;
-    }
-}
-
 hipError_t launch_mlp_ode(int prec, int hidden, const MlpParams &p, int cu, hipStream_t s)
 {
     if (p.net == 1) return launch_film_ode(prec, hidden, p, cu, s);
     switch (prec * 1000 + hidden) {
     case kF32 * 1000 + 128: return launch_one<kF32, 128>(p, cu, s);
     case kF32 * 1000 + 256: return launch_one<kF32, 256>(p, cu, s);
-    case kBF16 * 1000 + 128: return launch_one<kBF16, 128>(p, cu, s);
+    case kBF16 * 1000 + 128: return launch_wave<kBF16>(p, cu, s);
     case kBF16 * 1000 + 256: return launch_one<kBF16, 256>(p, cu, s);
     case kBF16 * 1000 + 512: return launch_one<kBF16, 512>(p, cu, s);
-    case kFP8 * 1000 + 128: return launch_one<kFP8, 128>(p, cu, s);
+    case kFP8 * 1000 + 128: return launch_wave<kFP8>(p, cu, s);
     case kFP8 * 1000 + 256: return launch_one<kFP8, 256>(p, cu, s);
     case kFP8 * 1000 + 512: return launch_one<kFP8, 512>(p, cu, s);
     default: return hipErrorInvalidValue;
