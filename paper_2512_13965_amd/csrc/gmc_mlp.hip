@@ -2,8 +2,9 @@
 // Matching", eq. 8; network of section "Network Architecture and Inputs"; decoding of eq. 11).
 //
 // BF16 and FP8 models of width 128 run mlp_wave_kernel (below).  The others: persistent workgroups
-// (four waves for FP32, eight in the two-group schedule of BF16 / FP8 models) each own a tile of samples at a time and carry it through all ODE
-// steps (Euler x <- x + v(x, k/K | c) / K, or classic RK4):
+// (four waves for FP32, eight in the two-group schedule of BF16 / FP8 models) each own a tile of
+// samples at a time and carry it through all ODE steps (Euler x <- x + v(x, k/K | c) / K, or
+// classic RK4):
 //   * the tile's activations live in LDS (128 x H), the ODE state x and the condition in LDS;
 //   * each hidden layer is a [H x H] x [H x 128] contraction on MFMA; each wave owns a set of
 //     32-row output tiles (four-wave kernels: wave w the rows [w*H/4, (w+1)*H/4); two-group
@@ -325,7 +326,18 @@ struct Cfg {
     static constexpr int CT = TM / 32;                      // sample column tiles of a tile
     static constexpr int LDS_ACT = TM * ACT_STRIDE;
     static constexpr int LDS_IN = TM * IN_STRIDE;
-    static constexpr int LDS_BYTES = LDS_ACT + LDS_IN + (5 + 6 + 5 + 5) * TM * 4;
+    // two-group schedule: the hidden layers' and the output layer's biases stay in LDS
+    static constexpr int BIAS = GROUPS ? 4 * H + 32 : 0;
+    static constexpr int LDS_BYTES = LDS_ACT + LDS_IN + (5 + 6 + 5 + 5) * TM * 4 + BIAS * 4;
+    // k-blocks of weight fragments a wave keeps on their way (two-group schedule).  A CU takes
+    // 64 bytes of them a cycle some 700 cycles after it asks; small tiles multiply a k-block too fast
+    // to load ahead by two of them, and have the registers for more.  RK4 x 12 at width 512, ring of
+    // 2 or 4 / 8 / 16 k-blocks: 10,000 samples (64 to a tile) BF16 862 / 923 / 1,028 us, FP8 676 (2) /
+    // 727 (4); 1,000 samples (32) BF16 625 / 627 / 803 us.  Full tiles keep 2: 4 spill (2^20 samples,
+    // Euler K = 16: BF16 21.2 / 21.4 ms, FP8 with 1 / 2 14.4 / 16.1 ms).
+    static constexpr int NJ = NKBH / 2 > 0 ? NKBH / 2 : 1;
+    static constexpr int WANT = (TM == kTileM ? 2 : TM == kMidTileM ? 4 : 8) / (PH == kFP8 ? 2 : 1);
+    static constexpr int RING = WANT < NJ ? WANT : NJ;
 };
 
 template <int MP, int H, int RK, int TM>
@@ -347,9 +359,10 @@ __global__ __launch_bounds__((Cfg<MP, H, TM>::THREADS), 1) void mlp_ode_kernel(M
     float *cf = xs + 5 * TM;                              // [6][128] condition features
     float *ksum = cf + 6 * TM;                            // [5][128] RK4 stage sum
     float *vout = ksum + 5 * TM;                          // [5][128] last network output
+    float *biases = vout + 5 * TM;                        // [4][H], [32] (two-group schedule)
 
     const int tid = threadIdx.x;
-    const int wave = tid >> 6, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
     // samples to process: the launch's own count, or one the device holds (a captured graph
     // sized for a bucket of counts); noise and raw keep the row stride p.n
     const int64_t n_items = p.n_dev ? (int64_t)*p.n_dev : p.n;
@@ -387,355 +400,452 @@ __global__ __launch_bounds__((Cfg<MP, H, TM>::THREADS), 1) void mlp_ode_kernel(M
             }
         }
     };
+    // two-group schedule: this wave's weight fragments of the hidden layers' next k-blocks (wrapping
+    // from the last hidden layer to the first of the next evaluation), and those of layer 1
+    using FragH = typename Mma<C::PH>::Frag;
+    using Frag1 = typename Mma<C::P1>::Frag;
+    FragH ring[C::RING][C::GROUPS ? C::RPG : 1];
+    Frag1 first[C::GROUPS ? C::RPG : 1];
+    const int tb = __builtin_amdgcn_readfirstlane((wave >> 2) * (C::NT / 2) + (wave & 3) * C::RPG);
+    auto load_hidden = [&](FragH (&slot)[C::GROUPS ? C::RPG : 1], Rsrc w, int kb) {
+#pragma unroll
+        for (int r = 0; r < C::RPG; ++r)
+            slot[r] = Mma<C::PH>::load_g(w, lane * frag_bytes(C::PH), ((tb + r) * C::NKBH + kb) * 64 * frag_bytes(C::PH));
+    };
+    auto load_first = [&] {
+        const Rsrc w = make_rsrc(p.wA[0], p.wA_bytes[0]);
+#pragma unroll
+        for (int r = 0; r < C::RPG; ++r)
+            first[r] = Mma<C::P1>::load_g(w, lane * frag_bytes(C::P1), (tb + r) * 64 * frag_bytes(C::P1));
+    };
+    if constexpr (C::GROUPS) {
+        for (int l = 0; l < 4; ++l)
+            for (int k = tid; k < H; k += C::THREADS) biases[l * H + k] = p.bias[l][k];
+        if (tid < 32) biases[4 * H + tid] = p.bias[4][tid];
+        const Rsrc w1 = make_rsrc(p.wA[1], p.wA_bytes[1]);
+        sfor<C::RING>([&](auto D) { load_hidden(ring[decltype(D)::value], w1, decltype(D)::value); });
+        load_first();
+        // visible after the barrier that follows the first tile's inputs
+    }
     const int T0 = wave * C::RTW;                    // first row tile (layer-by-layer path)
     const int TX = wave * C::RP, TY = C::NT / 2 + wave * C::RP;   // pass row tiles (pipelined path)
 
-    for (int64_t tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
-        const int64_t base = tile * TM;
-        if (tid < TM) {
-            const int64_t i = base + tid;
-            float z[5] = {0.f, 0.f, 0.f, 0.f, 0.f};
-            float lt = 0.f, cc = 0.f, yy = 0.5f, ss = 0.f, xx = 0.5f, co = 1.f, la = 0.f;
-            if (i < n_items) {
-                lt = p.log_tau[i];
-                cc = p.c[i];
-                yy = p.y_in[i];
-                ss = p.sin_th[i];
+    // The two groups of the two-group schedule run separate code (the same barriers in the same
+    // order): one code for both holds each group's registers through the other's phases (48
+    // registers spilled of the BF16 kernel of width 512; 4 now).  With the weights of the next
+    // phase on their way across the barriers, half of the output layer's at once and the biases in
+    // LDS: BF16 width 512, 2^20 samples, Euler K = 16 21.75 -> 21.16 ms (the library's own product
+    // of two 8192 x 8192 matrices runs at the rate of 22.1 ms: the power limit holds the clock),
+    // RK4 x 12 50,003 samples 3.62 -> 3.42 ms, 10,000 (64-sample tiles) 947 -> 862 us, 1,000 (32-sample
+    // tiles, their weights at 80 % of a CU's 64 bytes a cycle) 760 -> 626 us; FP8 1,000 531 -> 417 us.
+    auto tiles = [&](auto GRP) {
+        constexpr int grp = decltype(GRP)::value;
+        for (int64_t tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
+            const int64_t base = tile * TM;
+            if ((!C::GROUPS || grp == 0) && tid < TM) {
+                const int64_t i = base + tid;
+                float z[5] = {0.f, 0.f, 0.f, 0.f, 0.f};
+                float lt = 0.f, cc = 0.f, yy = 0.5f, ss = 0.f, xx = 0.5f, co = 1.f, la = 0.f;
+                if (i < n_items) {
+                    lt = p.log_tau[i];
+                    cc = p.c[i];
+                    yy = p.y_in[i];
+                    ss = p.sin_th[i];
+                    if (p.n_cond == 6) {
+                        xx = p.x_in[i];
+                        co = p.cos_phi[i];
+                    }
+                    if (p.log_aspect) la = p.log_aspect[i];
+                    else if (p.omega_x) la = p.omega_x[i];     // XY model: fifth feature omega_x
+                    if (p.noise) {
+#pragma unroll
+                        for (int d = 0; d < 5; ++d) z[d] = p.noise[d * p.n + i];
+                    } else {
+                        normal5(p.keys ? p.keys[i] : p.seed, p.ids ? p.ids[i] : p.id_base + (uint64_t)i, z);
+                    }
+                }
+#pragma unroll
+                for (int d = 0; d < 5; ++d) xs[d * TM + tid] = z[d];
+                // boundary model: (ln tau, c, 2 y_in - 1, sin th), rectangular cells add ln A, an
+                // XY-geometry model the entry direction's in-plane x component omega_x;
+                // internal model: (ln tau, c, 2 x - 1, 2 y - 1, cos phi, sin phi)
+                cf[0 * TM + tid] = lt;
+                cf[1 * TM + tid] = cc;
                 if (p.n_cond == 6) {
-                    xx = p.x_in[i];
-                    co = p.cos_phi[i];
-                }
-                if (p.log_aspect) la = p.log_aspect[i];
-                else if (p.omega_x) la = p.omega_x[i];     // XY model: fifth feature omega_x
-                if (p.noise) {
-#pragma unroll
-                    for (int d = 0; d < 5; ++d) z[d] = p.noise[d * p.n + i];
+                    cf[2 * TM + tid] = 2.0f * xx - 1.0f;
+                    cf[3 * TM + tid] = 2.0f * yy - 1.0f;
+                    cf[4 * TM + tid] = co;
+                    cf[5 * TM + tid] = ss;
                 } else {
-                    normal5(p.keys ? p.keys[i] : p.seed, p.ids ? p.ids[i] : p.id_base + (uint64_t)i, z);
+                    cf[2 * TM + tid] = 2.0f * yy - 1.0f;
+                    cf[3 * TM + tid] = ss;
+                    cf[4 * TM + tid] = la;
+                    cf[5 * TM + tid] = 0.0f;
                 }
             }
-#pragma unroll
-            for (int d = 0; d < 5; ++d) xs[d * TM + tid] = z[d];
-            // boundary model: (ln tau, c, 2 y_in - 1, sin th), rectangular cells add ln A, an
-            // XY-geometry model the entry direction's in-plane x component omega_x;
-            // internal model: (ln tau, c, 2 x - 1, 2 y - 1, cos phi, sin phi)
-            cf[0 * TM + tid] = lt;
-            cf[1 * TM + tid] = cc;
-            if (p.n_cond == 6) {
-                cf[2 * TM + tid] = 2.0f * xx - 1.0f;
-                cf[3 * TM + tid] = 2.0f * yy - 1.0f;
-                cf[4 * TM + tid] = co;
-                cf[5 * TM + tid] = ss;
-            } else {
-                cf[2 * TM + tid] = 2.0f * yy - 1.0f;
-                cf[3 * TM + tid] = ss;
-                cf[4 * TM + tid] = la;
-                cf[5 * TM + tid] = 0.0f;
-            }
-        }
-        __syncthreads();
+            __syncthreads();
 
-        // Two-group schedule: the layer-5 lanes apply the integrator's update (Euler step, RK4
-        // stage) and write the next input row themselves, so the input row is assembled here
-        // only for the first evaluation.
-        constexpr bool fold = C::GROUPS;
-        for (int e = 0; e < nevals; ++e) {
-            const int stage = rk4 ? (e & 3) : 0;
-            const int k = rk4 ? (e >> 2) : e;
-            const float t = ((float)k + (stage == 0 ? 0.0f : (stage == 3 ? 1.0f : 0.5f))) * dt;
-            // layer-1 input row of sample tid: [x0..x4, t, ln tau, c, 2y-1, sin th, 0 x 6]
-            if ((!fold || e == 0) && tid < TM) {
-                float v[16];
-                if (!rk4 || e == 0) {
+            // Two-group schedule: the layer-5 lanes apply the integrator's update (Euler step, RK4
+            // stage) and write the next input row themselves, so the input row is assembled here
+            // only for the first evaluation.
+            constexpr bool fold = C::GROUPS;
+            for (int e = 0; e < nevals; ++e) {
+                const int stage = rk4 ? (e & 3) : 0;
+                const int k = rk4 ? (e >> 2) : e;
+                const float t = ((float)k + (stage == 0 ? 0.0f : (stage == 3 ? 1.0f : 0.5f))) * dt;
+                // layer-1 input row of sample tid: [x0..x4, t, ln tau, c, 2y-1, sin th, 0 x 6]
+                if ((!fold || (e == 0 && grp == 0)) && tid < TM) {
+                    float v[16];
+                    if (!rk4 || e == 0) {
 #pragma unroll
-                    for (int d = 0; d < 5; ++d) v[d] = xs[d * TM + tid];
-                } else {
-                    advance(e - 1, v);
+                        for (int d = 0; d < 5; ++d) v[d] = xs[d * TM + tid];
+                    } else {
+                        advance(e - 1, v);
+                    }
+                    v[5] = t;
+#pragma unroll
+                    for (int d = 0; d < 6; ++d) v[6 + d] = cf[d * TM + tid];   // zero past n_cond
+#pragma unroll
+                    for (int d = 12; d < 16; ++d) v[d] = 0.0f;
+                    char *row = in0 + tid * C::IN_STRIDE;
+                    if constexpr (C::P1 == kF32) {
+#pragma unroll
+                        for (int q = 0; q < 4; ++q)
+                            *(f32x4 *)(row + 16 * q) = f32x4{v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]};
+                    } else {
+#pragma unroll
+                        for (int q = 0; q < 2; ++q)
+                            *(u32x4 *)(row + 16 * q) =
+                                u32x4{pack_bf16(v[8 * q], v[8 * q + 1]), pack_bf16(v[8 * q + 2], v[8 * q + 3]),
+                                      pack_bf16(v[8 * q + 4], v[8 * q + 5]), pack_bf16(v[8 * q + 6], v[8 * q + 7])};
+                    }
                 }
-                v[5] = t;
-#pragma unroll
-                for (int d = 0; d < 6; ++d) v[6 + d] = cf[d * TM + tid];   // zero past n_cond
-#pragma unroll
-                for (int d = 12; d < 16; ++d) v[d] = 0.0f;
-                char *row = in0 + tid * C::IN_STRIDE;
-                if constexpr (C::P1 == kF32) {
-#pragma unroll
-                    for (int q = 0; q < 4; ++q)
-                        *(f32x4 *)(row + 16 * q) = f32x4{v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]};
-                } else {
-#pragma unroll
-                    for (int q = 0; q < 2; ++q)
-                        *(u32x4 *)(row + 16 * q) =
-                            u32x4{pack_bf16(v[8 * q], v[8 * q + 1]), pack_bf16(v[8 * q + 2], v[8 * q + 3]),
-                                  pack_bf16(v[8 * q + 4], v[8 * q + 5]), pack_bf16(v[8 * q + 6], v[8 * q + 7])};
-                }
-            }
-            if (!fold || e == 0) __syncthreads();
+                if (!fold || e == 0) __syncthreads();
 
-            if constexpr (C::GROUPS) {
-                // Two-group schedule.  Per hidden layer, three barrier-separated phases:
-                //   P1: group 0 multiplies over the k-blocks of the first half of the input
-                //       features; group 1 runs the epilogue of its previous-layer rows (layer 1
-                //       included) and writes them over the second half (nobody reads it in P1)
-                //   P2: group 0 over the second half; group 1 over the first half
-                //   P3: group 0 runs its epilogue into the first half; group 1 over the
-                //       second half
-                // Every accumulator sums its k-blocks in natural order.
-                constexpr int RG = C::RPG;
-                // FP8 models: the last hidden layer writes BF16, two bytes per feature, whose
-                // first half would cover the FP8 second half that group 1 still reads in P3.
-                // Its outputs are therefore stored with the two halves swapped (row tile
-                // T -> T ^ NT/2) and layer 5 reads k-block kb from position kb ^ NKB5/2.
-                constexpr int XT = (C::PH != C::P5) ? C::NT / 2 : 0;
-                constexpr int SW5 = (C::PH != C::P5) ? C::NKB5 / 2 : 0;
-                const int grp = wave >> 2, wg = wave & 3;
-                const int TB = grp * (C::NT / 2) + wg * RG;       // first row tile of this wave
-                f32x16 acc[RG][C::CT];
-                // SiLU epilogue of accumulator tiles a[r][c] (row tile T0 + r, column tile c0 + c)
-                // into the activation tile, row tile index xor xt
-                auto drain_tiles = [&](auto POC, auto &a, int T0, int c0, float osc, float inv, int xt) {
-                    constexpr int PO = decltype(POC)::value;
-                    using A = std::remove_reference_t<decltype(a)>;
-                    constexpr int RX = std::extent_v<A, 0>, CX = std::extent_v<A, 1>;
+                if constexpr (C::GROUPS) {
+                    // Two-group schedule.  Per hidden layer, three barrier-separated phases:
+                    //   P1: group 0 multiplies over the k-blocks of the first half of the input
+                    //       features; group 1 runs the epilogue of its previous-layer rows (layer 1
+                    //       included) and writes them over the second half (nobody reads it in P1)
+                    //   P2: group 0 over the second half; group 1 over the first half
+                    //   P3: group 0 runs its epilogue into the first half; group 1 over the
+                    //       second half
+                    // Every accumulator sums its k-blocks in natural order.
+                    constexpr int RG = C::RPG;
+                    // FP8 models: the last hidden layer writes BF16, two bytes per feature, whose
+                    // first half would cover the FP8 second half that group 1 still reads in P3.
+                    // Its outputs are therefore stored with the two halves swapped (row tile
+                    // T -> T ^ NT/2) and layer 5 reads k-block kb from position kb ^ NKB5/2.
+                    constexpr int XT = (C::PH != C::P5) ? C::NT / 2 : 0;
+                    constexpr int SW5 = (C::PH != C::P5) ? C::NKB5 / 2 : 0;
+                    const int wg = wave & 3;
+                    const int TB = tb;                                // first row tile of this wave
+                    f32x16 acc[RG][C::CT];
+                    // SiLU epilogue of accumulator tiles a[r][c] (row tile T0 + r, column tile c0 + c)
+                    // into the activation tile, row tile index xor xt
+                    auto drain_tiles = [&](auto POC, auto &a, int T0, int c0, float osc, float inv, int xt) {
+                        constexpr int PO = decltype(POC)::value;
+                        using A = std::remove_reference_t<decltype(a)>;
+                        constexpr int RX = std::extent_v<A, 0>, CX = std::extent_v<A, 1>;
 #if GMC_DRAIN_PIPE
-                    drain_pipe<PO, C::SCALE, RX * CX>(
-                        [&](auto I) {
-                            constexpr int i = decltype(I)::value;
-                            return a[(i / 16) / CX][(i / 16) % CX][i % 16];
-                        },
-                        osc, inv,
-                        [&](auto TT, const uint32_t *wd) {
-                            constexpr int tt = decltype(TT)::value;
-                            store_tile<PO>(wd, (T0 + tt / CX) ^ xt, c0 + tt % CX, act, C::ACT_STRIDE, lane);
-                        });
-                    return;
+                        drain_pipe<PO, C::SCALE, RX * CX>(
+                            [&](auto I) {
+                                constexpr int i = decltype(I)::value;
+                                return a[(i / 16) / CX][(i / 16) % CX][i % 16];
+                            },
+                            osc, inv,
+                            [&](auto TT, const uint32_t *wd) {
+                                constexpr int tt = decltype(TT)::value;
+                                store_tile<PO>(wd, (T0 + tt / CX) ^ xt, c0 + tt % CX, act, C::ACT_STRIDE, lane);
+                            });
+                        return;
 #endif
-                    sfor<RX * CX>([&](auto TC) {
-                        constexpr int r = decltype(TC)::value / CX, c = decltype(TC)::value % CX;
-                        uint32_t wd[4 * words_per_unit(PO)];
-                        epi_tile<PO, C::SCALE>(a[r][c], osc, inv, wd);
-                        store_tile<PO>(wd, (T0 + r) ^ xt, c0 + c, act, C::ACT_STRIDE, lane);
-                    });
-                };
-                auto drain = [&](auto POC, float osc, float inv, int xt = 0) {
-                    constexpr int PO = decltype(POC)::value;
-                    constexpr int WPU = words_per_unit(PO);
+                        sfor<RX * CX>([&](auto TC) {
+                            constexpr int r = decltype(TC)::value / CX, c = decltype(TC)::value % CX;
+                            uint32_t wd[4 * words_per_unit(PO)];
+                            epi_tile<PO, C::SCALE>(a[r][c], osc, inv, wd);
+                            store_tile<PO>(wd, (T0 + r) ^ xt, c0 + c, act, C::ACT_STRIDE, lane);
+                        });
+                    };
+                    auto drain = [&](auto POC, float osc, float inv, int xt = 0) {
+                        constexpr int PO = decltype(POC)::value;
+                        constexpr int WPU = words_per_unit(PO);
 #if GMC_DRAIN_PIPE
-                    drain_pipe<PO, C::SCALE, RG * C::CT>(
-                        [&](auto I) {
-                            constexpr int i = decltype(I)::value;
-                            return acc[(i / 16) / C::CT][(i / 16) % C::CT][i % 16];
-                        },
-                        osc, inv,
-                        [&](auto TT, const uint32_t *wd) {
-                            constexpr int tt = decltype(TT)::value;
-                            store_tile<PO>(wd, (TB + tt / C::CT) ^ xt, tt % C::CT, act, C::ACT_STRIDE, lane);
-                        });
-                    return;
+                        drain_pipe<PO, C::SCALE, RG * C::CT>(
+                            [&](auto I) {
+                                constexpr int i = decltype(I)::value;
+                                return acc[(i / 16) / C::CT][(i / 16) % C::CT][i % 16];
+                            },
+                            osc, inv,
+                            [&](auto TT, const uint32_t *wd) {
+                                constexpr int tt = decltype(TT)::value;
+                                store_tile<PO>(wd, (TB + tt / C::CT) ^ xt, tt % C::CT, act, C::ACT_STRIDE, lane);
+                            });
+                        return;
 #endif
-                    sfor<RG * C::CT>([&](auto TC) {
-                        constexpr int r = decltype(TC)::value / C::CT, c = decltype(TC)::value % C::CT;
-                        uint32_t wd[4 * WPU];
-                        epi_tile<PO, C::SCALE>(acc[r][c], osc, inv, wd);
-                        store_tile<PO>(wd, (TB + r) ^ xt, c, act, C::ACT_STRIDE, lane);
-                    });
-                };
-                // layer 1 (10 -> H): both groups multiply their own rows; group 0 writes them now,
-                // group 1 during the first hidden layer's P1.  FP8 models (whose epilogue has
-                // the most vector work) split group 0's rows between the two waves of each SIMD
-                // instead: group 1 recomputes the second half of them (a single k-block of
-                // MFMAs) and runs that half's epilogue.
-                if constexpr (MP != kFP8 || C::CT < 4) {
-                    init_bias<RG, C::CT>(acc, make_rsrc(p.bias[0], p.bias_bytes[0]), TB, lane);
-                    mma_seq<C::P1, RG, C::CT, C::NKB1, C::NKB1, MapAll>(acc, make_rsrc(p.wA[0], p.wA_bytes[0]), TB,
-                                                                    in0, C::IN_STRIDE, 0, lane, [](auto) {});
-                    if (grp == 0) drain(std::integral_constant<int, C::PH>{}, p.oscale[0], p.inv_in_scale[1]);
-                } else {
-                    constexpr int RS = RG >= 2 ? RG / 2 : 1;       // row tiles of each share
-                    constexpr int CS = RG >= 2 ? 4 : 2;            // column tiles of each share
-                    constexpr int R_OFF = RG >= 2 ? RG / 2 : 0, C_OFF = RG >= 2 ? 0 : 2;
-                    const Rsrc w0 = make_rsrc(p.wA[0], p.wA_bytes[0]), b0 = make_rsrc(p.bias[0], p.bias_bytes[0]);
-                    f32x16 part[RS][CS];
-                    const int TS0 = wg * RG + (grp == 0 ? 0 : R_OFF), CS0 = (grp == 0) ? 0 : C_OFF;
-                    if (grp != 0) {
-                        init_bias<RG, C::CT>(acc, b0, TB, lane);
-                        mma_seq<C::P1, RG, C::CT, C::NKB1, C::NKB1, MapAll>(acc, w0, TB, in0, C::IN_STRIDE, 0, lane,
-                                                                        [](auto) {});
-                    }
-                    init_bias<RS, CS>(part, b0, TS0, lane);
-                    mma_seq<C::P1, RS, CS, C::NKB1, C::NKB1, MapAll>(part, w0, TS0, in0, C::IN_STRIDE, CS0, lane,
-                                                                     [](auto) {});
-                    drain_tiles(std::integral_constant<int, C::PH>{}, part, TS0, CS0, p.oscale[0],
-                                p.inv_in_scale[1], 0);
-                }
-                __syncthreads();
-                auto hidden = [&](int l, auto OUTP) {
-                    const Rsrc wl = make_rsrc(p.wA[l], p.wA_bytes[l]), bl = make_rsrc(p.bias[l], p.bias_bytes[l]);
-                    const int sc = (C::PH == kFP8) ? p.mscale[l] : 127;
-                    if (grp == 0) {
-                        init_bias<RG, C::CT>(acc, bl, TB, lane);
-                        mma_seq<C::PH, RG, C::CT, C::NKBH, C::NKBH / 2, MapHalf0<C::GH>>(
-                            acc, wl, TB, act, C::ACT_STRIDE, 0, lane, [](auto) {}, sc);
-                    } else {
-                        drain(std::integral_constant<int, C::PH>{}, p.oscale[l - 1], p.inv_in_scale[l]);
-                    }
-                    __syncthreads();
-                    if (grp == 0) {
-                        mma_seq<C::PH, RG, C::CT, C::NKBH, C::NKBH / 2, MapHalf1<C::GH>>(
-                            acc, wl, TB, act, C::ACT_STRIDE, 0, lane, [](auto) {}, sc);
-                    } else {
-                        init_bias<RG, C::CT>(acc, bl, TB, lane);
-                        mma_seq<C::PH, RG, C::CT, C::NKBH, C::NKBH / 2, MapHalf0<C::GH>>(
-                            acc, wl, TB, act, C::ACT_STRIDE, 0, lane, [](auto) {}, sc);
-                    }
-                    __syncthreads();
-                    if (grp == 0) {
-                        drain(OUTP, p.oscale[l], (l < 3) ? p.inv_in_scale[l + 1] : 1.0f,
-                              decltype(OUTP)::value != C::PH ? XT : 0);
-                    } else {
-                        mma_seq<C::PH, RG, C::CT, C::NKBH, C::NKBH / 2, MapHalf1<C::GH>>(
-                            acc, wl, TB, act, C::ACT_STRIDE, 0, lane, [](auto) {}, sc);
-                    }
-                    __syncthreads();
-                };
-                constexpr int NSAME = (C::PH == C::P5) ? 3 : 2;
-#pragma unroll 1
-                for (int l = 1; l <= NSAME; ++l) hidden(l, std::integral_constant<int, C::PH>{});
-                if constexpr (NSAME == 2) hidden(3, std::integral_constant<int, C::P5>{});
-                f32x16 out[1][1];
-                const Rsrc w4 = make_rsrc(p.wA[4], p.wA_bytes[4]);
-                // layer 5 (5 x H): group 0 wave w owns sample column tile w (small tiles: the
-                // waves w < CT); group 1 writes its layer-4 rows meanwhile
-                const bool l5 = (grp == 0) && (C::CT == 4 || wg < C::CT);
-                if (l5) {
-                    init_bias<1, 1>(out, make_rsrc(p.bias[4], p.bias_bytes[4]), 0, lane);
-                    mma_seq<C::P5, 1, 1, C::NKB5, C::NKB5 / 2, MapHalf0<C::G5>, 0, SW5>(
-                        out, w4, 0, act, C::ACT_STRIDE, wg, lane, [](auto) {});
-                } else if (grp != 0) {
-                    drain(std::integral_constant<int, C::P5>{}, p.oscale[3], 1.0f, XT);
-                }
-                __syncthreads();
-                if (l5) {
-                    mma_seq<C::P5, 1, 1, C::NKB5, C::NKB5 / 2, MapHalf1<C::G5>, 0, SW5>(
-                        out, w4, 0, act, C::ACT_STRIDE, wg, lane, [](auto) {});
-                    const int sn = wg * 32 + (lane & 31);
-                    if constexpr (fold && !rk4) {
-                        // x += dt v, then the next input row's x (and t) in BF16
-                        char *row = in0 + sn * C::IN_STRIDE;
-                        if (lane < 32) {
-                            float x[4];
+                        sfor<RG * C::CT>([&](auto TC) {
+                            constexpr int r = decltype(TC)::value / C::CT, c = decltype(TC)::value % C::CT;
+                            uint32_t wd[4 * WPU];
+                            epi_tile<PO, C::SCALE>(acc[r][c], osc, inv, wd);
+                            store_tile<PO>(wd, (TB + r) ^ xt, c, act, C::ACT_STRIDE, lane);
+                        });
+                    };
+                    // layer 1 (10 -> H): both groups multiply their own rows; group 0 writes them now,
+                    // group 1 during the first hidden layer's P1.  FP8 models (whose epilogue has
+                    // the most vector work) split group 0's rows between the two waves of each SIMD
+                    // instead: group 1 recomputes the second half of them (a single k-block of
+                    // MFMAs) and runs that half's epilogue.
+                    auto layer1 = [&] {
+                        static_assert(C::NKB1 == 1, "layer 1 is one k-block");
+                        init_bias_lds<RG, C::CT>(acc, biases, TB, lane);
+                        const char *sb = in0 + (lane & 31) * C::IN_STRIDE + (lane >> 5) * 16;
 #pragma unroll
-                            for (int d = 0; d < 4; ++d) {
-                                x[d] = xs[d * TM + sn] + out[0][0][d] * dt;
-                                xs[d * TM + sn] = x[d];
-                            }
-                            *(u32x2 *)row = u32x2{pack_bf16(x[0], x[1]), pack_bf16(x[2], x[3])};
-                        } else {
-                            const float x4 = xs[4 * TM + sn] + out[0][0][0] * dt;
-                            xs[4 * TM + sn] = x4;
-                            *(uint32_t *)(row + 8) = pack_bf16(x4, (float)(e + 1) * dt);
+                        for (int c = 0; c < C::CT; ++c) {
+                            const Frag1 b = Mma<C::P1>::load_s(sb + c * 32 * C::IN_STRIDE);
+#pragma unroll
+                            for (int r = 0; r < RG; ++r) Mma<C::P1>::run(acc[r][c], first[r], b, 127);
                         }
-                    } else if constexpr (fold) {
-                        // RK4 (the arithmetic of advance): stages 0..2 add v to the stage sum
-                        // and give the next stage's input, stage 3 finishes the step; then the
-                        // next input row's x (and t) in BF16
-                        auto update = [&](int d, float v) {
-                            const int o = d * TM + sn;
-                            if (stage < 3) {
-                                ksum[o] = stage == 0 ? v : ksum[o] + 2.0f * v;
-                                return xs[o] + (stage == 2 ? dt : 0.5f * dt) * v;
-                            }
-                            return xs[o] = xs[o] + (dt * (1.0f / 6.0f)) * (ksum[o] + v);
+                    };
+                    if constexpr (MP != kFP8 || C::CT < 4) {
+                        layer1();
+                        if constexpr (grp == 0) drain(std::integral_constant<int, C::PH>{}, p.oscale[0], p.inv_in_scale[1]);
+                    } else {
+                        constexpr int RS = RG >= 2 ? RG / 2 : 1;       // row tiles of each share
+                        constexpr int CS = RG >= 2 ? 4 : 2;            // column tiles of each share
+                        constexpr int R_OFF = RG >= 2 ? RG / 2 : 0, C_OFF = RG >= 2 ? 0 : 2;
+                        const Rsrc w0 = make_rsrc(p.wA[0], p.wA_bytes[0]);
+                        f32x16 part[RS][CS];
+                        const int TS0 = wg * RG + (grp == 0 ? 0 : R_OFF), CS0 = (grp == 0) ? 0 : C_OFF;
+                        if constexpr (grp != 0) layer1();
+                        init_bias_lds<RS, CS>(part, biases, TS0, lane);
+                        mma_seq<C::P1, RS, CS, C::NKB1, C::NKB1, MapAll>(part, w0, TS0, in0, C::IN_STRIDE, CS0, lane,
+                                                                         [](auto) {});
+                        drain_tiles(std::integral_constant<int, C::PH>{}, part, TS0, CS0, p.oscale[0],
+                                    p.inv_in_scale[1], 0);
+                    }
+                    __syncthreads();
+                    auto hidden = [&](int l, auto OUTP) {
+                        const int ln = l < 3 ? l + 1 : 1;
+                        const Rsrc wl = make_rsrc(p.wA[l], p.wA_bytes[l]), wn = make_rsrc(p.wA[ln], p.wA_bytes[ln]);
+                        const int sc = (C::PH == kFP8) ? p.mscale[l] : 127;
+                        constexpr int NJ = C::NJ, D = C::RING;
+                        auto products0 = [&] {
+                            init_bias_lds<RG, C::CT>(acc, biases + l * H, TB, lane);
+                            mma_ring<C::PH, RG, C::CT, NJ, D>(acc, ring, act, C::ACT_STRIDE, 0, 0, lane, sc, [&](auto J) {
+                                constexpr int j = decltype(J)::value;
+                                load_hidden(ring[j % D], wl, j + D);
+                            });
                         };
-                        const int e1 = e + 1, st1 = e1 & 3;
-                        const float t1 = ((float)(e1 >> 2) + (st1 == 0 ? 0.0f : (st1 == 3 ? 1.0f : 0.5f))) * dt;
-                        char *row = in0 + sn * C::IN_STRIDE;
-                        if (lane < 32) {
-                            float x[4];
-#pragma unroll
-                            for (int d = 0; d < 4; ++d) x[d] = update(d, out[0][0][d]);
-                            *(u32x2 *)row = u32x2{pack_bf16(x[0], x[1]), pack_bf16(x[2], x[3])};
-                        } else {
-                            const float x4 = update(4, out[0][0][0]);
-                            *(uint32_t *)(row + 8) = pack_bf16(x4, t1);
-                        }
-                    } else if (lane < 32) {
-#pragma unroll
-                        for (int d = 0; d < 4; ++d) emit(d, sn, out[0][0][d]);
-                    } else {
-                        emit(4, sn, out[0][0][0]);
+                        auto products1 = [&] {
+                            mma_ring<C::PH, RG, C::CT, NJ, D>(acc, ring, act, C::ACT_STRIDE, NJ, 0, lane, sc, [&](auto J) {
+                                constexpr int j = decltype(J)::value;
+                                if constexpr (j + D < NJ) load_hidden(ring[j % D], wl, NJ + j + D);
+                                else load_hidden(ring[j % D], wn, j + D - NJ);
+                            });
+                        };
+                        if constexpr (grp == 0) products0();
+                        else drain(std::integral_constant<int, C::PH>{}, p.oscale[l - 1], p.inv_in_scale[l]);
+                        __syncthreads();
+                        if constexpr (grp == 0) products1();
+                        else products0();
+                        __syncthreads();
+                        if constexpr (grp == 0)
+                            drain(OUTP, p.oscale[l], (l < 3) ? p.inv_in_scale[l + 1] : 1.0f,
+                                  decltype(OUTP)::value != C::PH ? XT : 0);
+                        else
+                            products1();
+                        __syncthreads();
+                    };
+                    constexpr int NSAME = (C::PH == C::P5) ? 3 : 2;
+#pragma unroll 1
+                    for (int l = 1; l <= NSAME; ++l) hidden(l, std::integral_constant<int, C::PH>{});
+                    if constexpr (NSAME == 2) hidden(3, std::integral_constant<int, C::P5>{});
+                    // layer 5 (5 x H): group 0 wave w owns sample column tile w (small tiles: the
+                    // waves w < CT); group 1 writes its layer-4 rows meanwhile.  Half of the layer's
+                    // fragments are on their way at once, the second half's before the barrier: a k-block
+                    // is one product of a single chain, and no time to load the next one in.
+                    constexpr int N5 = C::NKB5 / 2;
+                    using Frag5 = typename Mma<C::P5>::Frag;
+                    f32x16 out[1][1];
+                    Frag5 w5[N5][1];
+                    const Rsrc w4 = make_rsrc(p.wA[4], p.wA_bytes[4]);
+                    auto load5 = [&](int kb) {
+                        return Mma<C::P5>::load_g(w4, lane * frag_bytes(C::P5), kb * 64 * frag_bytes(C::P5));
+                    };
+                    const bool l5 = grp == 0 && (C::CT == 4 || wg < C::CT);
+                    if (l5) {
+                        sfor<N5>([&](auto J) { w5[decltype(J)::value][0] = load5(decltype(J)::value); });
+                        init_bias_lds<1, 1>(out, biases + 4 * H, 0, lane);
+                        mma_ring<C::P5, 1, 1, N5, N5, SW5>(out, w5, act, C::ACT_STRIDE, 0, wg, lane, 127, [&](auto J) {
+                            w5[decltype(J)::value][0] = load5(N5 + decltype(J)::value);
+                        });
+                    } else if constexpr (grp != 0) {
+                        drain(std::integral_constant<int, C::P5>{}, p.oscale[3], 1.0f, XT);
                     }
+                    load_first();
+                    __syncthreads();
+                    if (l5) {
+                        mma_ring<C::P5, 1, 1, N5, N5, SW5>(out, w5, act, C::ACT_STRIDE, N5, wg, lane, 127, [](auto) {});
+                        const int sn = wg * 32 + (lane & 31);
+                        if constexpr (fold && !rk4) {
+                            // x += dt v, then the next input row's x (and t) in BF16
+                            char *row = in0 + sn * C::IN_STRIDE;
+                            if (lane < 32) {
+                                float x[4];
+#pragma unroll
+                                for (int d = 0; d < 4; ++d) {
+                                    x[d] = xs[d * TM + sn] + out[0][0][d] * dt;
+                                    xs[d * TM + sn] = x[d];
+                                }
+                                *(u32x2 *)row = u32x2{pack_bf16(x[0], x[1]), pack_bf16(x[2], x[3])};
+                            } else {
+                                const float x4 = xs[4 * TM + sn] + out[0][0][0] * dt;
+                                xs[4 * TM + sn] = x4;
+                                *(uint32_t *)(row + 8) = pack_bf16(x4, (float)(e + 1) * dt);
+                            }
+                        } else if constexpr (fold) {
+                            // RK4 (the arithmetic of advance): stages 0..2 add v to the stage sum
+                            // and give the next stage's input, stage 3 finishes the step; then the
+                            // next input row's x (and t) in BF16
+                            auto update = [&](int d, float v) {
+                                const int o = d * TM + sn;
+                                if (stage < 3) {
+                                    ksum[o] = stage == 0 ? v : ksum[o] + 2.0f * v;
+                                    return xs[o] + (stage == 2 ? dt : 0.5f * dt) * v;
+                                }
+                                return xs[o] = xs[o] + (dt * (1.0f / 6.0f)) * (ksum[o] + v);
+                            };
+                            const int e1 = e + 1, st1 = e1 & 3;
+                            const float t1 = ((float)(e1 >> 2) + (st1 == 0 ? 0.0f : (st1 == 3 ? 1.0f : 0.5f))) * dt;
+                            char *row = in0 + sn * C::IN_STRIDE;
+                            if (lane < 32) {
+                                float x[4];
+#pragma unroll
+                                for (int d = 0; d < 4; ++d) x[d] = update(d, out[0][0][d]);
+                                *(u32x2 *)row = u32x2{pack_bf16(x[0], x[1]), pack_bf16(x[2], x[3])};
+                            } else {
+                                const float x4 = update(4, out[0][0][0]);
+                                *(uint32_t *)(row + 8) = pack_bf16(x4, t1);
+                            }
+                        } else if (lane < 32) {
+#pragma unroll
+                            for (int d = 0; d < 4; ++d) emit(d, sn, out[0][0][d]);
+                        } else {
+                            emit(4, sn, out[0][0][0]);
+                        }
+                    }
+                    __syncthreads();
+                    continue;
                 }
-                __syncthreads();
-                continue;
-            }
 
-            if constexpr (C::PIPE) {
-                // Cross-layer pipeline.  X holds a layer's first row pass, Y its second.  Each
-                // layer's second-pass epilogue runs inside the next layer's MFMA loop over the
-                // k-blocks holding first-pass outputs (already in LDS); its results are stored
-                // and the remaining k-blocks follow after a barrier.
-                constexpr int RP = C::RP;
-                f32x16 X[RP][4], Y[RP][4];
-                uint32_t pk[RP * 16 * C::WPK];
-                const Rsrc w0 = make_rsrc(p.wA[0], p.wA_bytes[0]), b0 = make_rsrc(p.bias[0], p.bias_bytes[0]);
-                init_bias<RP, 4>(X, b0, TX, lane);
-                mma_seq<C::P1, RP, 4, C::NKB1, C::NKB1, MapAll>(X, w0, TX, in0, C::IN_STRIDE, 0, lane, [](auto) {});
-                init_bias<RP, 4>(Y, b0, TY, lane);
-                mma_seq<C::P1, RP, 4, C::NKB1, C::NKB1, MapAll>(Y, w0, TY, in0, C::IN_STRIDE, 0, lane, [&](auto J) {
-                    drain_step<C::PH, C::SCALE, RP, C::NKB1, decltype(J)::value>(X, pk, p.oscale[0], p.inv_in_scale[1]);
-                });
-                store_pass<C::PH, RP>(pk, TX, act, C::ACT_STRIDE, lane);
+                if constexpr (C::PIPE) {
+                    // Cross-layer pipeline.  X holds a layer's first row pass, Y its second.  Each
+                    // layer's second-pass epilogue runs inside the next layer's MFMA loop over the
+                    // k-blocks holding first-pass outputs (already in LDS); its results are stored
+                    // and the remaining k-blocks follow after a barrier.
+                    constexpr int RP = C::RP;
+                    f32x16 X[RP][4], Y[RP][4];
+                    uint32_t pk[RP * 16 * C::WPK];
+                    const Rsrc w0 = make_rsrc(p.wA[0], p.wA_bytes[0]), b0 = make_rsrc(p.bias[0], p.bias_bytes[0]);
+                    init_bias<RP, 4>(X, b0, TX, lane);
+                    mma_seq<C::P1, RP, 4, C::NKB1, C::NKB1, MapAll>(X, w0, TX, in0, C::IN_STRIDE, 0, lane, [](auto) {});
+                    init_bias<RP, 4>(Y, b0, TY, lane);
+                    mma_seq<C::P1, RP, 4, C::NKB1, C::NKB1, MapAll>(Y, w0, TY, in0, C::IN_STRIDE, 0, lane, [&](auto J) {
+                        drain_step<C::PH, C::SCALE, RP, C::NKB1, decltype(J)::value>(X, pk, p.oscale[0], p.inv_in_scale[1]);
+                    });
+                    store_pass<C::PH, RP>(pk, TX, act, C::ACT_STRIDE, lane);
+                    __syncthreads();
+                    auto hidden = [&](int l, auto OUTP) {
+                        constexpr int PO = decltype(OUTP)::value;
+                        const Rsrc wl = make_rsrc(p.wA[l], p.wA_bytes[l]), bl = make_rsrc(p.bias[l], p.bias_bytes[l]);
+                        const float osc_prev = p.oscale[l - 1], inv_prev = p.inv_in_scale[l];
+                        const float osc = p.oscale[l], inv = (l < 3) ? p.inv_in_scale[l + 1] : 1.0f;
+                        const int sc = (C::PH == kFP8) ? p.mscale[l] : 127;
+                        init_bias<RP, 4>(X, bl, TX, lane);
+                        mma_seq<C::PH, RP, 4, C::NKBH, C::NKBH / 2, MapHalf0<C::GH>, GMC_VPM_A>(
+                            X, wl, TX, act, C::ACT_STRIDE, 0, lane, [&](auto J) {
+                                drain_step<C::PH, C::SCALE, RP, C::NKBH / 2, decltype(J)::value>(Y, pk, osc_prev, inv_prev);
+                            }, sc);
+                        store_pass<C::PH, RP>(pk, TY, act, C::ACT_STRIDE, lane);
+                        __syncthreads();
+                        mma_seq<C::PH, RP, 4, C::NKBH, C::NKBH / 2, MapHalf1<C::GH>>(
+                            X, wl, TX, act, C::ACT_STRIDE, 0, lane, [](auto) {}, sc);
+                        init_bias<RP, 4>(Y, bl, TY, lane);
+                        mma_seq<C::PH, RP, 4, C::NKBH, C::NKBH, MapAll, GMC_VPM_P>(
+                            Y, wl, TY, act, C::ACT_STRIDE, 0, lane, [&](auto J) {
+                                drain_step<PO, C::SCALE, RP, C::NKBH, decltype(J)::value>(X, pk, osc, inv);
+                            }, sc);
+                        __syncthreads();
+                        store_pass<PO, RP>(pk, TX, act, C::ACT_STRIDE, lane);
+                        __syncthreads();
+                    };
+                    constexpr int NSAME = (C::PH == C::P5) ? 3 : 2;
+#pragma unroll 1
+                    for (int l = 1; l <= NSAME; ++l) hidden(l, std::integral_constant<int, C::PH>{});
+                    if constexpr (NSAME == 2) hidden(3, std::integral_constant<int, C::P5>{});
+                    // layer 5 (5 x H, rows padded to one tile) over the first-pass k-blocks while
+                    // layer 4's second pass drains; wave w < 4 owns sample column tile w, further
+                    // waves only drain
+                    constexpr int CT5 = TM / 32;
+                    f32x16 out[1][1];
+                    const Rsrc w4 = make_rsrc(p.wA[4], p.wA_bytes[4]);
+                    auto drain4 = [&](auto J) {
+                        drain_step<C::P5, C::SCALE, RP, C::NKB5 / 2, decltype(J)::value>(Y, pk, p.oscale[3], 1.0f);
+                    };
+                    if (C::W == CT5 || wave < CT5) {
+                        init_bias<1, 1>(out, make_rsrc(p.bias[4], p.bias_bytes[4]), 0, lane);
+                        mma_seq<C::P5, 1, 1, C::NKB5, C::NKB5 / 2, MapHalf0<C::G5>, GMC_VPM_5>(
+                            out, w4, 0, act, C::ACT_STRIDE, wave, lane, drain4);
+                    } else {
+                        sfor<C::NKB5 / 2>(drain4);
+                    }
+                    store_pass<C::P5, RP>(pk, TY, act, C::ACT_STRIDE, lane);
+                    __syncthreads();
+                    if (C::W == CT5 || wave < CT5) {
+                        mma_seq<C::P5, 1, 1, C::NKB5, C::NKB5 / 2, MapHalf1<C::G5>>(
+                            out, w4, 0, act, C::ACT_STRIDE, wave, lane, [](auto) {});
+                        const int sn = wave * 32 + (lane & 31);
+                        if (lane < 32) {
+#pragma unroll
+                            for (int d = 0; d < 4; ++d) emit(d, sn, out[0][0][d]);
+                        } else {
+                            emit(4, sn, out[0][0][0]);
+                        }
+                    }
+                    __syncthreads();
+                    continue;
+                }
+
+                // layer 1: 10 -> H (reads in0, writes the activation tile: no barrier before writing)
+                dense_silu<C::P1, C::PH, C::RTW, C::NKB1, C::SCALE, false>(
+                    make_rsrc(p.wA[0], p.wA_bytes[0]), make_rsrc(p.bias[0], p.bias_bytes[0]), T0, in0, C::IN_STRIDE, act, C::ACT_STRIDE, lane,
+                    p.oscale[0], p.inv_in_scale[1]);
                 __syncthreads();
-                auto hidden = [&](int l, auto OUTP) {
-                    constexpr int PO = decltype(OUTP)::value;
-                    const Rsrc wl = make_rsrc(p.wA[l], p.wA_bytes[l]), bl = make_rsrc(p.bias[l], p.bias_bytes[l]);
-                    const float osc_prev = p.oscale[l - 1], inv_prev = p.inv_in_scale[l];
-                    const float osc = p.oscale[l], inv = (l < 3) ? p.inv_in_scale[l + 1] : 1.0f;
-                    const int sc = (C::PH == kFP8) ? p.mscale[l] : 127;
-                    init_bias<RP, 4>(X, bl, TX, lane);
-                    mma_seq<C::PH, RP, 4, C::NKBH, C::NKBH / 2, MapHalf0<C::GH>, GMC_VPM_A>(
-                        X, wl, TX, act, C::ACT_STRIDE, 0, lane, [&](auto J) {
-                            drain_step<C::PH, C::SCALE, RP, C::NKBH / 2, decltype(J)::value>(Y, pk, osc_prev, inv_prev);
-                        }, sc);
-                    store_pass<C::PH, RP>(pk, TY, act, C::ACT_STRIDE, lane);
-                    __syncthreads();
-                    mma_seq<C::PH, RP, 4, C::NKBH, C::NKBH / 2, MapHalf1<C::GH>>(
-                        X, wl, TX, act, C::ACT_STRIDE, 0, lane, [](auto) {}, sc);
-                    init_bias<RP, 4>(Y, bl, TY, lane);
-                    mma_seq<C::PH, RP, 4, C::NKBH, C::NKBH, MapAll, GMC_VPM_P>(
-                        Y, wl, TY, act, C::ACT_STRIDE, 0, lane, [&](auto J) {
-                            drain_step<PO, C::SCALE, RP, C::NKBH, decltype(J)::value>(X, pk, osc, inv);
-                        }, sc);
-                    __syncthreads();
-                    store_pass<PO, RP>(pk, TX, act, C::ACT_STRIDE, lane);
-                    __syncthreads();
-                };
+                // hidden layers 2..4: H -> H, in place.  One code instance in a runtime loop (layers
+                // whose output feeds an operand of the same type as their input); an FP8 model's
+                // last hidden layer writes BF16 for the output layer and is a second instance.
                 constexpr int NSAME = (C::PH == C::P5) ? 3 : 2;
 #pragma unroll 1
-                for (int l = 1; l <= NSAME; ++l) hidden(l, std::integral_constant<int, C::PH>{});
-                if constexpr (NSAME == 2) hidden(3, std::integral_constant<int, C::P5>{});
-                // layer 5 (5 x H, rows padded to one tile) over the first-pass k-blocks while
-                // layer 4's second pass drains; wave w < 4 owns sample column tile w, further
-                // waves only drain
-                constexpr int CT5 = TM / 32;
-                f32x16 out[1][1];
-                const Rsrc w4 = make_rsrc(p.wA[4], p.wA_bytes[4]);
-                auto drain4 = [&](auto J) {
-                    drain_step<C::P5, C::SCALE, RP, C::NKB5 / 2, decltype(J)::value>(Y, pk, p.oscale[3], 1.0f);
-                };
-                if (C::W == CT5 || wave < CT5) {
-                    init_bias<1, 1>(out, make_rsrc(p.bias[4], p.bias_bytes[4]), 0, lane);
-                    mma_seq<C::P5, 1, 1, C::NKB5, C::NKB5 / 2, MapHalf0<C::G5>, GMC_VPM_5>(
-                        out, w4, 0, act, C::ACT_STRIDE, wave, lane, drain4);
-                } else {
-                    sfor<C::NKB5 / 2>(drain4);
+                for (int l = 1; l <= NSAME; ++l) {
+                    dense_silu<C::PH, C::PH, C::RTW, C::NKBH, C::SCALE, true>(
+                        make_rsrc(p.wA[l], p.wA_bytes[l]), make_rsrc(p.bias[l], p.bias_bytes[l]), T0,
+                        act, C::ACT_STRIDE, act, C::ACT_STRIDE, lane, p.oscale[l],
+                        l < 3 ? p.inv_in_scale[l + 1] : 1.0f, (C::PH == kFP8) ? p.mscale[l] : 127);
+                    __syncthreads();
                 }
-                store_pass<C::P5, RP>(pk, TY, act, C::ACT_STRIDE, lane);
-                __syncthreads();
-                if (C::W == CT5 || wave < CT5) {
-                    mma_seq<C::P5, 1, 1, C::NKB5, C::NKB5 / 2, MapHalf1<C::G5>>(
-                        out, w4, 0, act, C::ACT_STRIDE, wave, lane, [](auto) {});
+                if constexpr (NSAME == 2) {
+                    dense_silu<C::PH, C::P5, C::RTW, C::NKBH, C::SCALE, true>(
+                        make_rsrc(p.wA[3], p.wA_bytes[3]), make_rsrc(p.bias[3], p.bias_bytes[3]), T0,
+                        act, C::ACT_STRIDE, act, C::ACT_STRIDE, lane, p.oscale[3], 1.0f,
+                        (C::PH == kFP8) ? p.mscale[3] : 127);
+                    __syncthreads();
+                }
+                // layer 5: H -> 5 (rows padded to 32); wave w handles sample column tile w
+                {
+                    f32x16 out[1][1];
+                    init_bias<1, 1>(out, make_rsrc(p.bias[4], p.bias_bytes[4]), 0, lane);
+                    mma_pass<C::P5, 1, 1, C::NKB5>(out, make_rsrc(p.wA[4], p.wA_bytes[4]), 0, act,
+                                                   C::ACT_STRIDE, wave, lane, [](auto) {});
                     const int sn = wave * 32 + (lane & 31);
                     if (lane < 32) {
 #pragma unroll
@@ -745,78 +855,43 @@ __global__ __launch_bounds__((Cfg<MP, H, TM>::THREADS), 1) void mlp_ode_kernel(M
                     }
                 }
                 __syncthreads();
-                continue;
             }
 
-            // layer 1: 10 -> H (reads in0, writes the activation tile: no barrier before writing)
-            dense_silu<C::P1, C::PH, C::RTW, C::NKB1, C::SCALE, false>(
-                make_rsrc(p.wA[0], p.wA_bytes[0]), make_rsrc(p.bias[0], p.bias_bytes[0]), T0, in0, C::IN_STRIDE, act, C::ACT_STRIDE, lane,
-                p.oscale[0], p.inv_in_scale[1]);
-            __syncthreads();
-            // hidden layers 2..4: H -> H, in place.  One code instance in a runtime loop (layers
-            // whose output feeds an operand of the same type as their input); an FP8 model's
-            // last hidden layer writes BF16 for the output layer and is a second instance.
-            constexpr int NSAME = (C::PH == C::P5) ? 3 : 2;
-#pragma unroll 1
-            for (int l = 1; l <= NSAME; ++l) {
-                dense_silu<C::PH, C::PH, C::RTW, C::NKBH, C::SCALE, true>(
-                    make_rsrc(p.wA[l], p.wA_bytes[l]), make_rsrc(p.bias[l], p.bias_bytes[l]), T0,
-                    act, C::ACT_STRIDE, act, C::ACT_STRIDE, lane, p.oscale[l],
-                    l < 3 ? p.inv_in_scale[l + 1] : 1.0f, (C::PH == kFP8) ? p.mscale[l] : 127);
-                __syncthreads();
-            }
-            if constexpr (NSAME == 2) {
-                dense_silu<C::PH, C::P5, C::RTW, C::NKBH, C::SCALE, true>(
-                    make_rsrc(p.wA[3], p.wA_bytes[3]), make_rsrc(p.bias[3], p.bias_bytes[3]), T0,
-                    act, C::ACT_STRIDE, act, C::ACT_STRIDE, lane, p.oscale[3], 1.0f,
-                    (C::PH == kFP8) ? p.mscale[3] : 127);
-                __syncthreads();
-            }
-            // layer 5: H -> 5 (rows padded to 32); wave w handles sample column tile w
-            {
-                f32x16 out[1][1];
-                init_bias<1, 1>(out, make_rsrc(p.bias[4], p.bias_bytes[4]), 0, lane);
-                mma_pass<C::P5, 1, 1, C::NKB5>(out, make_rsrc(p.wA[4], p.wA_bytes[4]), 0, act,
-                                               C::ACT_STRIDE, wave, lane, [](auto) {});
-                const int sn = wave * 32 + (lane & 31);
-                if (lane < 32) {
-#pragma unroll
-                    for (int d = 0; d < 4; ++d) emit(d, sn, out[0][0][d]);
+            if ((!C::GROUPS || grp == 0) && tid < TM) {
+                const int64_t i = base + tid;
+                float xk[5];
+                if constexpr (rk4 && !fold) {
+                    advance(nevals - 1, xk);
                 } else {
-                    emit(4, sn, out[0][0][0]);
+#pragma unroll
+                    for (int d = 0; d < 5; ++d) xk[d] = xs[d * TM + tid];
+                }
+                if (i < n_items) {
+                    const float a0 = xk[0], a1 = xk[1], a2 = xk[2], a3 = xk[3], a4 = xk[4];
+                    if (p.raw) {
+                        p.raw[0 * p.n + i] = a0;
+                        p.raw[1 * p.n + i] = a1;
+                        p.raw[2 * p.n + i] = a2;
+                        p.raw[3 * p.n + i] = a3;
+                        p.raw[4 * p.n + i] = a4;
+                    }
+                    Exit e;
+                    decode_exit(a0, a1, a2, a3, a4, e, p.xy != 0);
+                    p.face[i] = e.face;
+                    p.pos[i] = e.pos;
+                    p.dcos[i] = e.u;
+                    p.dsin[i] = e.v;
+                    p.path[i] = e.path;
                 }
             }
             __syncthreads();
         }
-
-        if (tid < TM) {
-            const int64_t i = base + tid;
-            float xk[5];
-            if constexpr (rk4 && !fold) {
-                advance(nevals - 1, xk);
-            } else {
-#pragma unroll
-                for (int d = 0; d < 5; ++d) xk[d] = xs[d * TM + tid];
-            }
-            if (i < n_items) {
-                const float a0 = xk[0], a1 = xk[1], a2 = xk[2], a3 = xk[3], a4 = xk[4];
-                if (p.raw) {
-                    p.raw[0 * p.n + i] = a0;
-                    p.raw[1 * p.n + i] = a1;
-                    p.raw[2 * p.n + i] = a2;
-                    p.raw[3 * p.n + i] = a3;
-                    p.raw[4 * p.n + i] = a4;
-                }
-                Exit e;
-                decode_exit(a0, a1, a2, a3, a4, e, p.xy != 0);
-                p.face[i] = e.face;
-                p.pos[i] = e.pos;
-                p.dcos[i] = e.u;
-                p.dsin[i] = e.v;
-                p.path[i] = e.path;
-            }
-        }
-        __syncthreads();
+    };
+    if constexpr (C::GROUPS) {
+        if (wave < 4) tiles(std::integral_constant<int, 0>{});
+        else tiles(std::integral_constant<int, 1>{});
+    } else {
+        tiles(std::integral_constant<int, 0>{});
     }
 }
 
@@ -870,7 +945,8 @@ __global__ __launch_bounds__((WaveCfg<MP>::THREADS), WaveCfg<MP>::W / 4) void ml
 
     // weights and biases to LDS; FP8 fragments (32 bytes a lane) as two lines of 16-byte halves
     auto copy = [&](int off, const void *src, int bytes) {
-        for (int b = tid * 16; b < bytes; b += C::THREADS * 16) *(u32x4 *)(smem + off + b) = *(const u32x4 *)((const char *)src + b);
+        for (int b = tid * 16; b < bytes; b += C::THREADS * 16)
+            *(u32x4 *)(smem + off + b) = *(const u32x4 *)((const char *)src + b);
     };
     copy(0, p.wA[0], C::LDS_1);
     for (int l = 0; l < 3; ++l) {

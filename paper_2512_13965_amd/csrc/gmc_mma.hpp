@@ -295,6 +295,58 @@ __device__ __forceinline__ void mma_seq(f32x16 (&acc)[RP][CT], Rsrc wA, int T0, 
     });
 }
 
+// acc[r][c][i] = bias as init_bias, from a layer's biases in LDS.
+template <int RP, int CT>
+__device__ __forceinline__ void init_bias_lds(f32x16 (&acc)[RP][CT], const float *bias, int T0, int lane)
+{
+    const float *b = bias + 32 * T0 + 4 * (lane >> 5);
+#pragma unroll
+    for (int r = 0; r < RP; ++r) {
+        f32x16 v;
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+            const f32x4 b4 = *(const f32x4 *)(b + 32 * r + 8 * g);
+            v[4 * g + 0] = b4.x;
+            v[4 * g + 1] = b4.y;
+            v[4 * g + 2] = b4.z;
+            v[4 * g + 3] = b4.w;
+        }
+#pragma unroll
+        for (int c = 0; c < CT; ++c) acc[r][c] = v;
+    }
+}
+
+// acc[r][c] += the products over the NJ k-blocks KB0 .. KB0 + NJ - 1 of an activation tile, with the
+// weight fragments a wave keeps on their way in a ring of D k-blocks: a[j % D] holds k-block j's when
+// it is used, and refill(j) then loads into it the fragments D places on, in this phase or the
+// next one (weights do not wait for barriers).  NJ is a multiple of D.
+template <int P, int RP, int CT, int NJ, int D, int SWAPB = 0, typename Refill>
+__device__ __forceinline__ void mma_ring(f32x16 (&acc)[RP][CT], typename Mma<P>::Frag (&a)[D][RP], const char *act,
+                                         int stride, int kb0, int col0, int lane, int sc, Refill &&refill)
+{
+    static_assert(NJ % D == 0, "the ring's places must fall alike in every phase");
+    using M = Mma<P>;
+    constexpr int KBB = kb_width(P) * elem_bytes(P);
+    const int h = lane >> 5, n = lane & 31;
+    const char *sb = act + (col0 * 32 + n) * stride + h * (KBB / 2);
+    typename M::Frag b[2][CT];
+    auto loadB = [&](int slot, int kb) {
+#pragma unroll
+        for (int c = 0; c < CT; ++c) b[slot][c] = M::load_s(sb + c * 32 * stride + (kb ^ SWAPB) * KBB);
+    };
+    loadB(0, kb0);
+    sfor<NJ>([&](auto JJ) {
+        constexpr int j = decltype(JJ)::value;
+        if constexpr (j + 1 < NJ) loadB((j + 1) % 2, kb0 + j + 1);
+#pragma unroll
+        for (int r = 0; r < RP; ++r)
+#pragma unroll
+            for (int c = 0; c < CT; ++c) M::run(acc[r][c], a[j % D][r], b[j % 2][c], sc);
+        refill(JJ);
+        __builtin_amdgcn_sched_barrier(0);
+    });
+}
+
 // Noise z and condition features cf of sample i of a launch (paper "Transport Algorithm",
 // second stage: noise drawn from the sample's Philox stream unless given).  Condition features:
 // boundary model (ln tau, c, 2 y_in - 1, sin th, f4, 0) with f4 = ln A for rectangular cells,
