@@ -9,8 +9,9 @@ namespace gmc {
 enum Prec { kF32 = 0, kBF16 = 1, kFP8 = 2 };
 
 // Samples per workgroup tile of the fused MLP/ODE kernel (and the small tiles of launches with
-// at most kSmallTileM or kMidTileM samples per compute unit) and waves per workgroup.
+// at most kSmallTileM, kMidTileM or kWideTileM samples per compute unit) and waves per workgroup.
 constexpr int kTileM = 128;
+constexpr int kWideTileM = 96;
 constexpr int kSmallTileM = 32;
 constexpr int kMidTileM = 64;
 constexpr int kWaves = 4;

@@ -336,7 +336,7 @@ struct Cfg {
     // 727 (4); 1,000 samples (32) BF16 625 / 627 / 803 us.  Full tiles keep 2: 4 spill (2^20 samples,
     // Euler K = 16: BF16 21.2 / 21.4 ms, FP8 with 1 / 2 14.4 / 16.1 ms).
     static constexpr int NJ = NKBH / 2 > 0 ? NKBH / 2 : 1;
-    static constexpr int WANT = (TM == kTileM ? 2 : TM == kMidTileM ? 4 : 8) / (PH == kFP8 ? 2 : 1);
+    static constexpr int WANT = (TM >= kWideTileM ? 2 : TM == kMidTileM ? 4 : 8) / (PH == kFP8 ? 2 : 1);
     static constexpr int RING = WANT < NJ ? WANT : NJ;
 };
 
@@ -344,7 +344,7 @@ template <int MP, int H, int RK, int TM>
 __global__ __launch_bounds__((Cfg<MP, H, TM>::THREADS), 1) void mlp_ode_kernel(MlpParams p)
 {
     using C = Cfg<MP, H, TM>;
-    static_assert(TM == kTileM || (C::GROUPS && (TM == kSmallTileM || TM == kMidTileM)),
+    static_assert(TM == kTileM || (C::GROUPS && (TM == kSmallTileM || TM == kMidTileM || TM == kWideTileM)),
                   "smaller tiles are built for the two-group schedule");
     static_assert(C::LDS_BYTES <= 160 * 1024, "LDS budget");
     static_assert(C::RTW >= 1 && C::NT % C::W == 0, "row tiles must split evenly over the waves");
@@ -427,6 +427,14 @@ __global__ __launch_bounds__((Cfg<MP, H, TM>::THREADS), 1) void mlp_ode_kernel(M
         load_first();
         // visible after the barrier that follows the first tile's inputs
     }
+    // This lane's index for the addresses of one phase.  The FP8 kernel of width 512 forms them
+    // anew in each: held through the other phases they spill (58 registers; 2 now; 2^20 samples
+    // 14.8 -> 14.3 ms).  The others have the registers, and would pay 1.8 % in vector instructions.
+    auto here = [&] {
+        int l = tid & 63;
+        if constexpr (MP == kFP8 && H == 512 && TM == kTileM) asm volatile("" : "+v"(l));
+        return l;
+    };
     const int T0 = wave * C::RTW;                    // first row tile (layer-by-layer path)
     const int TX = wave * C::RP, TY = C::NT / 2 + wave * C::RP;   // pass row tiles (pipelined path)
 
@@ -568,6 +576,7 @@ __global__ __launch_bounds__((Cfg<MP, H, TM>::THREADS), 1) void mlp_ode_kernel(M
                         });
                     };
                     auto drain = [&](auto POC, float osc, float inv, int xt = 0) {
+                        const int lane = here();
                         constexpr int PO = decltype(POC)::value;
                         constexpr int WPU = words_per_unit(PO);
 #if GMC_DRAIN_PIPE
@@ -630,6 +639,7 @@ __global__ __launch_bounds__((Cfg<MP, H, TM>::THREADS), 1) void mlp_ode_kernel(M
                         const int sc = (C::PH == kFP8) ? p.mscale[l] : 127;
                         constexpr int NJ = C::NJ, D = C::RING;
                         auto products0 = [&] {
+                            const int lane = here();
                             init_bias_lds<RG, C::CT>(acc, biases + l * H, TB, lane);
                             mma_ring<C::PH, RG, C::CT, NJ, D>(acc, ring, act, C::ACT_STRIDE, 0, 0, lane, sc, [&](auto J) {
                                 constexpr int j = decltype(J)::value;
@@ -637,6 +647,7 @@ __global__ __launch_bounds__((Cfg<MP, H, TM>::THREADS), 1) void mlp_ode_kernel(M
                             });
                         };
                         auto products1 = [&] {
+                            const int lane = here();
                             mma_ring<C::PH, RG, C::CT, NJ, D>(acc, ring, act, C::ACT_STRIDE, NJ, 0, lane, sc, [&](auto J) {
                                 constexpr int j = decltype(J)::value;
                                 if constexpr (j + D < NJ) load_hidden(ring[j % D], wl, NJ + j + D);
@@ -660,32 +671,37 @@ __global__ __launch_bounds__((Cfg<MP, H, TM>::THREADS), 1) void mlp_ode_kernel(M
 #pragma unroll 1
                     for (int l = 1; l <= NSAME; ++l) hidden(l, std::integral_constant<int, C::PH>{});
                     if constexpr (NSAME == 2) hidden(3, std::integral_constant<int, C::P5>{});
-                    // layer 5 (5 x H): group 0 wave w owns sample column tile w (small tiles: the
-                    // waves w < CT); group 1 writes its layer-4 rows meanwhile.  Half of the layer's
-                    // fragments are on their way at once, the second half's before the barrier: a k-block
-                    // is one product of a single chain, and no time to load the next one in.
-                    constexpr int N5 = C::NKB5 / 2;
+                    // layer 5 (5 x H): group 0 wave w owns sample column tile w (with small tiles the
+                    // waves beyond the last one repeat it); group 1 writes its layer-4 rows meanwhile.
+                    // A k-block is one product of a single chain, and no time to load the next one in:
+                    // eight k-blocks of fragments are on their way, the second half's before the barrier.
+                    constexpr int N5 = C::NKB5 / 2, D5 = N5 < 8 ? N5 : 8;
                     using Frag5 = typename Mma<C::P5>::Frag;
                     f32x16 out[1][1];
-                    Frag5 w5[N5][1];
+                    Frag5 w5[D5][1];
                     const Rsrc w4 = make_rsrc(p.wA[4], p.wA_bytes[4]);
                     auto load5 = [&](int kb) {
                         return Mma<C::P5>::load_g(w4, lane * frag_bytes(C::P5), kb * 64 * frag_bytes(C::P5));
                     };
-                    const bool l5 = grp == 0 && (C::CT == 4 || wg < C::CT);
-                    if (l5) {
-                        sfor<N5>([&](auto J) { w5[decltype(J)::value][0] = load5(decltype(J)::value); });
+                    const int wc = C::CT == 4 || wg < C::CT ? wg : C::CT - 1;
+                    if constexpr (grp == 0) {
+                        sfor<D5>([&](auto J) { w5[decltype(J)::value][0] = load5(decltype(J)::value); });
                         init_bias_lds<1, 1>(out, biases + 4 * H, 0, lane);
-                        mma_ring<C::P5, 1, 1, N5, N5, SW5>(out, w5, act, C::ACT_STRIDE, 0, wg, lane, 127, [&](auto J) {
-                            w5[decltype(J)::value][0] = load5(N5 + decltype(J)::value);
+                        mma_ring<C::P5, 1, 1, N5, D5, SW5>(out, w5, act, C::ACT_STRIDE, 0, wc, lane, 127, [&](auto J) {
+                            w5[decltype(J)::value % D5][0] = load5(D5 + decltype(J)::value);
                         });
-                    } else if constexpr (grp != 0) {
+                    } else {
                         drain(std::integral_constant<int, C::P5>{}, p.oscale[3], 1.0f, XT);
                     }
                     load_first();
                     __syncthreads();
-                    if (l5) {
-                        mma_ring<C::P5, 1, 1, N5, N5, SW5>(out, w5, act, C::ACT_STRIDE, N5, wg, lane, 127, [](auto) {});
+                    if constexpr (grp == 0) {
+                        mma_ring<C::P5, 1, 1, N5, D5, SW5>(out, w5, act, C::ACT_STRIDE, N5, wc, lane, 127, [&](auto J) {
+                            constexpr int k = decltype(J)::value;
+                            if constexpr (k + D5 < N5) w5[k % D5][0] = load5(N5 + D5 + k);
+                        });
+                    }
+                    if (grp == 0 && (C::CT == 4 || wg < C::CT)) {
                         const int sn = wg * 32 + (lane & 31);
                         if constexpr (fold && !rk4) {
                             // x += dt v, then the next input row's x (and t) in BF16
@@ -1175,32 +1191,35 @@ inline MlpParams sample_range(const MlpParams &p, int64_t off, int64_t cnt)
     return q;
 }
 
-// Launches with at most kSmallTileM (kMidTileM) samples per compute unit (the tail steps of a
-// transport run, small requests) take 32-sample (64-sample) tiles when the model runs the
+// Launches with at most kSmallTileM (kMidTileM, kWideTileM) samples per compute unit (the tail steps
+// of a transport run, small requests) take 32-sample (64-, 96-sample) tiles when the model runs the
 // two-group schedule: one round of them covers the launch on every CU, and a tile's latency
-// falls with its matrix work (RK4 x 12 at width 512: 0.75 ms for 32 samples, 1.6 ms for 128).
-// When only the device knows the count (n_dev) and its bound p.n is larger, the choice is made
-// on the device (MlpParams::n_dev_large) without a read-back; a sample's result is the same
-// with every tile size.  A count known on the host whose last round of 128-sample tiles would
-// hold at most 64 samples per CU runs that remainder as one round of smaller tiles.
+// falls with its matrix work (BF16 width 512: an evaluation of 32 / 64 / 96 / 128 samples takes
+// 13 / 18 / 29 / 40 us).  When only the device knows the count (n_dev) and its bound p.n is
+// larger, the choice is made on the device (MlpParams::n_dev_large; between 32, 64 and 128) without a
+// read-back; a sample's result is the same with every tile size.  A count known on the host whose
+// last round of 128-sample tiles would hold at most 96 samples per CU runs that remainder as one
+// round of smaller tiles.
 template <int MP, int H>
 hipError_t launch_one(const MlpParams &p, int cu, hipStream_t s)
 {
     MlpParams q = p;
     q.n_dev_large = nullptr;
     if constexpr (Cfg<MP, H>::GROUPS) {
-        const int64_t small = (int64_t)kSmallTileM * cu, mid = (int64_t)kMidTileM * cu;
+        const int64_t small = (int64_t)kSmallTileM * cu, mid = (int64_t)kMidTileM * cu, wide = (int64_t)kWideTileM * cu;
         if (p.n <= small) return launch_tiles<MP, H, kSmallTileM>(q, p.n, cu, s);
         if (!p.n_dev) {
             if (p.n <= mid) return launch_tiles<MP, H, kMidTileM>(q, p.n, cu, s);
+            if (p.n <= wide) return launch_tiles<MP, H, kWideTileM>(q, p.n, cu, s);
             const int64_t round = (int64_t)kTileM * cu, rem = p.n % round;
-            if (!p.noise && !p.raw && rem > 0 && rem <= mid) {
+            if (!p.noise && !p.raw && rem > 0 && rem <= wide) {
                 const MlpParams head = sample_range(q, 0, p.n - rem);
                 const hipError_t e = launch_tiles<MP, H, kTileM>(head, head.n, cu, s);
                 if (e != hipSuccess) return e;
                 const MlpParams tail = sample_range(q, p.n - rem, rem);
                 return rem <= small ? launch_tiles<MP, H, kSmallTileM>(tail, rem, cu, s)
-                                    : launch_tiles<MP, H, kMidTileM>(tail, rem, cu, s);
+                       : rem <= mid ? launch_tiles<MP, H, kMidTileM>(tail, rem, cu, s)
+                                    : launch_tiles<MP, H, kWideTileM>(tail, rem, cu, s);
             }
         } else if (p.n_dev_large) {
             // 32-sample kernel, then the 64-sample one, each handing on what it does not take
