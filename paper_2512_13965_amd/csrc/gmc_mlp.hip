@@ -210,32 +210,32 @@ __device__ __forceinline__ void drain_pipe(Val &&val, float oscale, float inv_ne
 }
 
 
-// One dense layer + SiLU for this wave's RTW row tiles and all 128 samples of the tile.  The
+// One dense layer + SiLU for this wave's RTW row tiles and all CT column tiles of samples.  The
 // rows are done in NP passes of RP row tiles; the epilogue of pass p runs interleaved with the
 // MFMA k-loop of pass p + 1 (it only reads pass p's accumulators), so the SiLU transcendentals
 // overlap the matrix unit.  Those results are held packed in registers until every wave has
 // finished reading the input tile (barrier, when `out` aliases the input); the last pass's
 // epilogue is computed and stored after that barrier.
-template <int PIN, int POUT, int RTW, int NKB, bool SCALE, bool IN_PLACE>
+template <int PIN, int POUT, int RTW, int CT, int NKB, bool SCALE, bool IN_PLACE>
 __device__ __forceinline__ void dense_silu(Rsrc wA, Rsrc bias, int T0, const char *in, int in_stride, char *out,
                                            int out_stride, int lane, float oscale, float inv_next, int sc = 127)
 {
     constexpr int RP = RTW >= 4 ? RTW / 2 : 1;     // row tiles per pass
     constexpr int NP = RTW / RP;                   // passes
-    constexpr int UNITS = RP * 4 * 4;              // epilogue units (4 values) per pass
+    constexpr int UNITS = RP * CT * 4;             // epilogue units (4 values) per pass
     constexpr int WPU = words_per_unit(POUT);
     constexpr int UPK = (UNITS + NKB - 1) / NKB;   // epilogue units per k-block
     uint32_t pk[NP > 1 ? NP - 1 : 1][UNITS * WPU];
-    f32x16 acc[2][RP][4];
+    f32x16 acc[2][RP][CT];
     auto epi = [&](auto PP, int u) {
         constexpr int pp = decltype(PP)::value;
-        const int r = u / 16, c = (u / 4) % 4, g = u % 4;
+        const int r = u / (4 * CT), c = (u / 4) % CT, g = u % 4;
         epi_unit<POUT, SCALE>(acc[pp % 2][r][c], g, oscale, inv_next, &pk[pp][u * WPU]);
     };
     sfor<NP>([&](auto P) {
         constexpr int p = decltype(P)::value;
-        init_bias<RP, 4>(acc[p % 2], bias, T0 + p * RP, lane);
-        mma_pass<PIN, RP, 4, NKB>(acc[p % 2], wA, T0 + p * RP, in, in_stride, 0, lane, [&](auto KB) {
+        init_bias<RP, CT>(acc[p % 2], bias, T0 + p * RP, lane);
+        mma_pass<PIN, RP, CT, NKB>(acc[p % 2], wA, T0 + p * RP, in, in_stride, 0, lane, [&](auto KB) {
             constexpr int kb = decltype(KB)::value;
             if constexpr (p > 0) {
                 sfor<UPK>([&](auto J) {
@@ -253,14 +253,14 @@ __device__ __forceinline__ void dense_silu(Rsrc wA, Rsrc bias, int T0, const cha
     if constexpr (IN_PLACE) __syncthreads();
     sfor<NP - 1>([&](auto P) {
         constexpr int p = decltype(P)::value;
-        sfor<RP * 4>([&](auto TC) {
-            constexpr int r = decltype(TC)::value / 4, c = decltype(TC)::value % 4;
-            store_tile<POUT>(&pk[p][(r * 4 + c) * 4 * WPU], T0 + p * RP + r, c, out, out_stride, lane);
+        sfor<RP * CT>([&](auto TC) {
+            constexpr int r = decltype(TC)::value / CT, c = decltype(TC)::value % CT;
+            store_tile<POUT>(&pk[p][(r * CT + c) * 4 * WPU], T0 + p * RP + r, c, out, out_stride, lane);
         });
     });
     constexpr int pl = NP - 1;
-    sfor<RP * 4>([&](auto TC) {
-        constexpr int r = decltype(TC)::value / 4, c = decltype(TC)::value % 4;
+    sfor<RP * CT>([&](auto TC) {
+        constexpr int r = decltype(TC)::value / CT, c = decltype(TC)::value % CT;
         uint32_t w[4 * WPU];
 #pragma unroll
         for (int g = 0; g < 4; ++g) epi_unit<POUT, SCALE>(acc[pl % 2][r][c], g, oscale, inv_next, &w[g * WPU]);
@@ -268,27 +268,27 @@ __device__ __forceinline__ void dense_silu(Rsrc wA, Rsrc bias, int T0, const cha
     });
 }
 
-// Part J of NJ of draining accumulator tiles src[RP][4] through the epilogue into packed words.
-template <int PO, bool SCALE, int RP, int NJ, int J>
-__device__ __forceinline__ void drain_step(const f32x16 (&src)[RP][4], uint32_t *pk, float osc, float inv)
+// Part J of NJ of draining accumulator tiles src[RP][CT] through the epilogue into packed words.
+template <int PO, bool SCALE, int NJ, int J, int RP, int CT>
+__device__ __forceinline__ void drain_step(const f32x16 (&src)[RP][CT], uint32_t *pk, float osc, float inv)
 {
-    constexpr int UNITS = RP * 16;
+    constexpr int UNITS = RP * CT * 4;
     constexpr int UPK = (UNITS + NJ - 1) / NJ;
     constexpr int WPU = words_per_unit(PO);
     sfor<UPK>([&](auto U) {
         constexpr int u = J * UPK + decltype(U)::value;
-        if constexpr (u < UNITS) epi_unit<PO, SCALE>(src[u / 16][(u / 4) % 4], u % 4, osc, inv, &pk[u * WPU]);
+        if constexpr (u < UNITS) epi_unit<PO, SCALE>(src[u / (4 * CT)][(u / 4) % CT], u % 4, osc, inv, &pk[u * WPU]);
     });
 }
 
 // Store the packed outputs of one row pass (row tiles Tb .. Tb + RP - 1, all column tiles).
-template <int PO, int RP>
+template <int PO, int RP, int CT>
 __device__ __forceinline__ void store_pass(const uint32_t *pk, int Tb, char *act, int stride, int lane)
 {
     constexpr int WPU = words_per_unit(PO);
-    sfor<RP * 4>([&](auto TC) {
-        constexpr int r = decltype(TC)::value / 4, c = decltype(TC)::value % 4;
-        store_tile<PO>(&pk[(r * 4 + c) * 4 * WPU], Tb + r, c, act, stride, lane);
+    sfor<RP * CT>([&](auto TC) {
+        constexpr int r = decltype(TC)::value / CT, c = decltype(TC)::value % CT;
+        store_tile<PO>(&pk[(r * CT + c) * 4 * WPU], Tb + r, c, act, stride, lane);
     });
 }
 
@@ -344,12 +344,9 @@ template <int MP, int H, int RK, int TM>
 __global__ __launch_bounds__((Cfg<MP, H, TM>::THREADS), 1) void mlp_ode_kernel(MlpParams p)
 {
     using C = Cfg<MP, H, TM>;
-    static_assert(TM == kTileM || (C::GROUPS && (TM == kSmallTileM || TM == kMidTileM || TM == kWideTileM)),
-                  "smaller tiles are built for the two-group schedule");
     static_assert(C::LDS_BYTES <= 160 * 1024, "LDS budget");
     static_assert(C::RTW >= 1 && C::NT % C::W == 0, "row tiles must split evenly over the waves");
-    static_assert(C::GROUPS || C::PIPE || C::W == TM / 32,
-                  "the layer-by-layer path maps one wave per column tile in layer 5");
+    static_assert(C::GROUPS || C::W >= C::CT, "one wave per column tile in layer 5");
     static_assert(!C::GROUPS || (C::RPG >= 1 && C::NKBH % 2 == 0 && C::NKB5 % 2 == 0),
                   "two-group schedule: each group's rows fill whole k-blocks of the consumer");
     __shared__ __attribute__((aligned(16))) char smem[C::LDS_BYTES];
@@ -759,17 +756,17 @@ __global__ __launch_bounds__((Cfg<MP, H, TM>::THREADS), 1) void mlp_ode_kernel(M
                     // layer's second-pass epilogue runs inside the next layer's MFMA loop over the
                     // k-blocks holding first-pass outputs (already in LDS); its results are stored
                     // and the remaining k-blocks follow after a barrier.
-                    constexpr int RP = C::RP;
-                    f32x16 X[RP][4], Y[RP][4];
-                    uint32_t pk[RP * 16 * C::WPK];
+                    constexpr int RP = C::RP, CT = C::CT;
+                    f32x16 X[RP][CT], Y[RP][CT];
+                    uint32_t pk[RP * CT * 4 * C::WPK];
                     const Rsrc w0 = make_rsrc(p.wA[0], p.wA_bytes[0]), b0 = make_rsrc(p.bias[0], p.bias_bytes[0]);
-                    init_bias<RP, 4>(X, b0, TX, lane);
-                    mma_seq<C::P1, RP, 4, C::NKB1, C::NKB1, MapAll>(X, w0, TX, in0, C::IN_STRIDE, 0, lane, [](auto) {});
-                    init_bias<RP, 4>(Y, b0, TY, lane);
-                    mma_seq<C::P1, RP, 4, C::NKB1, C::NKB1, MapAll>(Y, w0, TY, in0, C::IN_STRIDE, 0, lane, [&](auto J) {
-                        drain_step<C::PH, C::SCALE, RP, C::NKB1, decltype(J)::value>(X, pk, p.oscale[0], p.inv_in_scale[1]);
+                    init_bias<RP, CT>(X, b0, TX, lane);
+                    mma_seq<C::P1, RP, CT, C::NKB1, C::NKB1, MapAll>(X, w0, TX, in0, C::IN_STRIDE, 0, lane, [](auto) {});
+                    init_bias<RP, CT>(Y, b0, TY, lane);
+                    mma_seq<C::P1, RP, CT, C::NKB1, C::NKB1, MapAll>(Y, w0, TY, in0, C::IN_STRIDE, 0, lane, [&](auto J) {
+                        drain_step<C::PH, C::SCALE, C::NKB1, decltype(J)::value>(X, pk, p.oscale[0], p.inv_in_scale[1]);
                     });
-                    store_pass<C::PH, RP>(pk, TX, act, C::ACT_STRIDE, lane);
+                    store_pass<C::PH, RP, CT>(pk, TX, act, C::ACT_STRIDE, lane);
                     __syncthreads();
                     auto hidden = [&](int l, auto OUTP) {
                         constexpr int PO = decltype(OUTP)::value;
@@ -777,22 +774,22 @@ __global__ __launch_bounds__((Cfg<MP, H, TM>::THREADS), 1) void mlp_ode_kernel(M
                         const float osc_prev = p.oscale[l - 1], inv_prev = p.inv_in_scale[l];
                         const float osc = p.oscale[l], inv = (l < 3) ? p.inv_in_scale[l + 1] : 1.0f;
                         const int sc = (C::PH == kFP8) ? p.mscale[l] : 127;
-                        init_bias<RP, 4>(X, bl, TX, lane);
-                        mma_seq<C::PH, RP, 4, C::NKBH, C::NKBH / 2, MapHalf0<C::GH>, GMC_VPM_A>(
+                        init_bias<RP, CT>(X, bl, TX, lane);
+                        mma_seq<C::PH, RP, CT, C::NKBH, C::NKBH / 2, MapHalf0<C::GH>, GMC_VPM_A>(
                             X, wl, TX, act, C::ACT_STRIDE, 0, lane, [&](auto J) {
-                                drain_step<C::PH, C::SCALE, RP, C::NKBH / 2, decltype(J)::value>(Y, pk, osc_prev, inv_prev);
+                                drain_step<C::PH, C::SCALE, C::NKBH / 2, decltype(J)::value>(Y, pk, osc_prev, inv_prev);
                             }, sc);
-                        store_pass<C::PH, RP>(pk, TY, act, C::ACT_STRIDE, lane);
+                        store_pass<C::PH, RP, CT>(pk, TY, act, C::ACT_STRIDE, lane);
                         __syncthreads();
-                        mma_seq<C::PH, RP, 4, C::NKBH, C::NKBH / 2, MapHalf1<C::GH>>(
+                        mma_seq<C::PH, RP, CT, C::NKBH, C::NKBH / 2, MapHalf1<C::GH>>(
                             X, wl, TX, act, C::ACT_STRIDE, 0, lane, [](auto) {}, sc);
-                        init_bias<RP, 4>(Y, bl, TY, lane);
-                        mma_seq<C::PH, RP, 4, C::NKBH, C::NKBH, MapAll, GMC_VPM_P>(
+                        init_bias<RP, CT>(Y, bl, TY, lane);
+                        mma_seq<C::PH, RP, CT, C::NKBH, C::NKBH, MapAll, GMC_VPM_P>(
                             Y, wl, TY, act, C::ACT_STRIDE, 0, lane, [&](auto J) {
-                                drain_step<PO, C::SCALE, RP, C::NKBH, decltype(J)::value>(X, pk, osc, inv);
+                                drain_step<PO, C::SCALE, C::NKBH, decltype(J)::value>(X, pk, osc, inv);
                             }, sc);
                         __syncthreads();
-                        store_pass<PO, RP>(pk, TX, act, C::ACT_STRIDE, lane);
+                        store_pass<PO, RP, CT>(pk, TX, act, C::ACT_STRIDE, lane);
                         __syncthreads();
                     };
                     constexpr int NSAME = (C::PH == C::P5) ? 3 : 2;
@@ -802,22 +799,21 @@ __global__ __launch_bounds__((Cfg<MP, H, TM>::THREADS), 1) void mlp_ode_kernel(M
                     // layer 5 (5 x H, rows padded to one tile) over the first-pass k-blocks while
                     // layer 4's second pass drains; wave w < 4 owns sample column tile w, further
                     // waves only drain
-                    constexpr int CT5 = TM / 32;
                     f32x16 out[1][1];
                     const Rsrc w4 = make_rsrc(p.wA[4], p.wA_bytes[4]);
                     auto drain4 = [&](auto J) {
-                        drain_step<C::P5, C::SCALE, RP, C::NKB5 / 2, decltype(J)::value>(Y, pk, p.oscale[3], 1.0f);
+                        drain_step<C::P5, C::SCALE, C::NKB5 / 2, decltype(J)::value>(Y, pk, p.oscale[3], 1.0f);
                     };
-                    if (C::W == CT5 || wave < CT5) {
+                    if (C::W == CT || wave < CT) {
                         init_bias<1, 1>(out, make_rsrc(p.bias[4], p.bias_bytes[4]), 0, lane);
                         mma_seq<C::P5, 1, 1, C::NKB5, C::NKB5 / 2, MapHalf0<C::G5>, GMC_VPM_5>(
                             out, w4, 0, act, C::ACT_STRIDE, wave, lane, drain4);
                     } else {
                         sfor<C::NKB5 / 2>(drain4);
                     }
-                    store_pass<C::P5, RP>(pk, TY, act, C::ACT_STRIDE, lane);
+                    store_pass<C::P5, RP, CT>(pk, TY, act, C::ACT_STRIDE, lane);
                     __syncthreads();
-                    if (C::W == CT5 || wave < CT5) {
+                    if (C::W == CT || wave < CT) {
                         mma_seq<C::P5, 1, 1, C::NKB5, C::NKB5 / 2, MapHalf1<C::G5>>(
                             out, w4, 0, act, C::ACT_STRIDE, wave, lane, [](auto) {});
                         const int sn = wave * 32 + (lane & 31);
@@ -833,7 +829,7 @@ __global__ __launch_bounds__((Cfg<MP, H, TM>::THREADS), 1) void mlp_ode_kernel(M
                 }
 
                 // layer 1: 10 -> H (reads in0, writes the activation tile: no barrier before writing)
-                dense_silu<C::P1, C::PH, C::RTW, C::NKB1, C::SCALE, false>(
+                dense_silu<C::P1, C::PH, C::RTW, C::CT, C::NKB1, C::SCALE, false>(
                     make_rsrc(p.wA[0], p.wA_bytes[0]), make_rsrc(p.bias[0], p.bias_bytes[0]), T0, in0, C::IN_STRIDE, act, C::ACT_STRIDE, lane,
                     p.oscale[0], p.inv_in_scale[1]);
                 __syncthreads();
@@ -843,21 +839,21 @@ __global__ __launch_bounds__((Cfg<MP, H, TM>::THREADS), 1) void mlp_ode_kernel(M
                 constexpr int NSAME = (C::PH == C::P5) ? 3 : 2;
 #pragma unroll 1
                 for (int l = 1; l <= NSAME; ++l) {
-                    dense_silu<C::PH, C::PH, C::RTW, C::NKBH, C::SCALE, true>(
+                    dense_silu<C::PH, C::PH, C::RTW, C::CT, C::NKBH, C::SCALE, true>(
                         make_rsrc(p.wA[l], p.wA_bytes[l]), make_rsrc(p.bias[l], p.bias_bytes[l]), T0,
                         act, C::ACT_STRIDE, act, C::ACT_STRIDE, lane, p.oscale[l],
                         l < 3 ? p.inv_in_scale[l + 1] : 1.0f, (C::PH == kFP8) ? p.mscale[l] : 127);
                     __syncthreads();
                 }
                 if constexpr (NSAME == 2) {
-                    dense_silu<C::PH, C::P5, C::RTW, C::NKBH, C::SCALE, true>(
+                    dense_silu<C::PH, C::P5, C::RTW, C::CT, C::NKBH, C::SCALE, true>(
                         make_rsrc(p.wA[3], p.wA_bytes[3]), make_rsrc(p.bias[3], p.bias_bytes[3]), T0,
                         act, C::ACT_STRIDE, act, C::ACT_STRIDE, lane, p.oscale[3], 1.0f,
                         (C::PH == kFP8) ? p.mscale[3] : 127);
                     __syncthreads();
                 }
                 // layer 5: H -> 5 (rows padded to 32); wave w handles sample column tile w
-                {
+                if (C::W == C::CT || wave < C::CT) {
                     f32x16 out[1][1];
                     init_bias<1, 1>(out, make_rsrc(p.bias[4], p.bias_bytes[4]), 0, lane);
                     mma_pass<C::P5, 1, 1, C::NKB5>(out, make_rsrc(p.wA[4], p.wA_bytes[4]), 0, act,
@@ -1192,10 +1188,9 @@ inline MlpParams sample_range(const MlpParams &p, int64_t off, int64_t cnt)
 }
 
 // Launches with at most kSmallTileM (kMidTileM, kWideTileM) samples per compute unit (the tail steps
-// of a transport run, small requests) take 32-sample (64-, 96-sample) tiles when the model runs the
-// two-group schedule: one round of them covers the launch on every CU, and a tile's latency
+// of a transport run, small requests) take 32-sample (64-, 96-sample) tiles: one round of them covers the launch on every CU, and a tile's latency
 // falls with its matrix work (BF16 width 512: an evaluation of 32 / 64 / 96 / 128 samples takes
-// 13 / 18 / 29 / 40 us).  When only the device knows the count (n_dev) and its bound p.n is
+// 13 / 18 / 29 / 40 us, FP32 width 256 30 / 55 / 79 / 104 us).  When only the device knows the count (n_dev) and its bound p.n is
 // larger, the choice is made on the device (MlpParams::n_dev_large; between 32, 64 and 128) without a
 // read-back; a sample's result is the same with every tile size.  A count known on the host whose
 // last round of 128-sample tiles would hold at most 96 samples per CU runs that remainder as one
@@ -1205,36 +1200,34 @@ hipError_t launch_one(const MlpParams &p, int cu, hipStream_t s)
 {
     MlpParams q = p;
     q.n_dev_large = nullptr;
-    if constexpr (Cfg<MP, H>::GROUPS) {
-        const int64_t small = (int64_t)kSmallTileM * cu, mid = (int64_t)kMidTileM * cu, wide = (int64_t)kWideTileM * cu;
-        if (p.n <= small) return launch_tiles<MP, H, kSmallTileM>(q, p.n, cu, s);
-        if (!p.n_dev) {
-            if (p.n <= mid) return launch_tiles<MP, H, kMidTileM>(q, p.n, cu, s);
-            if (p.n <= wide) return launch_tiles<MP, H, kWideTileM>(q, p.n, cu, s);
-            const int64_t round = (int64_t)kTileM * cu, rem = p.n % round;
-            if (!p.noise && !p.raw && rem > 0 && rem <= wide) {
-                const MlpParams head = sample_range(q, 0, p.n - rem);
-                const hipError_t e = launch_tiles<MP, H, kTileM>(head, head.n, cu, s);
-                if (e != hipSuccess) return e;
-                const MlpParams tail = sample_range(q, p.n - rem, rem);
-                return rem <= small ? launch_tiles<MP, H, kSmallTileM>(tail, rem, cu, s)
-                       : rem <= mid ? launch_tiles<MP, H, kMidTileM>(tail, rem, cu, s)
-                                    : launch_tiles<MP, H, kWideTileM>(tail, rem, cu, s);
-            }
-        } else if (p.n_dev_large) {
-            // 32-sample kernel, then the 64-sample one, each handing on what it does not take
-            q.n_dev_large = p.n_dev_large;
-            q.small_max = small;
-            hipError_t e = launch_tiles<MP, H, kSmallTileM>(q, small, cu, s);
+    const int64_t small = (int64_t)kSmallTileM * cu, mid = (int64_t)kMidTileM * cu, wide = (int64_t)kWideTileM * cu;
+    if (p.n <= small) return launch_tiles<MP, H, kSmallTileM>(q, p.n, cu, s);
+    if (!p.n_dev) {
+        if (p.n <= mid) return launch_tiles<MP, H, kMidTileM>(q, p.n, cu, s);
+        if (p.n <= wide) return launch_tiles<MP, H, kWideTileM>(q, p.n, cu, s);
+        const int64_t round = (int64_t)kTileM * cu, rem = p.n % round;
+        if (!p.noise && !p.raw && rem > 0 && rem <= wide) {
+            const MlpParams head = sample_range(q, 0, p.n - rem);
+            const hipError_t e = launch_tiles<MP, H, kTileM>(head, head.n, cu, s);
             if (e != hipSuccess) return e;
-            q.n_dev = p.n_dev_large;
-            q.n_dev_large = p.n <= mid ? nullptr : p.n_dev_large + 1;
-            q.small_max = mid;
-            e = launch_tiles<MP, H, kMidTileM>(q, std::min<int64_t>(p.n, mid), cu, s);
-            if (e != hipSuccess || p.n <= mid) return e;
-            q.n_dev = p.n_dev_large + 1;
-            q.n_dev_large = nullptr;
+            const MlpParams tail = sample_range(q, p.n - rem, rem);
+            return rem <= small ? launch_tiles<MP, H, kSmallTileM>(tail, rem, cu, s)
+                   : rem <= mid ? launch_tiles<MP, H, kMidTileM>(tail, rem, cu, s)
+                                : launch_tiles<MP, H, kWideTileM>(tail, rem, cu, s);
         }
+    } else if (p.n_dev_large) {
+        // 32-sample kernel, then the 64-sample one, each handing on what it does not take
+        q.n_dev_large = p.n_dev_large;
+        q.small_max = small;
+        hipError_t e = launch_tiles<MP, H, kSmallTileM>(q, small, cu, s);
+        if (e != hipSuccess) return e;
+        q.n_dev = p.n_dev_large;
+        q.n_dev_large = p.n <= mid ? nullptr : p.n_dev_large + 1;
+        q.small_max = mid;
+        e = launch_tiles<MP, H, kMidTileM>(q, std::min<int64_t>(p.n, mid), cu, s);
+        if (e != hipSuccess || p.n <= mid) return e;
+        q.n_dev = p.n_dev_large + 1;
+        q.n_dev_large = nullptr;
     }
     return launch_tiles<MP, H, kTileM>(q, p.n, cu, s);
 }

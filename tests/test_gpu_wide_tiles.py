@@ -12,6 +12,7 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("net,precision,hidden", [("mlp", "bf16", 512), ("mlp", "fp8", 512), ("mlp", "bf16", 256),
+                                                  ("mlp", "fp32", 256), ("mlp", "fp32", 128),
                                                   ("mlp", "fp8", 256), ("film", "bf16", 512), ("film", "bf16", 256)])
 @pytest.mark.parametrize("integrator", ["euler", "rk4"])
 def test_tile_sizes_agree(net, precision, hidden, integrator):
