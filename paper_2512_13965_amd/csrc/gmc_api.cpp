@@ -419,7 +419,6 @@ int launch_walk_api(gmc::WalkParams p, int64_t n, int mode, uint64_t seed, uint6
     p.path = out.path;
     p.ncoll = ncoll_opt;
     p.n = n;
-    p.n_dev = nullptr;
     p.mode = mode;
     p.seed = seed;
     p.id_base = id_base;

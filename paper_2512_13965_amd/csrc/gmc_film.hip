@@ -11,9 +11,9 @@
 //   v   = W_o h + b_o
 //
 // One persistent workgroup per CU carries a tile of samples (128; 32, 64 or 96 where that covers the
-// launch in one round) through all evaluations; LDS holds the input row tile (32 features), the embedding tile (32 features) and the residual
-// stream h (128 x H), all in the operand precision, and the ODE state.  The input layer and the
-// embedding are MFMA contractions over the input row tile.
+// launch in one round) through all evaluations; LDS holds the input row tile (32 features), the
+// embedding tile (32 features) and the residual stream h, all in the operand precision, and the ODE
+// state.  The input layer and the embedding are MFMA contractions over the input row tile.
 //   * BF16, H >= 256: two groups of four waves (two waves per SIMD).  Group 0 owns the first
 //     half of a block's output rows, group 1 the second; per block, three barrier-separated
 //     phases pair one group's matrix k-loop with the other group's epilogue on the same SIMDs

@@ -123,10 +123,7 @@ struct WalkParams {
     int32_t *face;
     float *pos, *dcos, *dsin, *path;
     uint32_t *ncoll;          // optional
-    const uint64_t *ids;      // optional per-particle random stream ids (else id_base + i)
-    const uint64_t *keys;     // optional per-particle Philox keys (else seed)
     int64_t n;
-    const unsigned long long *n_dev;   // optional: particle count read on the device (<= n)
     int mode;
     uint64_t seed, id_base;
 };

@@ -1188,10 +1188,11 @@ inline MlpParams sample_range(const MlpParams &p, int64_t off, int64_t cnt)
 }
 
 // Launches with at most kSmallTileM (kMidTileM, kWideTileM) samples per compute unit (the tail steps
-// of a transport run, small requests) take 32-sample (64-, 96-sample) tiles: one round of them covers the launch on every CU, and a tile's latency
-// falls with its matrix work (BF16 width 512: an evaluation of 32 / 64 / 96 / 128 samples takes
-// 13 / 18 / 29 / 40 us, FP32 width 256 30 / 55 / 79 / 104 us).  When only the device knows the count (n_dev) and its bound p.n is
-// larger, the choice is made on the device (MlpParams::n_dev_large; between 32, 64 and 128) without a
+// of a transport run, small requests) take 32-sample (64-, 96-sample) tiles: one round of them
+// covers the launch on every CU, and a tile's latency falls with its matrix work (an evaluation of
+// 32 / 64 / 96 / 128 samples takes 13 / 18 / 29 / 40 us in BF16 at width 512 and 30 / 55 / 79 / 104 us
+// in FP32 at width 256).  When only the device knows the count (n_dev) and its bound p.n is larger,
+// the choice is made on the device (MlpParams::n_dev_large; between 32, 64 and 128) without a
 // read-back; a sample's result is the same with every tile size.  A count known on the host whose
 // last round of 128-sample tiles would hold at most 96 samples per CU runs that remainder as one
 // round of smaller tiles.

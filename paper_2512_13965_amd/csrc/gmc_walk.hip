@@ -13,13 +13,13 @@ constexpr int kWalkThreads = 256;
 
 // The conditions p.* of walks 0 .. n-1 to their exit records (see run_walks).  Bound by vector
 // issue; eight blocks per CU (64 registers) cover the latency of the condition loads.
-template <bool ANALOG, bool XY, bool KEYS>
+template <bool ANALOG, bool XY>
 __global__ __launch_bounds__(kWalkThreads, kWalkBlocksPerCu) void walk_kernel(WalkParams p)
 {
     __shared__ WalkGroups groups[kWalkThreads / 64];
     __shared__ uint32_t pool;
-    run_walks<ANALOG, XY, KEYS>(
-        p.n_dev ? (int64_t)*p.n_dev : p.n, p.seed, groups, &pool,
+    run_walks<ANALOG, XY, false>(
+        p.n, p.seed, groups, &pool,
         [&](int64_t i) {
             WalkStart w;
             const float s = p.sin_th[i];
@@ -31,8 +31,8 @@ __global__ __launch_bounds__(kWalkThreads, kWalkBlocksPerCu) void walk_kernel(Wa
             w.v = s;
             w.tau = expf(p.log_tau[i]);
             w.c = p.c[i];
-            w.stream = p.ids ? p.ids[i] : p.id_base + (uint64_t)i;
-            w.key = KEYS ? p.keys[i] : 0u;
+            w.stream = p.id_base + (uint64_t)i;
+            w.key = p.seed;
             return w;
         },
         [&](int64_t i, int face, float pos, float u, float v, float len, uint32_t ncoll) {
@@ -48,12 +48,9 @@ __global__ __launch_bounds__(kWalkThreads, kWalkBlocksPerCu) void walk_kernel(Wa
 template <bool ANALOG>
 void launch_walk_mode(const WalkParams &p, int grid, hipStream_t s)
 {
-    const bool xy = p.omega_x && !p.x_in;
     const dim3 g(grid), b(kWalkThreads);
-    if (xy && p.keys) hipLaunchKernelGGL((walk_kernel<ANALOG, true, true>), g, b, 0, s, p);
-    else if (xy) hipLaunchKernelGGL((walk_kernel<ANALOG, true, false>), g, b, 0, s, p);
-    else if (p.keys) hipLaunchKernelGGL((walk_kernel<ANALOG, false, true>), g, b, 0, s, p);
-    else hipLaunchKernelGGL((walk_kernel<ANALOG, false, false>), g, b, 0, s, p);
+    if (p.omega_x && !p.x_in) hipLaunchKernelGGL((walk_kernel<ANALOG, true>), g, b, 0, s, p);
+    else hipLaunchKernelGGL((walk_kernel<ANALOG, false>), g, b, 0, s, p);
 }
 
 __global__ __launch_bounds__(256) void decode_kernel(const float *__restrict__ raw, int64_t n,
@@ -91,10 +88,9 @@ __global__ __launch_bounds__(256) void split_kernel(WalkParams p, int32_t *flag)
     const float la = p.log_aspect ? p.log_aspect[i] : 0.0f;
     const float wa = la == 0.0f ? 1.0f : expf(la);
     const float u = p.omega_x ? p.omega_x[i] : sqrtf(fmaxf(1.0f - s * s, 0.0f));
-    const uint64_t id = p.ids ? p.ids[i] : p.id_base + (uint64_t)i;
-    const uint64_t key = p.keys ? p.keys[i] : p.seed;
     Exit e;
-    const bool unc = uncollided_exit(expf(p.log_tau[i]), p.c[i], p.y_in[i], u, s, wa, split_draw(key, id), e);
+    const bool unc = uncollided_exit(expf(p.log_tau[i]), p.c[i], p.y_in[i], u, s, wa,
+                                     split_draw(p.seed, p.id_base + (uint64_t)i), e);
     flag[i] = unc ? 1 : 0;
     if (unc) {
         p.face[i] = e.face;
