@@ -816,10 +816,33 @@ __global__ __launch_bounds__(kTallyThreads) void apply_kernel(BankDev in, int64_
     tally_flush(tl, cd);
 }
 
-__global__ void set_u64_kernel(unsigned long long *p, unsigned long long v, int n)
+// Ends a step or an injection: the bank's counters and the streamed crossings to the host's pinned
+// copy (a store over the bus; the stream's end makes it visible), the other bank's counters and the
+// split's count cleared for the next step.  One kernel of 3 us in the place of two that cleared and
+// two copies.
+__global__ __launch_bounds__(256) void finish_kernel(const unsigned long long *ctr, unsigned long long *other,
+                                                     unsigned long long *split_count,
+                                                     const unsigned long long *streamed, unsigned long long *host, int n)
 {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) p[i] = (i == 0) ? v : 0ull;
+    for (int i = threadIdx.x; i < n; i += 256) {
+        host[i] = ctr[i];
+        other[i] = 0ull;
+    }
+    if (threadIdx.x == 0) {
+        host[n] = *streamed;
+        *split_count = 0ull;
+    }
+}
+
+// After a step or injection that failed part way: the counters as its successor expects them.
+__global__ __launch_bounds__(256) void reset_kernel(unsigned long long *ctr, unsigned long long alive,
+                                                    unsigned long long *other, unsigned long long *split_count, int n)
+{
+    for (int i = threadIdx.x; i < n; i += 256) other[i] = 0ull;
+    if (threadIdx.x == 0) {
+        ctr[0] = alive;
+        *split_count = 0ull;
+    }
 }
 
 // Clears the tallies of cells [cell0, cell0 + n).
@@ -895,6 +918,7 @@ struct gmc_world {
     std::vector<StepGraph> step_graphs;
     // host bookkeeping
     int64_t n_alive = 0;
+    bool broken = false;                      // the last step or injection failed part way
     std::vector<int64_t> alive_pp;
     std::vector<ProblemDev> prob_host;
     std::vector<std::vector<double>> siga_host;   // per problem slot: sigma_a of its cells
@@ -971,14 +995,32 @@ void plan(gmc_world *w, Layout &L)
     L.add((void **)&w->counters, 8 * 2 * (1 + P));
 }
 
-int sync_counters(gmc_world *w, int which, hipStream_t s)
+// Enqueue the end of a step or injection that left the particles in bank `which`.
+hipError_t enqueue_finish(gmc_world *w, int which, hipStream_t s)
 {
-    const size_t bytes = 8 * (size_t)(1 + w->max_problems);
-    hipError_t e = hipMemcpyAsync(w->host_counters, w->cnt(which), bytes, hipMemcpyDeviceToHost, s);
-    if (e == hipSuccess)
-        e = hipMemcpyAsync(w->host_counters + 1 + w->max_problems, w->streamed, 8, hipMemcpyDeviceToHost, s);
-    if (e == hipSuccess) e = hipStreamSynchronize(s);
+    hipLaunchKernelGGL(finish_kernel, dim3(1), dim3(256), 0, s, w->cnt(which), w->cnt(1 - which), w->s_count,
+                       w->streamed, w->host_counters, 1 + w->max_problems);
+    return hipGetLastError();
+}
+
+// Before a step or injection: the counters put right if the last one failed.  Until
+// sync_counters has run, this one counts as failed.
+hipError_t begin_counters(gmc_world *w, hipStream_t s)
+{
+    const bool was = w->broken;
+    w->broken = true;
+    if (!was) return hipSuccess;
+    hipLaunchKernelGGL(reset_kernel, dim3(1), dim3(256), 0, s, w->cnt(w->cur), (unsigned long long)w->n_alive,
+                       w->cnt(1 - w->cur), w->s_count, 1 + w->max_problems);
+    return hipGetLastError();
+}
+
+// Wait for it and take its counts over.
+int sync_counters(gmc_world *w, hipStream_t s)
+{
+    const hipError_t e = hipStreamSynchronize(s);
     if (e != hipSuccess) return set_hip_error(e, "transport: reading counters");
+    w->broken = false;
     w->n_alive = (int64_t)w->host_counters[0];
     for (int p = 0; p < w->max_problems; ++p) w->alive_pp[p] = (int64_t)w->host_counters[1 + p];
     return GMC_OK;
@@ -1031,6 +1073,7 @@ int gmc_world_create(int64_t bank_capacity, int32_t max_problems, int64_t max_ce
     std::memset(w->host_counters, 0, 8 * (size_t)(2 + max_problems));
     e = hipMemset(w->counters, 0, 8 * 2 * (size_t)(1 + max_problems));
     if (e == hipSuccess) e = hipMemset(w->streamed, 0, 8);
+    if (e == hipSuccess) e = hipMemset(w->s_count, 0, 8);
     if (e == hipSuccess) e = hipDeviceSynchronize();
     if (e != hipSuccess) {
         (void)hipHostFree(w->host_counters);
@@ -1198,8 +1241,9 @@ int gmc_world_inject(gmc_world *w, int32_t pid, uint64_t h_begin, int64_t count,
         if (cu <= 0) return set_error(GMC_EDEVICE, "gmc_world_inject: cannot query the device");
         const int which = w->cur;
         unsigned long long *ctr = w->cnt(which);
-        // the bank's particle counter restarts at the number alive; per-problem counts continue
-        hipLaunchKernelGGL(set_u64_kernel, dim3(1), dim3(1), 0, s, ctr, (unsigned long long)w->n_alive, 1);
+        // the bank's counters stand at the particles alive, in all and per problem, and continue
+        const hipError_t eb = begin_counters(w, s);
+        if (eb != hipSuccess) return set_hip_error(eb, "gmc_world_inject: launch");
         if (w->src_face[pid] >= 0) {
             hipLaunchKernelGGL(surface_birth_kernel, dim3(tally_blocks(count, cu)), dim3(kTallyThreads), 0, s, w->cells(),
                                pid, (uint32_t)h_begin, count, w->bank[which], ctr, ctr + 1);
@@ -1246,8 +1290,9 @@ int gmc_world_inject(gmc_world *w, int32_t pid, uint64_t h_begin, int64_t count,
                                (uint32_t)h_begin, count, w->e_face, w->e_pos, w->e_dcos, w->e_dsin,
                                w->e_path, w->bank[which], ctr, ctr + 1);
         hipError_t e = hipGetLastError();
+        if (e == hipSuccess) e = enqueue_finish(w, which, s);
         if (e != hipSuccess) return set_hip_error(e, "gmc_world_inject: launch");
-        const int rc = sync_counters(w, which, s);
+        const int rc = sync_counters(w, s);
         if (rc != GMC_OK) return rc;
     }
     if (n_alive_out) *n_alive_out = w->n_alive;
@@ -1329,7 +1374,7 @@ int32_t only_problem(const gmc_world *w)
     return only;
 }
 
-// Enqueue one transport step on `s`: gather, sampler, counter reset, apply.  Grids are sized for
+// Enqueue one transport step on `s`: gather, sampler, apply, counters to the host.  Grids are sized for
 // `n_launch` particles; the kernels process n_dev[0] of them when n_dev is given (a captured step
 // serves every count up to its bucket), else n_launch.
 int enqueue_step(gmc_world *w, int sampler, const gmc_model *m, int K, hipStream_t s, int64_t n_launch,
@@ -1341,7 +1386,6 @@ int enqueue_step(gmc_world *w, int sampler, const gmc_model *m, int K, hipStream
     if (cu <= 0) return set_error(GMC_EDEVICE, "gmc_transport_step: cannot query the device");
     const CondDev o{w->c_ltau, w->c_c, w->c_yin, w->c_sth, w->c_la, w->c_ox, w->ids, w->keys};
     if (split) {
-        hipLaunchKernelGGL(set_u64_kernel, dim3(1), dim3(1), 0, s, w->s_count, 0ull, 1);
         const dim3 grid((unsigned)std::min<int64_t>((n_launch + 63) / 64, (int64_t)cu * kStreamBlocksPerCu));
         const int32_t only = w->graphs ? -1 : only_problem(w);
         if (only >= 0)
@@ -1398,13 +1442,12 @@ int enqueue_step(gmc_world *w, int sampler, const gmc_model *m, int K, hipStream
     }
     if (e != hipSuccess) return set_hip_error(e, "gmc_transport_step: sampler");
     unsigned long long *ctr = w->cnt(nxt);
-    hipLaunchKernelGGL(set_u64_kernel, dim3(blocks_for(1 + w->max_problems)), dim3(256), 0, s,
-                       ctr, 0ull, 1 + w->max_problems);
     hipLaunchKernelGGL(apply_kernel, dim3(tally_blocks(n_launch, cu)), dim3(kTallyThreads), 0, s, w->bank[cur], n_launch,
                        n_dev, w->e_face, w->e_pos, w->e_dcos, w->e_dsin, w->e_path, w->s_slot,
                        ExitDev{w->s_face, w->s_pos, w->s_dcos, w->s_dsin, w->s_path}, w->cells(), w->bank[nxt], ctr,
                        ctr + 1);
     e = hipGetLastError();
+    if (e == hipSuccess) e = enqueue_finish(w, nxt, s);
     if (e != hipSuccess) return set_hip_error(e, "gmc_transport_step: apply");
     return GMC_OK;
 }
@@ -1477,6 +1520,8 @@ int gmc_transport_step(gmc_world *w, int sampler, const gmc_model *m, int K, voi
     const int64_t n = w->n_alive;
     if (n > 0) {
         int rc;
+        const hipError_t eb = begin_counters(w, s);
+        if (eb != hipSuccess) return set_hip_error(eb, "gmc_transport_step: launch");
         if (w->graphs) {
             hipGraphExec_t x = nullptr;
             rc = step_graph(w, sampler, m, K, step_bucket(w, n), &x);
@@ -1490,7 +1535,7 @@ int gmc_transport_step(gmc_world *w, int sampler, const gmc_model *m, int K, voi
         const int nxt = 1 - w->cur;
         w->cur = nxt;
         w->stepped += n;
-        rc = sync_counters(w, nxt, s);
+        rc = sync_counters(w, s);
         if (rc != GMC_OK) return rc;
     }
     if (n_alive_out) *n_alive_out = w->n_alive;
