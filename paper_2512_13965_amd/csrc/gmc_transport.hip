@@ -79,9 +79,12 @@ struct CellsDev {
 };
 
 // Threads of a workgroup that tallies, and workgroups per compute unit of such a launch: its
-// workgroups take tiles of that many particles in turn, so that each fills one table.
-constexpr int kTallyThreads = 512;
-constexpr int kTallyBlocksPerCu = 2;
+// workgroups take tiles of that many particles in turn, so that each fills one table.  What a
+// launch adds to the global tallies grows with the number of tables: the checkerboard's 128 steps
+// take 17.6 ms with one table of 4,096 cells to a CU and 18.1 ms with two of 2,048 (the lattice's 30
+// smaller ones 16.3 and 16.1 ms).
+constexpr int kTallyThreads = 1024;
+constexpr int kTallyBlocksPerCu = 1;
 
 // Per-workgroup tally staging: the visit tallies of a workgroup's particles are summed per cell in
 // an LDS hash table and added to the global ones at its end.  Particles near a source crowd into
@@ -94,7 +97,7 @@ struct TallyTable {
     int32_t key[SLOTS];
     double v[SLOTS * kVisitTallies];
 };
-using TallyLds = TallyTable<2048>;
+using TallyLds = TallyTable<4096>;
 
 template <int SLOTS>
 __device__ __forceinline__ void tally_init(TallyTable<SLOTS> &tl)
@@ -756,7 +759,7 @@ struct ExitDev {
 
 // Stages 3-4 for every alive particle, survivors compacted into `out`.  Bound by its global atomics
 // (5 a cell of a workgroup's table and 2 a wave of survivors in an earlier form): 10^6 particles on
-// the 32 x 32 checkerboard 409 -> 43 us, 2 10^5 on the lattice 123 -> 26 us.
+// the 32 x 32 checkerboard 409 -> 37 us, 2 10^5 on the lattice 123 -> 26 us.
 __global__ __launch_bounds__(kTallyThreads) void apply_kernel(BankDev in, int64_t n_arg,
                                                               const unsigned long long *n_dev,
                                                               const int32_t *face_c, const float *pos,

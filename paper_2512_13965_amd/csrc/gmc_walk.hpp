@@ -22,9 +22,9 @@
 // short: same-address atomics complete one in 13 ns (2^23 walks at tau = 1, 64 to an atomic:
 // 1.7 ms).
 // Measured, against one lane per walk throughout and a launch-wide counter: 2^20 walks of mixed
-// cells (longest 5,200 flights) 2.90 -> 0.136 ms, 10^6 at tau = 100, c = 0.99 (12,000) 8.6 ->
-// 0.63 ms, 2^23 at tau = 100 12.7 -> 2.7 ms (2.4e11 flights/s), 2^23 at tau = 1 1.7 -> 0.25 ms.
-// The longest walk of a launch costs 20 ns a flight in the second regime.
+// cells (longest 5,200 flights) 2.95 -> 0.108 ms, 10^6 at tau = 100, c = 0.99 (12,000) 8.5 ->
+// 0.59 ms, 2^23 at tau = 100 12.7 -> 2.7 ms (2.4e11 flights/s), 2^23 at tau = 1 1.7 -> 0.25 ms.
+// The longest walk of a launch costs 15 ns a flight in the second regime.
 #pragma once
 
 #include "gmc_device.hpp"
@@ -395,7 +395,26 @@ __device__ __forceinline__ void run_walks(int64_t n, uint64_t seed, WalkGroups *
             const int coord = j == 1 ? 1 : (j == 2 ? 2 : 0);
             const f32v4 *step = (const f32v4 *)&G.step[coord][base];
             float *at = &G.at[coord][base];    // the lanes from j = 3 on repeat lane 0
-            if (g == 4) {
+            if (g == 64) {                     // base = 0
+                const f32v4 *step = (const f32v4 *)&G.step[coord][0];
+                float *at = &G.at[coord][0];
+                // the longest walks: eight flights at a time, the next eight's steps on their way;
+                // unrolled, without the loop's moves: 20 -> 15 ns a flight (24 steps on their way spill)
+                f32v4 s[2][4];
+#pragma unroll
+                for (int c = 0; c < 2; ++c)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) s[c][i] = step[4 * c + i];
+#pragma unroll
+                for (int c = 0; c < 8; ++c) {
+                    val = walk_chain<8>(val, s[c % 2], at + 8 * c);
+                    if (c + 2 < 8) {
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) s[c % 2][i] = step[4 * (c + 2) + i];
+                    }
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            } else if (g == 4) {
                 const f32v4 s[2] = {step[0], step[1]};
                 val = walk_chain<4>(val, s, at);
             } else {

@@ -1,5 +1,5 @@
 """Tallies and survivor counts of workgroups that take several tiles of particles: the same
-histories whatever the launch's size (edges of a 512-particle tile, one tile to a workgroup,
+histories whatever the launch's size (edges of a 1,024-particle tile, one tile to a workgroup,
 several), and whatever other problems share the bank (more of them than one table of cells
 holds).  Tallies of the same histories differ by the order of FP64 additions only: 1e-12 of the
 cell's sum bounds it for 10^6 positive addends of one rounding each (2^-53 each, averaged)."""
@@ -20,7 +20,7 @@ def _same(a, b, label):
         np.testing.assert_allclose(a[k], b[k], rtol=1e-12, atol=0.0, err_msg=f"{label} {k}")
 
 
-@pytest.mark.parametrize("n", [1, 511, 512, 513, 400_001])
+@pytest.mark.parametrize("n", [1, 511, 512, 513, 1023, 1025, 400_001])
 def test_chunks_of_any_size_tally_the_same(n):
     binding = require_gpu()
     prob = inputs.checkerboard_problem(8, tau=(0.5, 3.0), src=2)
@@ -35,7 +35,7 @@ def test_chunks_of_any_size_tally_the_same(n):
 
 def test_many_problems_share_workgroups():
     # 600 problems of 5 to 9 histories each: a workgroup's tile holds many problems, and their
-    # 600 * 25 cells overflow its table of 2,048
+    # 600 * 25 cells overflow its table of 4,096
     binding = require_gpu()
     P, prob = 600, inputs.checkerboard_problem(5, tau=(0.5, 3.0), src=1)
     hist = [5 + i % 5 for i in range(P)]
