@@ -937,6 +937,44 @@ struct WaveCfg {
     static constexpr int LDS_BYTES = OFF_B + (4 * H + 32) * 4;
 };
 
+// Lane n + 32's value in lane n.
+__device__ __forceinline__ float upper_half(float x)
+{
+    const auto r = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(uint32_t, x), __builtin_bit_cast(uint32_t, x),
+                                                    false, false);
+    return __builtin_bit_cast(float, (uint32_t)r[1]);
+}
+
+// Layer 1's operand of 32 samples in one wave: the input row [x0..x4, t, cf0..cf5, 0 x 4], of which
+// lanes 0-31 hold features 0-7 and lanes 32-63 features 8-15; of the state xi lanes 0-31 hold x0..x3
+// and lanes 32-63 x4 (as the output layer's rows fall).  c01, c23, c45: the condition in pairs.
+__device__ __forceinline__ u32x4 wave_input(const float (&xi)[4], float t, uint32_t c01, uint32_t c23, uint32_t c45,
+                                            int half)
+{
+    const uint32_t x4t = pack_bf16(upper_half(xi[0]), t);
+    return half ? u32x4{c23, c45, 0u, 0u} : u32x4{pack_bf16(xi[0], xi[1]), pack_bf16(xi[2], xi[3]), x4t, c01};
+}
+
+// x <- x + dt v, or the RK4 stage (as in mlp_ode_kernel); xi: the next evaluation's input.
+template <bool rk4>
+__device__ __forceinline__ void wave_update(float (&x)[4], float (&xi)[4], float (&ks)[4], const f32x16 &out, int stage,
+                                            float dt)
+{
+#pragma unroll
+    for (int d = 0; d < 4; ++d) {
+        const float v = out[d];
+        if constexpr (!rk4) {
+            x[d] += v * dt;
+            xi[d] = x[d];
+        } else if (stage < 3) {
+            ks[d] = stage == 0 ? v : ks[d] + 2.0f * v;
+            xi[d] = x[d] + (stage == 2 ? dt : 0.5f * dt) * v;
+        } else {
+            xi[d] = x[d] = x[d] + (dt * (1.0f / 6.0f)) * (ks[d] + v);
+        }
+    }
+}
+
 // Four packed words as a BF16 operand fragment.
 template <typename F>
 __device__ __forceinline__ void put16(F &f, const uint32_t *w)
@@ -955,6 +993,8 @@ __global__ __launch_bounds__((WaveCfg<MP>::THREADS), WaveCfg<MP>::W / 4) void ml
     __shared__ __attribute__((aligned(16))) char smem[C::LDS_BYTES];
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, half = lane >> 5;
 
+    const int64_t n_items = p.n_dev ? (int64_t)*p.n_dev : p.n;
+    if (n_items == 0) return;                              // taken by the teams
     // weights and biases to LDS; FP8 fragments (32 bytes a lane) as two lines of 16-byte halves
     auto copy = [&](int off, const void *src, int bytes) {
         for (int b = tid * 16; b < bytes; b += C::THREADS * 16)
@@ -977,7 +1017,6 @@ __global__ __launch_bounds__((WaveCfg<MP>::THREADS), WaveCfg<MP>::W / 4) void ml
     copy(C::OFF_B + 4 * C::H * 4, p.bias[4], 32 * 4);
     __syncthreads();
 
-    const int64_t n_items = p.n_dev ? (int64_t)*p.n_dev : p.n;
     const int64_t ntiles = (n_items + 31) / 32;
     const float dt = 1.0f / (float)p.K;
     const int nevals = rk4 ? 4 * p.K : p.K;
@@ -1001,18 +1040,10 @@ __global__ __launch_bounds__((WaveCfg<MP>::THREADS), WaveCfg<MP>::W / 4) void ml
         }
         return v;
     };
-    auto upper = [](float x) {               // lane n's value in lane n + 32
-        const auto r = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(uint32_t, x),
-                                                        __builtin_bit_cast(uint32_t, x), false, false);
-        return __builtin_bit_cast(float, (uint32_t)r[1]);
-    };
-
     for (int64_t tile = (int64_t)wave * gridDim.x + blockIdx.x; tile < ntiles; tile += (int64_t)gridDim.x * C::W) {
         const int64_t i = tile * 32 + (lane & 31);
         float z[5], cf[6];
         sampler_inputs(p, i, n_items, z, cf);
-        // the input row [x0..x4, t, cf0..cf5, 0 x 4]: lanes 0-31 hold features 0-7, lanes 32-63 8-15;
-        // of the state lanes 0-31 hold x0..x3, lanes 32-63 x4 (as the output layer's rows fall)
         const uint32_t c01 = pack_bf16(cf[0], cf[1]), c23 = pack_bf16(cf[2], cf[3]), c45 = pack_bf16(cf[4], cf[5]);
         float x[4], ks[4], xi[4];
 #pragma unroll
@@ -1030,9 +1061,7 @@ __global__ __launch_bounds__((WaveCfg<MP>::THREADS), WaveCfg<MP>::W / 4) void ml
             const int stage = rk4 ? (e & 3) : 0;
             const int k = rk4 ? (e >> 2) : e;
             const float t = ((float)k + (stage == 0 ? 0.0f : (stage == 3 ? 1.0f : 0.5f))) * dt;
-            const uint32_t x4t = pack_bf16(upper(xi[0]), t);
-            const u32x4 in = half ? u32x4{c23, c45, 0u, 0u}
-                                  : u32x4{pack_bf16(xi[0], xi[1]), pack_bf16(xi[2], xi[3]), x4t, c01};
+            const u32x4 in = wave_input(xi, t, c01, c23, c45, half);
             f32x16 X[2], Y[2], out;
             typename MH::Frag B[2][C::NKBH];          // operands of the layer read, of the one written
             u32x4 b5[C::NKB5];
@@ -1127,22 +1156,9 @@ __global__ __launch_bounds__((WaveCfg<MP>::THREADS), WaveCfg<MP>::W / 4) void ml
             silu_pair(Y, std::integral_constant<int, C::P5>{}, I2{}, I2{}, p.oscale[3], 1.0f,
                       std::integral_constant<int, C::NKB5 / 2>{}, last);
             sfor<C::NKB5 / 2>([&](auto M) { last(std::integral_constant<int, C::NKB5 / 2 + decltype(M)::value>{}); });
-            // x <- x + dt v, or the RK4 stage (as in mlp_ode_kernel)
-#pragma unroll
-            for (int d = 0; d < 4; ++d) {
-                const float v = out[d];
-                if constexpr (!rk4) {
-                    x[d] += v * dt;
-                    xi[d] = x[d];
-                } else if (stage < 3) {
-                    ks[d] = stage == 0 ? v : ks[d] + 2.0f * v;
-                    xi[d] = x[d] + (stage == 2 ? dt : 0.5f * dt) * v;
-                } else {
-                    xi[d] = x[d] = x[d] + (dt * (1.0f / 6.0f)) * (ks[d] + v);
-                }
-            }
+            wave_update<rk4>(x, xi, ks, out, stage, dt);
         }
-        const float x4 = upper(x[0]);
+        const float x4 = upper_half(x[0]);
         if (half == 0 && i < n_items) {
             const float xk[5] = {x[0], x[1], x[2], x[3], x4};
             sampler_outputs(p, i, xk);
@@ -1150,10 +1166,160 @@ __global__ __launch_bounds__((WaveCfg<MP>::THREADS), WaveCfg<MP>::W / 4) void ml
     }
 }
 
-template <int MP>
-hipError_t launch_wave(const MlpParams &p, int cu, hipStream_t s)
+// The same network and arithmetic for launches of few tiles, where a wave by itself (mlp_wave_kernel)
+// takes as long as its 256 activations a lane in sequence: a team of four waves, one to a SIMD,
+// shares 32 samples.  Wave T holds the fragments of row tile T of every layer in registers (BF16
+// 132), so nothing is loaded in the loop; a layer's packed outputs pass through LDS in operand
+// order, two buffers in turn, with one barrier a layer; the output layer and the state's update
+// run in all four waves alike, so the state is not exchanged.  Bound by latency (a layer's eight
+// products of one chain, 16 activations, the exchange).
+// Measured, RK4 x 12, a wave each -> a team: 1,000 samples BF16 227 -> 112 us, FP8 222 -> 104; 8,192
+// BF16 233 -> 120; 16,384 (two teams to a CU) BF16 237 -> 158, FP8 225 -> 155.  The lattice of 200,000
+// particles, whose late steps hold few: 16.0 -> 14.0 ms.
+template <int MP, int RK>
+__global__ __launch_bounds__(256, 2) void mlp_team_kernel(MlpParams p)
 {
     using C = WaveCfg<MP>;
+    using M1 = Mma<kBF16>;
+    using MH = Mma<C::PH>;
+    constexpr bool rk4 = (RK == 1);
+    constexpr int EX = 8 * 64 * 16;                        // one buffer: 128 BF16 values of 32 samples
+    __shared__ __attribute__((aligned(16))) char ex[2 * EX];
+    __shared__ __attribute__((aligned(16))) float biases[4 * C::H + 32];
+    const int tid = threadIdx.x, T = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, half = lane >> 5;
+
+    const int64_t n_items = p.n_dev ? (int64_t)*p.n_dev : p.n;
+    if (p.n_dev_large) {
+        const bool large = n_items > p.small_max;
+        if (blockIdx.x == 0 && tid == 0) *p.n_dev_large = large ? (unsigned long long)n_items : 0ull;
+        if (large) return;
+    }
+    const int64_t ntiles = (n_items + 31) / 32;
+    if (blockIdx.x >= ntiles) return;
+    const float dt = 1.0f / (float)p.K;
+    const int nevals = rk4 ? 4 * p.K : p.K;
+    for (int l = 0; l < 4; ++l)
+        if (tid < C::H) biases[l * C::H + tid] = p.bias[l][tid];
+    if (tid < 32) biases[4 * C::H + tid] = p.bias[4][tid];
+    u32x4 w1 = M1::load_g(make_rsrc(p.wA[0], p.wA_bytes[0]), lane * 16, T * C::TILE);
+    typename MH::Frag wh[3][C::NKBH];
+    u32x4 w5[C::NKB5];
+#pragma unroll
+    for (int l = 0; l < 3; ++l) {
+        const Rsrc w = make_rsrc(p.wA[1 + l], p.wA_bytes[1 + l]);
+#pragma unroll
+        for (int kb = 0; kb < C::NKBH; ++kb)
+            wh[l][kb] = MH::load_g(w, lane * frag_bytes(C::PH), (T * C::NKBH + kb) * 64 * frag_bytes(C::PH));
+    }
+    {
+        const Rsrc w = make_rsrc(p.wA[4], p.wA_bytes[4]);
+#pragma unroll
+        for (int kb = 0; kb < C::NKB5; ++kb) w5[kb] = M1::load_g(w, lane * 16, kb * C::TILE);
+    }
+    __syncthreads();
+    auto load_bias = [&](int off) {          // the accumulator's start for one row tile
+        const float *b = biases + off + 4 * half;
+        f32x16 v;
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+            const f32x4 q = *(const f32x4 *)(b + 8 * g);
+            v[4 * g + 0] = q.x;
+            v[4 * g + 1] = q.y;
+            v[4 * g + 2] = q.z;
+            v[4 * g + 3] = q.w;
+        }
+        return v;
+    };
+    // SiLU of the row tile to buffer `to`: BF16, its two k-blocks' 16 bytes a lane each; FP8, its half
+    // of a k-block's 32 bytes
+    auto silu_out = [&](f32x16 &acc, auto PO, char *to, float osc, float inv) {
+        drain_pipe<decltype(PO)::value, C::SCALE, 1>(
+            [&](auto I) { return acc[decltype(I)::value]; }, osc, inv,
+            [&](auto, const uint32_t *w) {
+                if constexpr (decltype(PO)::value == kBF16) {
+                    *(u32x4 *)(to + 2 * T * C::TILE + lane * 16) = u32x4{w[0], w[1], w[2], w[3]};
+                    *(u32x4 *)(to + (2 * T + 1) * C::TILE + lane * 16) = u32x4{w[4], w[5], w[6], w[7]};
+                } else {
+                    *(u32x4 *)(to + T * C::TILE + lane * 16) = u32x4{w[0], w[1], w[2], w[3]};
+                }
+            });
+    };
+
+    for (int64_t tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
+        const int64_t i = tile * 32 + (lane & 31);
+        float z[5], cf[6];
+        sampler_inputs(p, i, n_items, z, cf);
+        const uint32_t c01 = pack_bf16(cf[0], cf[1]), c23 = pack_bf16(cf[2], cf[3]), c45 = pack_bf16(cf[4], cf[5]);
+        float x[4], ks[4], xi[4];
+#pragma unroll
+        for (int d = 0; d < 4; ++d) {
+            x[d] = half ? (d == 0 ? z[4] : 0.0f) : z[d];
+            xi[d] = x[d];
+            ks[d] = 0.0f;
+        }
+#pragma unroll 1
+        for (int e = 0; e < nevals; ++e) {
+            const int stage = rk4 ? (e & 3) : 0;
+            const int k = rk4 ? (e >> 2) : e;
+            const float t = ((float)k + (stage == 0 ? 0.0f : (stage == 3 ? 1.0f : 0.5f))) * dt;
+            const u32x4 in = wave_input(xi, t, c01, c23, c45, half);
+            f32x16 acc = load_bias(32 * T);
+            M1::run(acc, w1, in, 127);
+            silu_out(acc, std::integral_constant<int, C::PH>{}, ex, p.oscale[0], p.inv_in_scale[1]);
+            sfor<3>([&](auto L) {
+                constexpr int l = decltype(L)::value;
+                using PO = std::integral_constant<int, l == 2 ? C::P5 : C::PH>;
+                const char *from = ex + (l % 2) * EX + lane * 16;
+                acc = load_bias(C::H * (1 + l) + 32 * T);
+                const int sc = (C::PH == kFP8) ? p.mscale[1 + l] : 127;
+                __syncthreads();
+#pragma unroll
+                for (int kb = 0; kb < C::NKBH; ++kb) {
+                    if constexpr (C::PH == kFP8)
+                        MH::run(acc, wh[l][kb],
+                                MH::cat(*(const u32x4 *)(from + 2 * kb * C::TILE), *(const u32x4 *)(from + (2 * kb + 1) * C::TILE)), sc);
+                    else
+                        MH::run(acc, wh[l][kb], *(const u32x4 *)(from + kb * C::TILE), sc);
+                }
+                silu_out(acc, PO{}, ex + ((l + 1) % 2) * EX, p.oscale[1 + l], l < 2 ? p.inv_in_scale[2 + l] : 1.0f);
+            });
+            f32x16 out = load_bias(4 * C::H);
+            __syncthreads();
+#pragma unroll
+            for (int kb = 0; kb < C::NKB5; ++kb)
+                M1::run(out, w5[kb], *(const u32x4 *)(ex + EX + kb * C::TILE + lane * 16), 127);
+            wave_update<rk4>(x, xi, ks, out, stage, dt);
+        }
+        const float x4 = upper_half(x[0]);
+        if (T == 0 && half == 0 && i < n_items) {
+            const float xk[5] = {x[0], x[1], x[2], x[3], x4};
+            sampler_outputs(p, i, xk);
+        }
+    }
+}
+
+// Launches of at most 64 samples per compute unit (two teams to a CU: 158 us against 237 at 16,384; a
+// third round of teams would take longer than the 234 us that a wave each takes up to twelve to a CU)
+// run teams; a count known only on the device chooses there, as in launch_one.
+template <int MP>
+hipError_t launch_wave(const MlpParams &p_in, int cu, hipStream_t s)
+{
+    using C = WaveCfg<MP>;
+    MlpParams p = p_in;
+    p.n_dev_large = nullptr;
+    const int64_t few = (int64_t)64 * cu;
+    if (p.n <= few || p_in.n_dev_large) {
+        const bool chain = p.n > few;
+        MlpParams q = p;
+        q.n_dev_large = chain ? p_in.n_dev_large : nullptr;
+        q.small_max = few;
+        const int grid = (int)std::max<int64_t>(1, std::min<int64_t>((p.n + 31) / 32, (int64_t)2 * cu));
+        if (p.integrator == 1) hipLaunchKernelGGL((mlp_team_kernel<MP, 1>), dim3(grid), dim3(256), 0, s, q);
+        else hipLaunchKernelGGL((mlp_team_kernel<MP, 0>), dim3(grid), dim3(256), 0, s, q);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess || !chain) return e;
+        p.n_dev = p_in.n_dev_large;
+    }
     const int grid = (int)std::max<int64_t>(1, std::min<int64_t>((p.n + 31) / 32, cu));
     if (p.integrator == 1) hipLaunchKernelGGL((mlp_wave_kernel<MP, 1>), dim3(grid), dim3(C::THREADS), 0, s, p);
     else hipLaunchKernelGGL((mlp_wave_kernel<MP, 0>), dim3(grid), dim3(C::THREADS), 0, s, p);

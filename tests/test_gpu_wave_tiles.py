@@ -33,7 +33,7 @@ def test_results_do_not_depend_on_the_launch(precision, n_in, integrator, K):
 
     want = run(N)
     assert np.isfinite(want["raw"]).all()
-    for n in (1, 31, 32, 33, 257, 8191, 98_337):
+    for n in (1, 31, 32, 33, 257, 8191, 16_384, 16_385, 98_337):
         got = run(n)
         for k in want:
             np.testing.assert_array_equal(got[k], want[k][..., :n], err_msg=f"{k}, {n} samples")
