@@ -169,7 +169,7 @@ __device__ __forceinline__ DrawPrefix split_prefix(uint32_t hist, uint32_t k0, u
 __device__ __forceinline__ float split_draw(const DrawPrefix &q, uint32_t k0, uint32_t k1, uint32_t visit)
 {
     const uint64_t g = (uint64_t)kPhiloxM0 * (visit ^ q.a);
-    return u01(philox_rest(q.b, q.c, (uint32_t)(g >> 32) ^ q.d, (uint32_t)g, k0, k1).a);
+    return u01(philox_rest(U4{q.b, q.c, (uint32_t)(g >> 32) ^ q.d, (uint32_t)g}, k0, k1).a);
 }
 
 struct Next {

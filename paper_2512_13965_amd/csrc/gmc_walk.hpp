@@ -22,9 +22,9 @@
 // short: same-address atomics complete one in 13 ns (2^23 walks at tau = 1, 64 to an atomic:
 // 1.7 ms).
 // Measured, against one lane per walk throughout and a launch-wide counter: 2^20 walks of mixed
-// cells (longest 5,200 flights) 2.95 -> 0.108 ms, 10^6 at tau = 100, c = 0.99 (12,000) 8.5 ->
+// cells (longest 5,200 flights) 2.96 -> 0.11 ms, 10^6 at tau = 100, c = 0.99 (12,000) 8.5 ->
 // 0.59 ms, 2^23 at tau = 100 12.7 -> 2.7 ms (2.4e11 flights/s), 2^23 at tau = 1 1.7 -> 0.25 ms.
-// The longest walk of a launch costs 15 ns a flight in the second regime.
+// The longest walk of a launch costs 11 ns a flight in the end.
 #pragma once
 
 #include "gmc_device.hpp"
@@ -112,26 +112,35 @@ __device__ __forceinline__ uint32_t xor3(uint32_t a, uint32_t b, uint32_t c)
     return __builtin_amdgcn_bitop3_b32(a, b, c, 0x96);
 }
 
-// Rounds 3 to 10 of a Philox block.
-__device__ __forceinline__ U4 philox_rest(uint32_t c0, uint32_t c1, uint32_t c2, uint32_t c3, uint32_t k0, uint32_t k1)
+// Round r (from 0) of a Philox block.
+__device__ __forceinline__ void philox_round(U4 &c, uint32_t k0, uint32_t k1, uint32_t r)
 {
-#pragma unroll
-    for (uint32_t r = 2; r < 10; ++r) {
-        const uint64_t p0 = (uint64_t)kPhiloxM0 * c0, p1 = (uint64_t)kPhiloxM1 * c2;
-        c0 = xor3((uint32_t)(p1 >> 32), c1, k0 + r * kPhiloxW0);
-        c2 = xor3((uint32_t)(p0 >> 32), c3, k1 + r * kPhiloxW1);
-        c1 = (uint32_t)p1;
-        c3 = (uint32_t)p0;
-    }
-    return U4{c0, c1, c2, c3};
+    const uint64_t p0 = (uint64_t)kPhiloxM0 * c.a, p1 = (uint64_t)kPhiloxM1 * c.c;
+    c.a = xor3((uint32_t)(p1 >> 32), c.b, k0 + r * kPhiloxW0);
+    c.c = xor3((uint32_t)(p0 >> 32), c.d, k1 + r * kPhiloxW1);
+    c.b = (uint32_t)p1;
+    c.d = (uint32_t)p0;
 }
 
-// draw4(key, stream, flight, kTagWalk) from the prefix of (stream, key).
-__device__ __forceinline__ U4 draw_flight(const DrawPrefix &q, uint32_t k0, uint32_t k1, uint32_t flight)
+// Rounds 3 to 10 of a Philox block.
+__device__ __forceinline__ U4 philox_rest(U4 c, uint32_t k0, uint32_t k1)
+{
+#pragma unroll
+    for (uint32_t r = 2; r < 10; ++r) philox_round(c, k0, k1, r);
+    return c;
+}
+
+// draw4(key, stream, flight, kTagWalk) from the prefix of (stream, key): its first two rounds, and all.
+__device__ __forceinline__ U4 draw_begin(const DrawPrefix &q, uint32_t flight)
 {
     const uint64_t f = (uint64_t)kPhiloxM1 * flight;
     const uint64_t g = (uint64_t)kPhiloxM0 * ((uint32_t)(f >> 32) ^ q.a);
-    return philox_rest(q.b ^ (uint32_t)f, q.c, (uint32_t)(g >> 32) ^ q.d, (uint32_t)g, k0, k1);
+    return U4{q.b ^ (uint32_t)f, q.c, (uint32_t)(g >> 32) ^ q.d, (uint32_t)g};
+}
+
+__device__ __forceinline__ U4 draw_flight(const DrawPrefix &q, uint32_t k0, uint32_t k1, uint32_t flight)
+{
+    return philox_rest(draw_begin(q, flight), k0, k1);
 }
 
 // The walks or particles 0 .. n-1 that a block of a launch takes: granules of consecutive ones,
@@ -377,6 +386,7 @@ __device__ __forceinline__ void run_walks(int64_t n, uint64_t seed, WalkGroups *
                 G.step[1][lane].y = v;
             }
         }
+        if (g == 64) break;
         bool ends = false, xface = false, absorbed = false;
         float db = 0.0f, ds = 0.0f, un = 0.0f, vn = 0.0f;
         if (alive) {
@@ -395,26 +405,7 @@ __device__ __forceinline__ void run_walks(int64_t n, uint64_t seed, WalkGroups *
             const int coord = j == 1 ? 1 : (j == 2 ? 2 : 0);
             const f32v4 *step = (const f32v4 *)&G.step[coord][base];
             float *at = &G.at[coord][base];    // the lanes from j = 3 on repeat lane 0
-            if (g == 64) {                     // base = 0
-                const f32v4 *step = (const f32v4 *)&G.step[coord][0];
-                float *at = &G.at[coord][0];
-                // the longest walks: eight flights at a time, the next eight's steps on their way;
-                // unrolled, without the loop's moves: 20 -> 15 ns a flight (24 steps on their way spill)
-                f32v4 s[2][4];
-#pragma unroll
-                for (int c = 0; c < 2; ++c)
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) s[c][i] = step[4 * c + i];
-#pragma unroll
-                for (int c = 0; c < 8; ++c) {
-                    val = walk_chain<8>(val, s[c % 2], at + 8 * c);
-                    if (c + 2 < 8) {
-#pragma unroll
-                        for (int i = 0; i < 4; ++i) s[c % 2][i] = step[4 * (c + 2) + i];
-                    }
-                    __builtin_amdgcn_sched_barrier(0);
-                }
-            } else if (g == 4) {
+            if (g == 4) {
                 const f32v4 s[2] = {step[0], step[1]};
                 val = walk_chain<4>(val, s, at);
             } else {
@@ -440,7 +431,7 @@ __device__ __forceinline__ void run_walks(int64_t n, uint64_t seed, WalkGroups *
         }
         const uint64_t all = __ballot(ends);
         if (alive) {
-            const uint64_t ours = (all >> base) & (g == 64 ? ~0ull : (1ull << g) - 1ull);
+            const uint64_t ours = (all >> base) & ((1ull << g) - 1ull);
             if (ours) {
                 if (j == __ffsll((unsigned long long)ours) - 1) {
                     const uint32_t f = flight + (uint32_t)j;
@@ -462,6 +453,83 @@ __device__ __forceinline__ void run_walks(int64_t n, uint64_t seed, WalkGroups *
                     G.step[1][base].y = vn;
                 }
             }
+        }
+        wave_sync();
+    }
+
+    // ---- the wave's last walk, by all its lanes (base = 0, j = lane; what belongs to the walk is
+    // uniform): a chain of 64 flights, eight at a time and unrolled, with the next eight's steps on
+    // their way (24 steps on their way spill) and, in the shadow of each eight, one of the last eight
+    // Philox rounds of the next 64 flights' draws.  A flight of the longest walk: 20 ns in the loop
+    // above, 15 unrolled, 11 with the draws in the shadow (2^16 walks at tau = 1000 7.8 -> 5.9 ms).
+    auto uniform = [](uint32_t a) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)a); };
+    auto uniform_f = [](float a) { return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(a))); };
+    q = DrawPrefix{uniform(q.a), uniform(q.b), uniform(q.c), uniform(q.d)};
+    key0 = uniform(KEYS ? key0 : s0);
+    key1 = uniform(KEYS ? key1 : s1);
+    flight = uniform(flight);
+    wa = uniform_f(wa);
+    inv_sig = uniform_f(inv_sig);
+    if constexpr (ANALOG) cs = uniform_f(cs);
+    const int coord = lane == 1 ? 1 : (lane == 2 ? 2 : 0);
+    const f32v4 *step = (const f32v4 *)&G.step[coord][0];
+    float *at = &G.at[coord][0];               // the lanes from 3 on repeat lane 0
+    U4 r = draw_flight(q, key0, key1, flight + (uint32_t)lane);
+    for (;;) {
+        float un, vn;
+        const float ds = flight_length(r, inv_sig);
+        scatter_direction<XY>(r, un, vn);
+        const bool absorbed = ANALOG && u01(r.c) > cs;
+        G.step[0][lane].x = ds;
+        G.step[1][lane].x = ds;
+        G.step[2][lane] = f32v2{ds, 1.0f};
+        G.step[0][lane + 1].y = un;
+        G.step[1][lane + 1].y = vn;
+        wave_sync();
+        f32v4 s[2][4];
+#pragma unroll
+        for (int c = 0; c < 2; ++c)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) s[c][i] = step[4 * c + i];
+        r = draw_begin(q, flight + 64u + (uint32_t)lane);
+#pragma unroll
+        for (int c = 0; c < 8; ++c) {
+            val = walk_chain<8>(val, s[c % 2], at + 8 * c);
+            if (c + 2 < 8) {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) s[c % 2][i] = step[4 * (c + 2) + i];
+            }
+            philox_round(r, key0, key1, 2u + c);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        wave_sync();
+        x = G.at[0][lane];
+        y = G.at[1][lane];
+        len = G.at[2][lane];
+        u = G.step[0][lane].y;
+        v = G.step[1][lane].y;
+        bool xface;
+        const float db = walk_boundary(x, y, u, v, wa, xface);
+        const uint32_t f = flight + (uint32_t)lane;
+        const uint64_t ends = __ballot(ds >= db || absorbed || f + 1u >= kMaxFlights);
+        if (ends) {
+            if (lane == __ffsll((unsigned long long)ends) - 1) {
+                if (ds >= db) {
+                    float pos;
+                    const int face = walk_exit(x, y, u, v, wa, db, xface, pos);
+                    emit(idx, face, pos, u, v, len + db, f);
+                } else if (absorbed) {
+                    emit(idx, kAbsorbed, 0.0f, u, v, len + ds, f + 1u);
+                } else {
+                    emit(idx, kCapped, 0.0f, un, vn, len + ds, f + 1u);
+                }
+            }
+            return;
+        }
+        flight += 64u;
+        if (lane == 63) {                      // the first direction of the next round
+            G.step[0][0].y = un;
+            G.step[1][0].y = vn;
         }
         wave_sync();
     }
