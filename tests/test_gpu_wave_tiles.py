@@ -48,3 +48,29 @@ def test_results_do_not_depend_on_the_launch(precision, n_in, integrator, K):
     call(m, sub, integrator, K, 4, 0, noise=zz, raw=raw)
     assert torch.equal(raw[:, :64], raw[:, 64:128]) and torch.equal(raw[:, :64], raw[:, 128:])
     m.close()
+
+
+@pytest.mark.parametrize("precision,split,graphs", [("bf16", True, False), ("fp8", True, True), ("bf16", False, True)])
+def test_transport_does_not_depend_on_who_chooses(precision, split, graphs):
+    """Counts that only the device knows (a split step's collided crossings, a captured step's
+    count) choose between teams and waves there when the host's bound exceeds 64 samples per
+    compute unit.  A bank of all histories takes both choices as the count falls, a bank of 64 per
+    compute unit only ever runs teams; the tallies agree up to the order of their FP64 additions
+    (n terms of at most 1 each)."""
+    from paper_2512_13965_amd import transport
+    binding = require_gpu()
+    few = 64 * torch.cuda.get_device_properties(0).multi_processor_count
+    prob = inputs.checkerboard_problem(16, src=2)
+    n = 5 * few // 2
+    m = binding.Model(inputs.pack_blob(inputs.random_weights(128, 31, flags=2 if split else 0)), precision)
+    out = []
+    for cap in (4 * few, few):
+        w = binding.World(cap, 1, 1 << 12)
+        w.set_graphs(graphs)
+        out.append(transport.run_problem(w, prob, n, 5, binding.SAMPLER_GMC, m, 4, chunk=cap))
+        w.close()
+    m.close()
+    a, b = out
+    assert a["transmissions"] == b["transmissions"]
+    for k in ("flux", "absorbed", "leak", "cutoff", "wpath", "path", "visits"):
+        np.testing.assert_allclose(a[k], b[k], rtol=1e-12, atol=1e-12 * n, err_msg=k)
