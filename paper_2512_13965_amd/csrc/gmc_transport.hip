@@ -837,15 +837,17 @@ __global__ __launch_bounds__(256) void finish_kernel(const unsigned long long *c
     }
 }
 
-// After a step or injection that failed part way: the counters as its successor expects them.
-__global__ __launch_bounds__(256) void reset_kernel(unsigned long long *ctr, unsigned long long alive,
+// After a step or injection that failed part way: the counters as its successor expects them, of
+// the particles alive before it (in all and per problem).
+__global__ __launch_bounds__(256) void reset_kernel(const unsigned long long *alive, unsigned long long *ctr,
                                                     unsigned long long *other, unsigned long long *split_count, int n)
 {
-    for (int i = threadIdx.x; i < n; i += 256) other[i] = 0ull;
-    if (threadIdx.x == 0) {
-        ctr[0] = alive;
-        *split_count = 0ull;
+    const int i = blockIdx.x * 256 + threadIdx.x;
+    if (i < n) {
+        ctr[i] = alive[i];
+        other[i] = 0ull;
     }
+    if (i == 0) *split_count = 0ull;
 }
 
 // Clears the tallies of cells [cell0, cell0 + n).
@@ -1006,16 +1008,30 @@ hipError_t enqueue_finish(gmc_world *w, int which, hipStream_t s)
     return hipGetLastError();
 }
 
-// Before a step or injection: the counters put right if the last one failed.  Until
-// sync_counters has run, this one counts as failed.
+// Before a step or injection: the counters put right if the last one failed (its kernels no longer
+// run, see failed_call, so the host's copy of the counters is free).  Until sync_counters has run,
+// this one counts as failed.
 hipError_t begin_counters(gmc_world *w, hipStream_t s)
 {
     const bool was = w->broken;
     w->broken = true;
     if (!was) return hipSuccess;
-    hipLaunchKernelGGL(reset_kernel, dim3(1), dim3(256), 0, s, w->cnt(w->cur), (unsigned long long)w->n_alive,
-                       w->cnt(1 - w->cur), w->s_count, 1 + w->max_problems);
+    w->host_counters[0] = (unsigned long long)w->n_alive;
+    for (int p = 0; p < w->max_problems; ++p) w->host_counters[1 + p] = (unsigned long long)w->alive_pp[p];
+    const int n = 1 + w->max_problems;
+    hipLaunchKernelGGL(reset_kernel, dim3(blocks_for(n)), dim3(256), 0, s, w->host_counters, w->cnt(w->cur),
+                       w->cnt(1 - w->cur), w->s_count, n);
     return hipGetLastError();
+}
+
+// Ends a step or injection that failed after begin_counters: waits for what it had enqueued, and
+// leaves no error behind for the next call to find.  The bank, the counts and the number of steps
+// stay as they were before it; tallies its kernels made stand.
+int failed_call(hipStream_t s, int rc)
+{
+    (void)hipStreamSynchronize(s);
+    (void)hipGetLastError();
+    return rc;
 }
 
 // Wait for it and take its counts over.
@@ -1246,7 +1262,7 @@ int gmc_world_inject(gmc_world *w, int32_t pid, uint64_t h_begin, int64_t count,
         unsigned long long *ctr = w->cnt(which);
         // the bank's counters stand at the particles alive, in all and per problem, and continue
         const hipError_t eb = begin_counters(w, s);
-        if (eb != hipSuccess) return set_hip_error(eb, "gmc_world_inject: launch");
+        if (eb != hipSuccess) return failed_call(s, set_hip_error(eb, "gmc_world_inject: launch"));
         if (w->src_face[pid] >= 0) {
             hipLaunchKernelGGL(surface_birth_kernel, dim3(tally_blocks(count, cu)), dim3(kTallyThreads), 0, s, w->cells(),
                                pid, (uint32_t)h_begin, count, w->bank[which], ctr, ctr + 1);
@@ -1286,7 +1302,7 @@ int gmc_world_inject(gmc_world *w, int32_t pid, uint64_t h_begin, int64_t count,
             p.seed = 0;
             p.id_base = 0;
             hipError_t e = launch_mlp_ode(m->precision, m->hidden, p, cu, s);
-            if (e != hipSuccess) return set_hip_error(e, "gmc_world_inject: internal sampler");
+            if (e != hipSuccess) return failed_call(s, set_hip_error(e, "gmc_world_inject: internal sampler"));
         }
         if (w->src_face[pid] < 0)
             hipLaunchKernelGGL(birth_apply_kernel, dim3(tally_blocks(count, cu)), dim3(kTallyThreads), 0, s, w->cells(), pid,
@@ -1294,9 +1310,9 @@ int gmc_world_inject(gmc_world *w, int32_t pid, uint64_t h_begin, int64_t count,
                                w->e_path, w->bank[which], ctr, ctr + 1);
         hipError_t e = hipGetLastError();
         if (e == hipSuccess) e = enqueue_finish(w, which, s);
-        if (e != hipSuccess) return set_hip_error(e, "gmc_world_inject: launch");
+        if (e != hipSuccess) return failed_call(s, set_hip_error(e, "gmc_world_inject: launch"));
         const int rc = sync_counters(w, s);
-        if (rc != GMC_OK) return rc;
+        if (rc != GMC_OK) return failed_call(s, rc);
     }
     if (n_alive_out) *n_alive_out = w->n_alive;
     return GMC_OK;
@@ -1522,24 +1538,21 @@ int gmc_transport_step(gmc_world *w, int sampler, const gmc_model *m, int K, voi
     hipStream_t s = (hipStream_t)stream;
     const int64_t n = w->n_alive;
     if (n > 0) {
-        int rc;
-        const hipError_t eb = begin_counters(w, s);
-        if (eb != hipSuccess) return set_hip_error(eb, "gmc_transport_step: launch");
+        int rc = GMC_OK;
+        hipError_t e = begin_counters(w, s);
+        if (e != hipSuccess) return failed_call(s, set_hip_error(e, "gmc_transport_step: launch"));
         if (w->graphs) {
             hipGraphExec_t x = nullptr;
             rc = step_graph(w, sampler, m, K, step_bucket(w, n), &x);
-            if (rc != GMC_OK) return rc;
-            const hipError_t e = hipGraphLaunch(x, s);
-            if (e != hipSuccess) return set_hip_error(e, "gmc_transport_step: graph launch");
+            if (rc == GMC_OK && (e = hipGraphLaunch(x, s)) != hipSuccess)
+                rc = set_hip_error(e, "gmc_transport_step: graph launch");
         } else {
             rc = enqueue_step(w, sampler, m, K, s, n, nullptr);
-            if (rc != GMC_OK) return rc;
         }
-        const int nxt = 1 - w->cur;
-        w->cur = nxt;
+        if (rc == GMC_OK) rc = sync_counters(w, s);
+        if (rc != GMC_OK) return failed_call(s, rc);
+        w->cur = 1 - w->cur;
         w->stepped += n;
-        rc = sync_counters(w, s);
-        if (rc != GMC_OK) return rc;
     }
     if (n_alive_out) *n_alive_out = w->n_alive;
     return GMC_OK;

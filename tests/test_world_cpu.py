@@ -1,0 +1,29 @@
+"""CPU checks of the transport world's host code against a stand-in for the HIP runtime
+(tests/hip_stub.cpp, tests/world_host_checks.py), one child process each."""
+import os
+import subprocess
+import sys
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+
+@pytest.fixture(scope="module")
+def stub(tmp_path_factory):
+    out = str(tmp_path_factory.mktemp("stub") / "hip_stub.so")
+    subprocess.check_call(["g++", "-O1", "-std=c++17", "-Wall", "-shared", "-fPIC",
+                           os.path.join(ROOT, "tests", "hip_stub.cpp"), "-o", out])
+    return out
+
+
+def _check(stub, name):
+    from paper_2512_13965_amd import binding
+    preload = " ".join([stub, *os.environ.get("LD_PRELOAD", "").split()])
+    r = subprocess.run([sys.executable, "-m", "tests.world_host_checks", binding.LIB_PATH, stub, name], cwd=ROOT,
+                       env=dict(os.environ, LD_PRELOAD=preload), capture_output=True, text=True, timeout=120)
+    assert r.returncode == 0 and r.stdout.strip().endswith("OK"), r.stdout + r.stderr
+
+
+def test_failed_calls_leave_the_world_as_it_was(stub):
+    _check(stub, "failed_calls")
