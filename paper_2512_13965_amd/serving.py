@@ -21,7 +21,7 @@ from dataclasses import dataclass, field
 
 import numpy as np
 
-CELL_BYTES = 8 + 8 + 8 + 4 + 4 + 8 * 8     # tau, c, sigma_a (FP64), ln tau, c (FP32), 8 FP64 tallies
+CELL_BYTES = 8 + 8 + 4 + 4 + 8 * 8         # tau, sigma_a (FP64), ln tau, c (FP32), 8 FP64 tallies
 
 
 @dataclass

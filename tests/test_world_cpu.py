@@ -27,3 +27,7 @@ def _check(stub, name):
 
 def test_failed_calls_leave_the_world_as_it_was(stub):
     _check(stub, "failed_calls")
+
+
+def test_tallies_are_read_by_the_columns_asked_for(stub):
+    _check(stub, "tally_bytes")

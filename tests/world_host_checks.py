@@ -131,6 +131,23 @@ def failed_calls(lib, stub):
     assert S.stub_arg(stub.launches("12apply_kernel")[0], 0) != bank and not stub.launches("reset_kernel")
 
 
+def tally_bytes(lib, stub):
+    """Reading tallies brings back the columns asked for and nothing else."""
+    w = World(lib, 1 << 10, 1, 1 << 20)
+    prob = inputs.checkerboard_problem(500, src=2)
+    pid, n = w.add(prob), prob.n_cells
+    out = [np.zeros(n) for _ in range(5)]
+    at = [o.ctypes.data for o in out]
+    for call, args in ((w.L.gmc_problem_tally, (at[0], None, None, None)),
+                       (w.L.gmc_problem_tally, (None, at[1], None, at[3])),
+                       (w.L.gmc_problem_tally, tuple(at[:4])),
+                       (w.L.gmc_problem_path_tally, (None, None, at[2], None, None)),
+                       (w.L.gmc_problem_path_tally, tuple(at))):
+        stub.S.stub_clear()
+        assert call(w.h, pid, *args, None) == OK
+        assert stub.S.stub_copied(2) <= 8 * n * sum(a is not None for a in args), args
+
+
 def main():
     lib, stub, check = sys.argv[1:4]
     globals()[check](lib, Stub(stub))
