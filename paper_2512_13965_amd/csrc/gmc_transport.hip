@@ -850,6 +850,16 @@ __global__ __launch_bounds__(256) void reset_kernel(const unsigned long long *al
     if (i == 0) *split_count = 0ull;
 }
 
+// Materials of cells [cell0, cell0 + n) of width L: tau is in place, c and ln tau were uploaded to the
+// cells' own places for cutoff and leak tallies (cleared afterwards).
+__global__ __launch_bounds__(256) void materials_kernel(CellsDev cd, CellMat *mat, int64_t cell0, int64_t n, double L)
+{
+    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (i >= n) return;
+    const double c = cd.cutoff[cell0 + i];
+    mat[cell0 + i] = CellMat{((const float *)(cd.leak + cell0))[i], (float)c, (1.0 - c) * cd.tau[cell0 + i] / L};
+}
+
 // Clears the tallies of cells [cell0, cell0 + n).
 __global__ void zero_tallies_kernel(CellsDev cd, int64_t cell0, int64_t n)
 {
@@ -1211,15 +1221,13 @@ int gmc_problem_add(gmc_world *w, const gmc_problem_desc *d, int32_t *pid_out, v
     for (int p = 0; p < w->max_problems; ++p)
         if (!w->in_use[p]) { pid = p; break; }
     if (pid < 0) return set_error(GMC_ENOMEM, "gmc_problem_add: no free problem slot");
-    std::vector<CellMat> mat;
+    std::vector<float> lt;
     try {
-        mat.resize(n);
+        lt.resize(n);
     } catch (const std::bad_alloc &) {
         return set_error(GMC_ENOMEM, "gmc_problem_add: host staging");
     }
-    for (int64_t i = 0; i < n; ++i)
-        mat[i] = CellMat{d->tau[i] > 0.0 ? (float)std::log(d->tau[i]) : -1.0e4f, (float)d->c[i],
-                         (1.0 - d->c[i]) * d->tau[i] / d->L};
+    for (int64_t i = 0; i < n; ++i) lt[i] = d->tau[i] > 0.0 ? (float)std::log(d->tau[i]) : -1.0e4f;
     int64_t cell0 = -1;
     for (auto &r : w->free_cells)
         if (r.second - r.first >= n) {
@@ -1237,13 +1245,15 @@ int gmc_problem_add(gmc_world *w, const gmc_problem_desc *d, int32_t *pid_out, v
                  max_visits};
     hipStream_t s = (hipStream_t)stream;
     hipError_t e = hipMemcpyAsync(w->tau + cell0, d->tau, 8 * n, hipMemcpyHostToDevice, s);
-    if (e == hipSuccess) e = hipMemcpyAsync(w->mat + cell0, mat.data(), sizeof(CellMat) * n, hipMemcpyHostToDevice, s);
+    if (e == hipSuccess) e = hipMemcpyAsync(w->cutoff + cell0, d->c, 8 * n, hipMemcpyHostToDevice, s);
+    if (e == hipSuccess) e = hipMemcpyAsync(w->leak + cell0, lt.data(), 4 * n, hipMemcpyHostToDevice, s);
     if (e == hipSuccess) e = hipMemcpyAsync(w->prob + pid, &P, sizeof P, hipMemcpyHostToDevice, s);
     if (e == hipSuccess) {
+        hipLaunchKernelGGL(materials_kernel, dim3(blocks_for(n)), dim3(256), 0, s, w->cells(), w->mat, cell0, n, d->L);
         hipLaunchKernelGGL(zero_tallies_kernel, dim3(blocks_for(n)), dim3(256), 0, s, w->cells(), cell0, n);
         e = hipGetLastError();
     }
-    if (e == hipSuccess) e = hipStreamSynchronize(s);      // the host staging vectors go away
+    if (e == hipSuccess) e = hipStreamSynchronize(s);      // the host staging vector goes away
     if (e != hipSuccess) {
         w->free_cells.push_back({cell0, cell0 + n});
         return set_hip_error(e, "gmc_problem_add: upload");

@@ -31,3 +31,7 @@ def test_failed_calls_leave_the_world_as_it_was(stub):
 
 def test_tallies_are_read_by_the_columns_asked_for(stub):
     _check(stub, "tally_bytes")
+
+
+def test_adding_a_problem_uploads_its_materials_once(stub):
+    _check(stub, "add_bytes")

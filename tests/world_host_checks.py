@@ -148,6 +148,15 @@ def tally_bytes(lib, stub):
         assert stub.S.stub_copied(2) <= 8 * n * sum(a is not None for a in args), args
 
 
+def add_bytes(lib, stub):
+    """Adding a problem uploads its two FP64 materials and ln tau in FP32, and its description."""
+    w = World(lib, 1 << 10, 1, 1 << 20)
+    prob = inputs.checkerboard_problem(500, src=2)
+    stub.S.stub_clear()
+    w.add(prob)
+    assert stub.S.stub_copied(1) <= (8 + 8 + 4) * prob.n_cells + 1024
+
+
 def main():
     lib, stub, check = sys.argv[1:4]
     globals()[check](lib, Stub(stub))
