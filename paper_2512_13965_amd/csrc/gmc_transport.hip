@@ -228,7 +228,7 @@ __device__ __forceinline__ Next move_on(const CellsDev &cd, const ProblemDev &P,
 }
 
 // What a workgroup's append shares: survivors of each wave and their first index, and the
-// survivors per problem (a table as large as the workgroup, so that every problem finds a slot).
+// survivors per problem in a hash table.
 struct AppendLds {
     uint32_t wave[kTallyThreads / 64];
     unsigned long long base;
@@ -244,9 +244,8 @@ __device__ __forceinline__ void append_init(AppendLds &al)
 
 // Append the alive threads' particles to `out` and count them per problem.  One atomic on the
 // counter per call (a wave's own would queue up: one in 12 ns), none on the problems' counts until
-// append_flush.  Called by all threads of the workgroup; per wave at most 64 problems differ, so a
-// table of kTallyThreads slots filled over several calls can hold more problems than slots only
-// if a world's problems do: such a problem's count goes to its global counter directly.
+// append_flush, but for problems that find neither their slot nor a free one within kTallyProbes
+// probes: those count globally.  Called by all threads of the workgroup.
 __device__ __forceinline__ void append(AppendLds &al, bool alive, const Next &nx, int32_t pid, double w,
                                        uint32_t hist, uint32_t event, BankDev out,
                                        unsigned long long *counter, unsigned long long *pcount)
@@ -277,23 +276,24 @@ __device__ __forceinline__ void append(AppendLds &al, bool alive, const Next &nx
         out.hist[j] = hist;
         out.event[j] = event;
     }
-    uint64_t m = mask;
-    while (m) {
+    // one lane of each distinct problem counts for all of its survivors in the wave
+    uint32_t mine = 0;
+    for (uint64_t m = mask; m;) {
         const int l0 = __ffsll((unsigned long long)m) - 1;
-        const int p0 = __shfl(pid, l0);
-        const uint64_t same = __ballot(alive && pid == p0);
-        if (lane == l0) {
-            uint32_t s = (uint32_t)p0 % kTallyThreads;
-            int k = 0;
-            for (; k < kTallyThreads; ++k) {
-                const int prev = atomicCAS(&al.pid[s], -1, p0);
-                if (prev == -1 || prev == p0) break;
-                s = (s + 1) % kTallyThreads;
-            }
-            if (k < kTallyThreads) atomicAdd(&al.count[s], (uint32_t)__popcll(same));
-            else atomicAdd(&pcount[p0], (unsigned long long)__popcll(same));
-        }
+        const uint64_t same = __ballot(alive && pid == __shfl(pid, l0));
+        if (lane == l0) mine = (uint32_t)__popcll(same);
         m &= ~same;
+    }
+    if (mine > 0) {
+        uint32_t s = (uint32_t)pid % kTallyThreads;
+        int k = 0;
+        for (; k < kTallyProbes; ++k) {
+            const int prev = atomicCAS(&al.pid[s], -1, pid);
+            if (prev == -1 || prev == pid) break;
+            s = (s + 1) % kTallyThreads;
+        }
+        if (k < kTallyProbes) atomicAdd(&al.count[s], mine);
+        else atomicAdd(&pcount[pid], (unsigned long long)mine);
     }
     __syncthreads();       // al.wave and al.base are read before the next call writes them
 }
