@@ -822,16 +822,18 @@ __global__ __launch_bounds__(kTallyThreads) void apply_kernel(BankDev in, int64_
 // Ends a step or an injection: the bank's counters and the streamed crossings to the host's pinned
 // copy (a store over the bus; the stream's end makes it visible), the other bank's counters and the
 // split's count cleared for the next step.  One kernel of 3 us in the place of two that cleared and
-// two copies.
+// two copies; a thread a counter (a step of 1,000 particles in a world of 16,384 / 65,536 problem
+// slots 44 / 95 us, with one workgroup for all of them 53 / 123).
 __global__ __launch_bounds__(256) void finish_kernel(const unsigned long long *ctr, unsigned long long *other,
                                                      unsigned long long *split_count,
                                                      const unsigned long long *streamed, unsigned long long *host, int n)
 {
-    for (int i = threadIdx.x; i < n; i += 256) {
+    const int i = blockIdx.x * 256 + threadIdx.x;
+    if (i < n) {
         host[i] = ctr[i];
         other[i] = 0ull;
     }
-    if (threadIdx.x == 0) {
+    if (i == 0) {
         host[n] = *streamed;
         *split_count = 0ull;
     }
@@ -1056,8 +1058,9 @@ void plan(gmc_world *w, Layout &L)
 // Enqueue the end of a step or injection that left the particles in bank `which`.
 hipError_t enqueue_finish(gmc_world *w, int which, hipStream_t s)
 {
-    hipLaunchKernelGGL(finish_kernel, dim3(1), dim3(256), 0, s, w->cnt(which), w->cnt(1 - which), w->s_count,
-                       w->streamed, w->host_counters, 1 + w->max_problems);
+    const int n = 1 + w->max_problems;
+    hipLaunchKernelGGL(finish_kernel, dim3(blocks_for(n)), dim3(256), 0, s, w->cnt(which), w->cnt(1 - which),
+                       w->s_count, w->streamed, w->host_counters, n);
     return hipGetLastError();
 }
 

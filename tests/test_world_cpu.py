@@ -35,3 +35,7 @@ def test_tallies_are_read_by_the_columns_asked_for(stub):
 
 def test_adding_a_problem_uploads_its_materials_once(stub):
     _check(stub, "add_bytes")
+
+
+def test_the_end_of_a_step_has_a_thread_for_every_counter(stub):
+    _check(stub, "finish_grid")

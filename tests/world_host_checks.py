@@ -157,6 +157,20 @@ def add_bytes(lib, stub):
     assert stub.S.stub_copied(1) <= (8 + 8 + 4) * prob.n_cells + 1024
 
 
+def finish_grid(lib, stub):
+    """The kernel that ends a step has a thread for every counter of the world."""
+    for problems in (1, 255, 256, 65536):
+        w = World(lib, 1 << 10, problems, 256)
+        pid = w.add(inputs.checkerboard_problem(8, src=2))
+        stub.S.stub_clear()
+        stub.counts(5, *[5 if p == pid else 0 for p in range(problems)])
+        assert w.inject(pid, 0, 10) == (OK, 5)
+        i, = stub.launches("finish_kernel")
+        threads = stub.S.stub_grid(i) * stub.S.stub_block(i)
+        assert 1 + problems <= threads < 1 + problems + 256, (problems, threads)
+        assert w.L.gmc_world_destroy(w.h) == OK
+
+
 def main():
     lib, stub, check = sys.argv[1:4]
     globals()[check](lib, Stub(stub))
