@@ -977,6 +977,7 @@ struct gmc_world {
     std::vector<int64_t> alive_pp;
     std::vector<ProblemDev> prob_host;
     std::vector<char> in_use;
+    int32_t problems = 0, only = -1;    // problems held; the one held, -1 if not exactly one
     std::vector<int32_t> src_face;      // per problem slot: -1 volumetric, else a surface side
     std::vector<char> rect;             // per problem slot: non-square cells
     std::vector<char> xyg;              // per problem slot: XY geometry
@@ -1262,6 +1263,7 @@ int gmc_problem_add(gmc_world *w, const gmc_problem_desc *d, int32_t *pid_out, v
         return set_hip_error(e, "gmc_problem_add: upload");
     }
     w->in_use[pid] = 1;
+    w->only = ++w->problems == 1 ? pid : -1;
     w->src_face[pid] = d->src_face;
     w->rect[pid] = Ly != d->L;
     w->xyg[pid] = d->xy ? 1 : 0;
@@ -1288,6 +1290,7 @@ int gmc_problem_remove(gmc_world *w, int32_t pid)
     }
     w->free_cells.swap(merged);
     w->in_use[pid] = 0;
+    w->only = --w->problems == 1 ? (int32_t)(std::find(w->in_use.begin(), w->in_use.end(), 1) - w->in_use.begin()) : -1;
     w->rect[pid] = 0;
     w->xyg[pid] = 0;
     return GMC_OK;
@@ -1431,18 +1434,6 @@ bool world_xy(const gmc_world *w)
     return false;
 }
 
-// The one problem the world holds, -1 if it holds several.
-int32_t only_problem(const gmc_world *w)
-{
-    int32_t only = -1;
-    for (int p = 0; p < w->max_problems; ++p)
-        if (w->in_use[p]) {
-            if (only >= 0) return -1;
-            only = p;
-        }
-    return only;
-}
-
 // Enqueue one transport step on `s`: gather, sampler, apply, counters to the host.  Grids are sized for
 // `n_launch` particles; the kernels process n_dev[0] of them when n_dev is given (a captured step
 // serves every count up to its bucket), else n_launch.
@@ -1456,7 +1447,7 @@ int enqueue_step(gmc_world *w, int sampler, const gmc_model *m, int K, hipStream
     const CondDev o{w->c_ltau, w->c_c, w->c_yin, w->c_sth, w->c_la, w->c_ox, w->ids, w->keys};
     if (split) {
         const dim3 grid((unsigned)std::min<int64_t>((n_launch + 63) / 64, (int64_t)cu * kStreamBlocksPerCu));
-        const int32_t only = w->graphs ? -1 : only_problem(w);
+        const int32_t only = w->graphs ? -1 : w->only;
         if (only >= 0)
             hipLaunchKernelGGL(gather_split_kernel<true>, grid, dim3(kStreamThreads), 0, s, w->bank[cur], n_launch,
                                n_dev, w->cells(), o, w->s_slot, w->s_count, w->e_face, w->e_pos, w->e_dcos, w->e_dsin,
@@ -1499,7 +1490,7 @@ int enqueue_step(gmc_world *w, int sampler, const gmc_model *m, int K, hipStream
     } else {
         // one problem alone: its key and shape are the launch's (a captured step serves any set of
         // problems)
-        const int32_t only = w->graphs ? -1 : only_problem(w);
+        const int32_t only = w->graphs ? -1 : w->only;
         const float lr = only >= 0 ? w->prob_host[only].lr : 0.0f;
         const uint64_t seed = only >= 0 ? w->prob_host[only].seed : 0;
         const bool xy = world_xy(w);

@@ -39,3 +39,7 @@ def test_adding_a_problem_uploads_its_materials_once(stub):
 
 def test_the_end_of_a_step_has_a_thread_for_every_counter(stub):
     _check(stub, "finish_grid")
+
+
+def test_the_one_problem_of_a_world_is_known(stub):
+    _check(stub, "one_problem")

@@ -171,6 +171,34 @@ def finish_grid(lib, stub):
         assert w.L.gmc_world_destroy(w.h) == OK
 
 
+def one_problem(lib, stub):
+    """A step of a world with one problem takes that problem's key and shape from the launch, one of
+    a world with several reads each particle's; problems may come and go in any order."""
+    w = World(lib, 1 << 10, 300, 300 * 64)
+    prob = inputs.checkerboard_problem(8, src=2)
+    w.L.gmc_problem_remove.argtypes = [P, I32]
+    held = []
+
+    def keyed(pid):
+        stub.S.stub_clear()
+        stub.counts(5, *[5 if p == pid else 0 for p in range(300)])
+        assert w.inject(pid, 0, 10) == (OK, 5)
+        stub.counts(0)
+        assert w.step() == (OK, 0)
+        name = stub.S.stub_name(stub.launches("walk_step_kernel")[0]).decode()
+        assert "Lb0ELb0E" in name or "Lb0ELb1E" in name, name
+        return "Lb0ELb1E" in name
+
+    rng = np.random.default_rng(1)
+    for _ in range(60):
+        if held and (len(held) == 4 or rng.random() < 0.5):
+            assert w.L.gmc_problem_remove(w.h, held.pop(rng.integers(len(held)))) == OK
+        else:
+            held.append(w.add(prob))
+        if held:
+            assert keyed(held[-1]) == (len(held) > 1), held
+
+
 def main():
     lib, stub, check = sys.argv[1:4]
     globals()[check](lib, Stub(stub))
