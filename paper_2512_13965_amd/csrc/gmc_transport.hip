@@ -78,13 +78,14 @@ struct CellsDev {
     const ProblemDev *prob;
 };
 
-// Threads of a workgroup that tallies, and workgroups per compute unit of such a launch: its
-// workgroups take tiles of that many particles in turn, so that each fills one table.  What a
-// launch adds to the global tallies grows with the number of tables: the checkerboard's 128 steps
-// take 17.6 ms with one table of 4,096 cells to a CU and 18.1 ms with two of 2,048 (the lattice's 30
-// smaller ones 16.3 and 16.1 ms).
+// Threads of a workgroup that tallies, and cells of its table.  Large launches: one workgroup of 1,024
+// to a compute unit, which takes tiles of that many particles in turn, so that each fills one table:
+// what a launch adds to the global tallies grows with the number of tables (the checkerboard's 128
+// steps take 17.6 ms with one table of 4,096 cells to a CU and 18.1 ms with two of 2,048; the lattice's
+// 30 smaller ones 16.3 and 16.1 ms).  Small ones: a workgroup of 256 to each 256 particles.
 constexpr int kTallyThreads = 1024;
-constexpr int kTallyBlocksPerCu = 1;
+constexpr int kSmallTallyThreads = 256;
+constexpr int tally_slots(int threads) { return threads == kTallyThreads ? 4096 : 512; }
 
 // Per-workgroup tally staging: the visit tallies of a workgroup's particles are summed per cell in
 // an LDS hash table and added to the global ones at its end.  Particles near a source crowd into
@@ -97,8 +98,6 @@ struct TallyTable {
     int32_t key[SLOTS];
     double v[SLOTS * kVisitTallies];
 };
-using TallyLds = TallyTable<4096>;
-
 template <int SLOTS>
 __device__ __forceinline__ void tally_init(TallyTable<SLOTS> &tl)
 {
@@ -229,14 +228,16 @@ __device__ __forceinline__ Next move_on(const CellsDev &cd, const ProblemDev &P,
 
 // What a workgroup's append shares: survivors of each wave and their first index, and the
 // survivors per problem in a hash table.
+template <int THREADS>
 struct AppendLds {
-    uint32_t wave[kTallyThreads / 64];
+    uint32_t wave[THREADS / 64];
     unsigned long long base;
-    int32_t pid[kTallyThreads];
-    uint32_t count[kTallyThreads];
+    int32_t pid[THREADS];
+    uint32_t count[THREADS];
 };
 
-__device__ __forceinline__ void append_init(AppendLds &al)
+template <int THREADS>
+__device__ __forceinline__ void append_init(AppendLds<THREADS> &al)
 {
     al.pid[threadIdx.x] = -1;
     al.count[threadIdx.x] = 0;
@@ -246,7 +247,8 @@ __device__ __forceinline__ void append_init(AppendLds &al)
 // counter per call (a wave's own would queue up: one in 12 ns), none on the problems' counts until
 // append_flush, but for problems that find neither their slot nor a free one within kTallyProbes
 // probes: those count globally.  Called by all threads of the workgroup.
-__device__ __forceinline__ void append(AppendLds &al, bool alive, const Next &nx, int32_t pid, double w,
+template <int THREADS>
+__device__ __forceinline__ void append(AppendLds<THREADS> &al, bool alive, const Next &nx, int32_t pid, double w,
                                        uint32_t hist, uint32_t event, BankDev out,
                                        unsigned long long *counter, unsigned long long *pcount)
 {
@@ -256,7 +258,7 @@ __device__ __forceinline__ void append(AppendLds &al, bool alive, const Next &nx
     __syncthreads();
     if (threadIdx.x == 0) {
         uint32_t total = 0;
-        for (int k = 0; k < kTallyThreads / 64; ++k) {
+        for (int k = 0; k < THREADS / 64; ++k) {
             const uint32_t c = al.wave[k];
             al.wave[k] = total;
             total += c;
@@ -285,12 +287,12 @@ __device__ __forceinline__ void append(AppendLds &al, bool alive, const Next &nx
         m &= ~same;
     }
     if (mine > 0) {
-        uint32_t s = (uint32_t)pid % kTallyThreads;
+        uint32_t s = (uint32_t)pid % THREADS;
         int k = 0;
         for (; k < kTallyProbes; ++k) {
             const int prev = atomicCAS(&al.pid[s], -1, pid);
             if (prev == -1 || prev == pid) break;
-            s = (s + 1) % kTallyThreads;
+            s = (s + 1) % THREADS;
         }
         if (k < kTallyProbes) atomicAdd(&al.count[s], mine);
         else atomicAdd(&pcount[pid], (unsigned long long)mine);
@@ -298,7 +300,8 @@ __device__ __forceinline__ void append(AppendLds &al, bool alive, const Next &nx
     __syncthreads();       // al.wave and al.base are read before the next call writes them
 }
 
-__device__ __forceinline__ void append_flush(AppendLds &al, unsigned long long *pcount)
+template <int THREADS>
+__device__ __forceinline__ void append_flush(AppendLds<THREADS> &al, unsigned long long *pcount)
 {
     __syncthreads();
     if (al.pid[threadIdx.x] >= 0)
@@ -363,7 +366,7 @@ __global__ __launch_bounds__(kTallyThreads) void surface_birth_kernel(CellsDev c
                                                                       unsigned long long *counter,
                                                                       unsigned long long *pcount)
 {
-    __shared__ AppendLds al;
+    __shared__ AppendLds<kTallyThreads> al;
     append_init(al);
     __syncthreads();
     const ProblemDev P = cd.prob[pid];
@@ -429,20 +432,21 @@ __global__ __launch_bounds__(256) void source_kernel(CellsDev cd, int32_t pid, u
 
 // Stages 3-4 of the volumetric births (exits in the cell's own frame, which is the global
 // orientation): tally, move, append.
-__global__ __launch_bounds__(kTallyThreads) void birth_apply_kernel(CellsDev cd, int32_t pid, uint32_t h0,
+template <int THREADS>
+__global__ __launch_bounds__(THREADS) void birth_apply_kernel(CellsDev cd, int32_t pid, uint32_t h0,
                                                                     int64_t count, const int32_t *face_c,
                                                                     const float *pos, const float *dcos,
                                                                     const float *dsin, const float *path,
                                                                     BankDev out, unsigned long long *counter,
                                                                     unsigned long long *pcount)
 {
-    __shared__ TallyLds tl;
-    __shared__ AppendLds al;
+    __shared__ TallyTable<tally_slots(THREADS)> tl;
+    __shared__ AppendLds<THREADS> al;
     tally_init(tl);
     append_init(al);
     __syncthreads();
     const ProblemDev P = cd.prob[pid];
-    for (int64_t t0 = (int64_t)blockIdx.x * kTallyThreads; t0 < count; t0 += (int64_t)gridDim.x * kTallyThreads) {
+    for (int64_t t0 = (int64_t)blockIdx.x * THREADS; t0 < count; t0 += (int64_t)gridDim.x * THREADS) {
         const int64_t t = t0 + threadIdx.x;
         bool alive = false;
         Next nx{};
@@ -760,7 +764,8 @@ struct ExitDev {
 // Stages 3-4 for every alive particle, survivors compacted into `out`.  Bound by its global atomics
 // (5 a cell of a workgroup's table and 2 a wave of survivors in an earlier form): 10^6 particles on
 // the 32 x 32 checkerboard 409 -> 37 us, 2 10^5 on the lattice 123 -> 26 us.
-__global__ __launch_bounds__(kTallyThreads) void apply_kernel(BankDev in, int64_t n_arg,
+template <int THREADS>
+__global__ __launch_bounds__(THREADS) void apply_kernel(BankDev in, int64_t n_arg,
                                                               const unsigned long long *n_dev,
                                                               const int32_t *face_c, const float *pos,
                                                               const float *dcos, const float *dsin,
@@ -768,13 +773,13 @@ __global__ __launch_bounds__(kTallyThreads) void apply_kernel(BankDev in, int64_
                                                               CellsDev cd, BankDev out, unsigned long long *counter,
                                                               unsigned long long *pcount)
 {
-    __shared__ TallyLds tl;
-    __shared__ AppendLds al;
+    __shared__ TallyTable<tally_slots(THREADS)> tl;
+    __shared__ AppendLds<THREADS> al;
     tally_init(tl);
     append_init(al);
     __syncthreads();
     const int64_t n = n_dev ? (int64_t)*n_dev : n_arg;
-    for (int64_t i0 = (int64_t)blockIdx.x * kTallyThreads; i0 < n; i0 += (int64_t)gridDim.x * kTallyThreads) {
+    for (int64_t i0 = (int64_t)blockIdx.x * THREADS; i0 < n; i0 += (int64_t)gridDim.x * THREADS) {
         const int64_t i = i0 + threadIdx.x;
         bool alive = false;
         Next nx{};
@@ -914,10 +919,19 @@ __global__ __launch_bounds__(256) void columns_kernel(CellsDev cd, int64_t cell0
 
 int blocks_for(int64_t n) { return (int)((n + 255) / 256); }
 
-// Grid of a launch that tallies over n particles on a device of cu compute units.
+// Whether a launch over n particles on a device of cu compute units takes small workgroups: with
+// at most 128 particles to a compute unit.  A large one clears and looks through 147 KB for its few
+// particles and adds 1,024 of them to the source's few cells one after another.  Births of 300 / 4,000 /
+// 16,000 histories on the lattice, large -> small: 27.8 -> 26.3 / 30.6 -> 28.0 / 32.7 -> 30.5 us, in a
+// source of one cell 29.3 -> 27.6 / 35.7 -> 29.4 / 37.2 -> 31.2; 33,000 on the lattice the same with
+// both, 65,536 34 against 39.
+bool small_tally(int64_t n, int cu) { return n <= (int64_t)128 * cu; }
+
+// Its grid.
 int tally_blocks(int64_t n, int cu)
 {
-    return (int)std::min<int64_t>((n + kTallyThreads - 1) / kTallyThreads, (int64_t)cu * kTallyBlocksPerCu);
+    if (small_tally(n, cu)) return (int)((n + kSmallTallyThreads - 1) / kSmallTallyThreads);
+    return (int)std::min<int64_t>((n + kTallyThreads - 1) / kTallyThreads, (int64_t)cu);
 }
 
 }  // namespace
@@ -1317,7 +1331,8 @@ int gmc_world_inject(gmc_world *w, int32_t pid, uint64_t h_begin, int64_t count,
         const hipError_t eb = begin_counters(w, s);
         if (eb != hipSuccess) return failed_call(s, set_hip_error(eb, "gmc_world_inject: launch"));
         if (w->src_face[pid] >= 0) {
-            hipLaunchKernelGGL(surface_birth_kernel, dim3(tally_blocks(count, cu)), dim3(kTallyThreads), 0, s, w->cells(),
+            hipLaunchKernelGGL(surface_birth_kernel, dim3((unsigned)std::min<int64_t>((count + kTallyThreads - 1) / kTallyThreads, cu)),
+                               dim3(kTallyThreads), 0, s, w->cells(),
                                pid, (uint32_t)h_begin, count, w->bank[which], ctr, ctr + 1);
         } else if (!w->src_model) {
             const dim3 grid(walk_grid(count, cu));
@@ -1357,10 +1372,13 @@ int gmc_world_inject(gmc_world *w, int32_t pid, uint64_t h_begin, int64_t count,
             hipError_t e = launch_mlp_ode(m->precision, m->hidden, p, cu, s);
             if (e != hipSuccess) return failed_call(s, set_hip_error(e, "gmc_world_inject: internal sampler"));
         }
-        if (w->src_face[pid] < 0)
-            hipLaunchKernelGGL(birth_apply_kernel, dim3(tally_blocks(count, cu)), dim3(kTallyThreads), 0, s, w->cells(), pid,
-                               (uint32_t)h_begin, count, w->e_face, w->e_pos, w->e_dcos, w->e_dsin,
+        if (w->src_face[pid] < 0) {
+            const bool small = small_tally(count, cu);
+            auto *kernel = small ? birth_apply_kernel<kSmallTallyThreads> : birth_apply_kernel<kTallyThreads>;
+            hipLaunchKernelGGL(kernel, dim3(tally_blocks(count, cu)), dim3(small ? kSmallTallyThreads : kTallyThreads), 0,
+                               s, w->cells(), pid, (uint32_t)h_begin, count, w->e_face, w->e_pos, w->e_dcos, w->e_dsin,
                                w->e_path, w->bank[which], ctr, ctr + 1);
+        }
         hipError_t e = hipGetLastError();
         if (e == hipSuccess) e = enqueue_finish(w, which, s);
         if (e != hipSuccess) return failed_call(s, set_hip_error(e, "gmc_world_inject: launch"));
@@ -1502,8 +1520,10 @@ int enqueue_step(gmc_world *w, int sampler, const gmc_model *m, int K, hipStream
     }
     if (e != hipSuccess) return set_hip_error(e, "gmc_transport_step: sampler");
     unsigned long long *ctr = w->cnt(nxt);
-    hipLaunchKernelGGL(apply_kernel, dim3(tally_blocks(n_launch, cu)), dim3(kTallyThreads), 0, s, w->bank[cur], n_launch,
-                       n_dev, w->e_face, w->e_pos, w->e_dcos, w->e_dsin, w->e_path, w->s_slot,
+    const bool small = small_tally(n_launch, cu);
+    auto *kernel = small ? apply_kernel<kSmallTallyThreads> : apply_kernel<kTallyThreads>;
+    hipLaunchKernelGGL(kernel, dim3(tally_blocks(n_launch, cu)), dim3(small ? kSmallTallyThreads : kTallyThreads), 0, s,
+                       w->bank[cur], n_launch, n_dev, w->e_face, w->e_pos, w->e_dcos, w->e_dsin, w->e_path, w->s_slot,
                        ExitDev{w->s_face, w->s_pos, w->s_dcos, w->s_dsin, w->s_path}, w->cells(), w->bank[nxt], ctr,
                        ctr + 1);
     e = hipGetLastError();

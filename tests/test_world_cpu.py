@@ -43,3 +43,7 @@ def test_the_end_of_a_step_has_a_thread_for_every_counter(stub):
 
 def test_the_one_problem_of_a_world_is_known(stub):
     _check(stub, "one_problem")
+
+
+def test_few_particles_are_tallied_by_small_workgroups(stub):
+    _check(stub, "small_tallies")

@@ -199,6 +199,27 @@ def one_problem(lib, stub):
             assert keyed(held[-1]) == (len(held) > 1), held
 
 
+def small_tallies(lib, stub):
+    """Few particles are tallied by workgroups of at most 256 of them, many by at most one workgroup
+    to a compute unit (256 of them here); every particle has a thread either way."""
+    w = World(lib, 1 << 20, 1, 256)
+    pid = w.add(inputs.checkerboard_problem(8, src=2))
+    h = 0
+    for n in (1, 256, 257, 4000, 128 * 256, 128 * 256 + 1, 500_000):
+        stub.S.stub_clear()
+        stub.counts(n, n)
+        assert w.inject(pid, h, n) == (OK, n)
+        stub.counts(0)
+        assert w.step() == (OK, 0)
+        h += n
+        for i in stub.launches("apply_kernel"):                 # the births' and the step's
+            grid, block = stub.S.stub_grid(i), stub.S.stub_block(i)
+            if n <= 128 * 256:
+                assert block == 256 and grid == (n + 255) // 256, (n, grid, block)
+            else:
+                assert block == 1024 and grid == min((n + 1023) // 1024, 256), (n, grid, block)
+
+
 def main():
     lib, stub, check = sys.argv[1:4]
     globals()[check](lib, Stub(stub))
