@@ -973,7 +973,7 @@ struct gmc_world {
     ProblemDev *prob = nullptr;
     unsigned long long *counters = nullptr;   // [2][1 + max_problems]: n_alive, per-problem
     unsigned long long *host_counters = nullptr;
-    double *host_columns = nullptr;           // kHostColumns doubles of pinned memory, after the counters
+    double *host_columns = nullptr;           // host_doubles of pinned memory, after the counters
     // captured transport steps, one per (sampler, model, K, integrator, bank parity, bucket)
     struct StepGraph {
         int sampler, K, integrator, cur, ff, xy;
@@ -1004,12 +1004,13 @@ struct gmc_world {
 
 namespace {
 
-// Doubles of a world's pinned memory (4 MB) through which tallies are read: the kernel that forms
-// their columns stores them there, a part of the cells at a time, and the host copies them on.
+// Doubles of a world's pinned memory (at most 4 MB; five columns of its cells if that is less) through
+// which tallies are read: the kernel that forms their columns stores them there, a part of the
+// cells at a time, and the host copies them on.
 // Four columns / one of 112^2 cells 33 / 18 us, 362^2 195 / 57 us, 3000^2 16.2 / 4.3 ms; by a copy of
 // each column from an array of its own on the device 52 / 14 us, 203 / 53 us, 16.1 / 4.0 ms; by a copy
 // of the cells' four tallies, taken apart on the host, 63 / 36 us, 484 / 349 us, 93 / 81 ms.
-constexpr int64_t kHostColumns = (int64_t)1 << 19;
+int64_t host_doubles(int64_t max_cells) { return std::min<int64_t>((int64_t)1 << 19, 5 * max_cells); }
 
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
@@ -1048,9 +1049,6 @@ void plan(gmc_world *w, Layout &L)
     L.add((void **)&w->s_dcos, 4 * C);
     L.add((void **)&w->s_dsin, 4 * C);
     L.add((void **)&w->s_path, 4 * C);
-    L.add((void **)&w->s_count, 8);
-    L.add((void **)&w->n_large, 16);
-    L.add((void **)&w->streamed, 8);
     L.add((void **)&w->c_cos, 4 * C);
     L.add((void **)&w->ids, 8 * C);
     L.add((void **)&w->keys, 8 * C);
@@ -1067,6 +1065,10 @@ void plan(gmc_world *w, Layout &L)
     L.add((void **)&w->rej_w, 8 * N);
     L.add((void **)&w->rej_n, 8 * N);
     L.add((void **)&w->prob, sizeof(ProblemDev) * P);
+    // cleared together when the world is made
+    L.add((void **)&w->s_count, 8);
+    L.add((void **)&w->streamed, 8);
+    L.add((void **)&w->n_large, 16);
     L.add((void **)&w->counters, 8 * 2 * (1 + P));
 }
 
@@ -1154,7 +1156,8 @@ int gmc_world_create(int64_t bank_capacity, int32_t max_problems, int64_t max_ce
     e = hipMalloc(&w->mem, L.total);
     if (e != hipSuccess) { delete w; return set_error(GMC_ENOMEM, "gmc_world_create: device allocation failed"); }
     for (auto &pr : L.parts) *pr.first = (char *)w->mem + pr.second;
-    e = hipHostMalloc((void **)&w->host_counters, 8 * ((size_t)(2 + max_problems) + kHostColumns), hipHostMallocDefault);
+    e = hipHostMalloc((void **)&w->host_counters, 8 * ((size_t)(2 + max_problems) + host_doubles(max_cells)),
+                      hipHostMallocDefault);
     if (e != hipSuccess) {
         (void)hipFree(w->mem);
         delete w;
@@ -1162,9 +1165,7 @@ int gmc_world_create(int64_t bank_capacity, int32_t max_problems, int64_t max_ce
     }
     std::memset(w->host_counters, 0, 8 * (size_t)(2 + max_problems));
     w->host_columns = (double *)(w->host_counters + 2 + max_problems);
-    e = hipMemset(w->counters, 0, 8 * 2 * (size_t)(1 + max_problems));
-    if (e == hipSuccess) e = hipMemset(w->streamed, 0, 8);
-    if (e == hipSuccess) e = hipMemset(w->s_count, 0, 8);
+    e = hipMemset(w->s_count, 0, (size_t)((char *)w->mem + L.total - (char *)w->s_count));
     if (e == hipSuccess) e = hipDeviceSynchronize();
     if (e != hipSuccess) {
         (void)hipHostFree(w->host_counters);
@@ -1644,7 +1645,7 @@ int read_columns(gmc_world *w, int32_t pid, const Column *cols, double *const *d
             q.col[q.count] = cols[i];
             to[q.count++] = dst[i];
         }
-    const int64_t most = kHostColumns / (q.count > 0 ? q.count : 1);
+    const int64_t most = host_doubles(w->max_cells) / (q.count > 0 ? q.count : 1);
     for (int64_t i0 = 0; q.count > 0 && i0 < n; i0 += most) {
         const int64_t m = std::min(most, n - i0);
         hipLaunchKernelGGL(columns_kernel, dim3(blocks_for(m)), dim3(256), 0, s, w->cells(), P.cell0 + i0, m, V, q,
