@@ -590,6 +590,12 @@ constexpr int kStreamThreads = 512;
 constexpr int kStreamBlocksPerCu = 1;
 constexpr int kStreamRefill = 16;
 using TallyStream = TallyTable<4096>;
+// Largest bank of a world and most cells that a particle streams through in a step: together the
+// crossings that one workgroup may count.
+constexpr int64_t kMaxBank = (int64_t)1 << 31;
+constexpr int kMaxStreaming = 1024;
+using StreamCount = unsigned long long;
+static_assert((unsigned long long)kMaxBank * kMaxStreaming <= ~(StreamCount)0, "a workgroup's count of crossings");
 
 template <bool ONE>
 __global__ __launch_bounds__(kStreamThreads) void gather_split_kernel(BankDev b, int64_t n_arg,
@@ -601,7 +607,8 @@ __global__ __launch_bounds__(kStreamThreads) void gather_split_kernel(BankDev b,
                                                                       unsigned long long *streamed)
 {
     __shared__ TallyStream tl;
-    __shared__ uint32_t pool, beyond, waves[kStreamThreads / 64];
+    __shared__ uint32_t pool, waves[kStreamThreads / 64];
+    __shared__ StreamCount beyond;
     __shared__ unsigned long long first;
     tally_init(tl);
     if (threadIdx.x == 0) {
@@ -622,7 +629,8 @@ __global__ __launch_bounds__(kStreamThreads) void gather_split_kernel(BankDev b,
     int cell = 0, ci = 0, cj = 0, e = 0;
     float gx = 0.0f, gy = 0.0f, yy = 0.0f;
     double w = 0.0;
-    uint32_t ev = 0, hist = 0, passed = 0, tot = 0;
+    uint32_t ev = 0, hist = 0, passed = 0;
+    StreamCount tot = 0;
     int32_t fate = 0;
     DrawPrefix q{};
     bool dry = mine.items == 0;
@@ -723,10 +731,10 @@ __global__ __launch_bounds__(kStreamThreads) void gather_split_kernel(BankDev b,
         }
     }
 #pragma unroll
-    for (int m = 32; m >= 1; m >>= 1) tot += (uint32_t)__shfl_xor((int)tot, m);
+    for (int m = 32; m >= 1; m >>= 1) tot += __shfl_xor(tot, m);
     if (lane == 0 && tot > 0) atomicAdd(&beyond, tot);
     __syncthreads();                         // also: the bank's and e_face's new values
-    if (threadIdx.x == 0 && beyond > 0) atomicAdd(streamed, (unsigned long long)beyond);
+    if (threadIdx.x == 0 && beyond > 0) atomicAdd(streamed, beyond);
     tally_flush(tl, cd);
     // the collided particles of this share to the sampler's staging, one atomic per workgroup tile
     for (uint32_t v0 = 0; v0 < mine.items; v0 += kStreamThreads) {
@@ -1140,7 +1148,7 @@ int gmc_world_create(int64_t bank_capacity, int32_t max_problems, int64_t max_ce
 {
     if (!out) return set_error(GMC_EINVAL, "gmc_world_create: null output");
     *out = nullptr;
-    if (bank_capacity <= 0 || bank_capacity > ((int64_t)1 << 31) || max_problems <= 0 ||
+    if (bank_capacity <= 0 || bank_capacity > kMaxBank || max_problems <= 0 ||
         max_problems > 65536 || max_cells <= 0 || max_cells > ((int64_t)1 << 31))
         return set_error(GMC_EINVAL, "gmc_world_create: capacity out of range");
     const int irc = gmc_device_init();
@@ -1414,7 +1422,7 @@ int gmc_world_set_integrator(gmc_world *w, int integrator)
 int gmc_world_set_streaming(gmc_world *w, int max_crossings)
 {
     if (!w) return set_error(GMC_EINVAL, "gmc_world_set_streaming: null world");
-    if (max_crossings < 1 || max_crossings > 1024)
+    if (max_crossings < 1 || max_crossings > kMaxStreaming)
         return set_error(GMC_EINVAL, "gmc_world_set_streaming: max_crossings must be in 1..1024");
     std::lock_guard<std::mutex> lk(w->mu);
     w->ff_max = max_crossings;
