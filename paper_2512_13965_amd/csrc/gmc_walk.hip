@@ -27,7 +27,7 @@ __global__ __launch_bounds__(kWalkThreads, kWalkBlocksPerCu) void walk_kernel(Wa
             w.wa = la == 0.0f ? 1.0f : expf(la);
             w.x = p.x_in ? p.x_in[i] : 0.0f;       // birth inside the cell, or entry on the left face
             w.y = p.y_in[i];
-            w.u = p.x_in ? p.cos_phi[i] : (XY ? p.omega_x[i] : sqrtf(fmaxf(1.0f - s * s, 0.0f)));
+            w.u = p.x_in ? p.cos_phi[i] : (XY ? p.omega_x[i] : sqrtf(fmaxf(__builtin_fmaf(-s, s, 1.0f), 0.0f)));
             w.v = s;
             w.tau = expf(p.log_tau[i]);
             w.c = p.c[i];

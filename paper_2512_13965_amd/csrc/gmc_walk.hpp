@@ -16,7 +16,8 @@
 //     three lanes of the group follow, one for x, one for y and one for the path length, a
 //     fused multiply-add a flight; then each lane tests its own flight for the cell's boundary
 //     and the first one that ends the walk writes its record.  Every value is the one that the
-//     first regime computes, bit for bit.
+//     first regime computes, bit for bit: all fused multiply-adds are written as such, none is
+//     left to the compiler's choice.
 // The walks are dealt out to blocks in advance (BlockShare), and the waves of a block take from
 // its share through a counter in LDS.  One counter for the whole launch costs more than the walks where they are
 // short: same-address atomics complete one in 13 ns (2^23 walks at tau = 1, 64 to an atomic:
@@ -176,11 +177,11 @@ __device__ __forceinline__ int walk_exit(float x, float y, float u, float v, flo
                                          float &pos)
 {
     if (xface) {
-        const float ye = fminf(fmaxf(y + db * v, 0.0f), 1.0f);
+        const float ye = fminf(fmaxf(__builtin_fmaf(db, v, y), 0.0f), 1.0f);
         pos = u > 0.0f ? ye : 1.0f - ye;
         return u > 0.0f ? 1 : 3;
     }
-    const float xe = fminf(fmaxf(x + db * u, 0.0f), wa);
+    const float xe = fminf(fmaxf(__builtin_fmaf(db, u, x), 0.0f), wa);
     pos = v > 0.0f ? (wa - xe) / wa : xe / wa;
     return v > 0.0f ? 2 : 0;
 }
@@ -201,8 +202,8 @@ __device__ __forceinline__ void scatter_direction(const U4 &r, float &u, float &
     u = cos_turns(ph);
     v = sin_turns(ph);
     if constexpr (XY) {
-        const float mu = 2.0f * u01(r.d) - 1.0f;
-        const float st = sqrtf(fmaxf(1.0f - mu * mu, 0.0f));
+        const float mu = __builtin_fmaf(2.0f, u01(r.d), -1.0f);
+        const float st = sqrtf(fmaxf(__builtin_fmaf(-mu, mu, 1.0f), 0.0f));
         u *= st;
         v *= st;
     }
@@ -304,8 +305,8 @@ __device__ __forceinline__ void run_walks(int64_t n, uint64_t seed, WalkGroups *
                     alive = false;
                 } else {
                     len += ds;
-                    x += ds * u;
-                    y += ds * v;
+                    x = __builtin_fmaf(ds, u, x);
+                    y = __builtin_fmaf(ds, v, y);
                     flight += 1;
                     if (ANALOG && u01(r.c) > cs) {
                         alive = false;
