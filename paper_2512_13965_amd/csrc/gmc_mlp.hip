@@ -24,36 +24,6 @@
 #include "gmc_internal.hpp"
 #include "gmc_mma.hpp"
 
-// MFMA / epilogue interleave: vector instructions placed after each MFMA in the overlapped
-// k-loops (0 = leave the order to the scheduler).
-#ifndef GMC_VPM_A
-#define GMC_VPM_A 0
-#endif
-#ifndef GMC_VPM_P
-#define GMC_VPM_P 0
-#endif
-#ifndef GMC_VPM_5
-#define GMC_VPM_5 0
-#endif
-#ifndef GMC_DRAIN_STAGED
-#define GMC_DRAIN_STAGED 1
-#endif
-#ifndef GMC_DRAIN_W
-#define GMC_DRAIN_W 16
-#endif
-// Drains of the two-group schedule: 1 = software-pipelined epilogue (drain_pipe), 0 = one
-// accumulator tile at a time (epi_tile).  GMC_PIPE_D: iterations between a value's stages.
-#ifndef GMC_DRAIN_PIPE
-#define GMC_DRAIN_PIPE 1
-#endif
-#ifndef GMC_PIPE_D
-#define GMC_PIPE_D 1
-#endif
-// 8: BF16 / FP8 models of width >= 256 use the two-group schedule (eight waves); 4: they use
-// the single-group cross-layer pipeline (four waves).  Both give bit-identical results.
-#ifndef GMC_WIDE_WAVES
-#define GMC_WIDE_WAVES 8
-#endif
 namespace gmc {
 namespace {
 
@@ -65,111 +35,23 @@ namespace {
 // activation scale (a power of two, folded into the reciprocal's argument) and their e4m3
 // layers apply 2 sw sa through the matrix core's operand scale.  FP32 models keep plain
 // activations.
-template <int PO, bool SCALE>
-constexpr bool exp2_folded()
+
+// One epilogue unit of an FP32 model: the activation of accumulator values 4g .. 4g+3.
+__device__ __forceinline__ void epi_unit(const f32x16 &acc, int g, uint32_t *w)
 {
-    return SCALE || PO == kBF16;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) w[j] = __builtin_bit_cast(uint32_t, silu(acc[4 * g + j]));
 }
 
-// -log2(e) SiLU(a) from a' = -log2(e) a.
-__device__ __forceinline__ float silu_exp2(float a)
-{
-    return a * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(a));
-}
-
-// Multiplier of the accumulator that gives the exponential's argument: -log2(e) times the
-// scaled pre-activation, or 1 where the activations carry that factor already.
-template <int PO, bool SCALE>
-__device__ __forceinline__ float exp2_factor(float)
-{
-    if constexpr (exp2_folded<PO, SCALE>()) return 1.0f;
-    else return -1.4426950408889634f;
-}
-
-// One epilogue unit: the activation of accumulator values 4g .. 4g+3 times oscale * inv_next,
-// packed in the consumer's operand type (BF16 and FP8 models: the scaled activation, see
-// exp2_folded).
-template <int PO, bool SCALE>
-__device__ __forceinline__ void epi_unit(const f32x16 &acc, int g, float oscale, float inv_next,
-                                         uint32_t *w)
-{
-    float y[4];
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        const float a = acc[4 * g + j];
-        if constexpr (SCALE) y[j] = silu_exp2(a) * (oscale * inv_next);
-        else if constexpr (exp2_folded<PO, SCALE>()) y[j] = silu_exp2(a);
-        else y[j] = silu(a);
-    }
-    if constexpr (PO == kF32) {
-#pragma unroll
-        for (int j = 0; j < 4; ++j) w[j] = __builtin_bit_cast(uint32_t, y[j]);
-    } else if constexpr (PO == kBF16) {
-        w[0] = pack_bf16(y[0], y[1]);
-        w[1] = pack_bf16(y[2], y[3]);
-    } else {
-        w[0] = pack_fp8x4(y[0], y[1], y[2], y[3]);
-    }
-}
-
-// The epilogue of a whole accumulator tile (16 values per lane): the operations of epi_unit,
-// issued stage by stage over DW values so that independent transcendentals follow each other.
-template <int PO, bool SCALE>
-__device__ __forceinline__ void epi_tile(const f32x16 &acc, float oscale, float inv_next, uint32_t *w)
-{
-#if GMC_DRAIN_STAGED
-    constexpr int DW = GMC_DRAIN_W;
-    // acc * c1 is the exponential's argument (c1 = 1 where the accumulator carries -log2(e));
-    // with per-layer scales (powers of two) (acc * c2) * sigmoid is (acc * sigmoid) * c2 with
-    // its single rounding, since scaling by a power of two is exact.
-    const float c1 = exp2_factor<PO, SCALE>(oscale);
-    const float c2 = oscale * inv_next;
-    sfor<16 / DW>([&](auto HH) {
-        constexpr int h0 = decltype(HH)::value * DW;
-        float a[DW], t[DW];
-#pragma unroll
-        for (int i = 0; i < DW; ++i) {
-            a[i] = SCALE ? acc[h0 + i] * c2 : acc[h0 + i];
-            t[i] = c1 * acc[h0 + i];
-        }
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int i = 0; i < DW; ++i) t[i] = __builtin_amdgcn_exp2f(t[i]);
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int i = 0; i < DW; ++i) t[i] = __builtin_amdgcn_rcpf(1.0f + t[i]);
-        __builtin_amdgcn_sched_barrier(0);
-        float y[DW];
-#pragma unroll
-        for (int i = 0; i < DW; ++i) y[i] = a[i] * t[i];
-        if constexpr (PO == kF32) {
-#pragma unroll
-            for (int i = 0; i < DW; ++i) w[h0 + i] = __builtin_bit_cast(uint32_t, y[i]);
-        } else if constexpr (PO == kBF16) {
-#pragma unroll
-            for (int i = 0; i < DW / 2; ++i) w[h0 / 2 + i] = pack_bf16(y[2 * i], y[2 * i + 1]);
-        } else {
-#pragma unroll
-            for (int i = 0; i < DW / 4; ++i) w[h0 / 4 + i] = pack_fp8x4(y[4 * i], y[4 * i + 1], y[4 * i + 2], y[4 * i + 3]);
-        }
-    });
-#else
-    constexpr int WPU = words_per_unit(PO);
-#pragma unroll
-    for (int g = 0; g < 4; ++g) epi_unit<PO, SCALE>(acc, g, oscale, inv_next, &w[g * WPU]);
-#endif
-}
-
-// The SiLU epilogue of the NT accumulator tiles a(t) (16 values each, value i = 16 t + i % 16),
-// software-pipelined: iteration j issues the first multiply of value j, the exponential of value
-// j - D, the add of value j - 2D, the reciprocal of value j - 3D and the final multiply of value
-// j - 4D -- independent instructions -- and packs groups of values as they complete;
-// store(t, words) receives each tile's packed words (the layout of epi_tile) once its last value
-// is done.  The arithmetic is epi_tile's: acc * c1 is -log2(e) times the pre-activation (c1 = 1
-// in BF16 and FP8 models, whose accumulators carry the factor: the multiply drops out), and
-// with per-layer scales the output factor c2 = oscale * inv_next (a power of two) moves into
-// the reciprocal's argument, acc * rcp((1 + e) / c2) being exactly (acc * c2) * rcp(1 + e).
+// The SiLU epilogue of the NT accumulator tiles a(t) of a BF16 or FP8 model (16 values each, value
+// i = 16 t + i % 16), software-pipelined: iteration j issues the exponential of value j - D, the add of
+// value j - 2D, the reciprocal of value j - 3D and the final multiply of value j - 4D -- independent
+// instructions -- and packs groups of values as they complete; store(t, words) receives each
+// tile's packed words once its last value is done.  With per-layer scales the output factor
+// oscale * inv_next (a power of two) goes into the reciprocal's argument, acc * rcp((1 + e) / c)
+// being exactly (acc * c) * rcp(1 + e).
 // hook(j) runs in iteration j (matrix work of the same wave, spread over the pipeline).
+constexpr int kPipeD = 1;
 struct NoHook {
     template <typename J> __device__ __forceinline__ void operator()(J) const {}
 };
@@ -177,14 +59,14 @@ template <int PO, bool SCALE, int NT, typename Val, typename Store, typename Hoo
 __device__ __forceinline__ void drain_pipe(Val &&val, float oscale, float inv_next, Store &&store, Hook &&hook = Hook{})
 {
     constexpr int NV = NT * 16;
-    constexpr int D = GMC_PIPE_D;
-    const float c1 = exp2_factor<PO, SCALE>(oscale);
+    constexpr int D = kPipeD;
+    static_assert(PO == kBF16 || PO == kFP8, "FP32 models take epi_unit");
     const float k = SCALE ? 1.0f / (oscale * inv_next) : 1.0f;
     float t[NV], y[NV];
     uint32_t wd[NT][4 * words_per_unit(PO)];
     sfor<NV + 4 * D>([&](auto J) {
         constexpr int j = decltype(J)::value;
-        if constexpr (j < NV) t[j] = c1 * val(std::integral_constant<int, j>{});
+        if constexpr (j < NV) t[j] = val(std::integral_constant<int, j>{});
         if constexpr (j - D >= 0 && j - D < NV) t[j - D] = __builtin_amdgcn_exp2f(t[j - D]);
         if constexpr (j - 2 * D >= 0 && j - 2 * D < NV) {
             if constexpr (SCALE) t[j - 2 * D] = __builtin_fmaf(t[j - 2 * D], k, k);
@@ -195,9 +77,7 @@ __device__ __forceinline__ void drain_pipe(Val &&val, float oscale, float inv_ne
             constexpr int i = j - 4 * D;
             y[i] = val(std::integral_constant<int, i>{}) * t[i];
             constexpr int tt = i / 16, v = i % 16;
-            if constexpr (PO == kF32) {
-                wd[tt][v] = __builtin_bit_cast(uint32_t, y[i]);
-            } else if constexpr (PO == kBF16) {
+            if constexpr (PO == kBF16) {
                 if constexpr (v % 2 == 1) wd[tt][v / 2] = pack_bf16(y[i - 1], y[i]);
             } else {
                 if constexpr (v % 4 == 3) wd[tt][v / 4] = pack_fp8x4(y[i - 3], y[i - 2], y[i - 1], y[i]);
@@ -210,32 +90,32 @@ __device__ __forceinline__ void drain_pipe(Val &&val, float oscale, float inv_ne
 }
 
 
-// One dense layer + SiLU for this wave's RTW row tiles and all CT column tiles of samples.  The
-// rows are done in NP passes of RP row tiles; the epilogue of pass p runs interleaved with the
+// One dense layer + SiLU of an FP32 model for this wave's RTW row tiles and all CT column tiles of
+// samples.  The rows are done in NP passes of RP row tiles; the epilogue of pass p runs interleaved with the
 // MFMA k-loop of pass p + 1 (it only reads pass p's accumulators), so the SiLU transcendentals
 // overlap the matrix unit.  Those results are held packed in registers until every wave has
 // finished reading the input tile (barrier, when `out` aliases the input); the last pass's
 // epilogue is computed and stored after that barrier.
-template <int PIN, int POUT, int RTW, int CT, int NKB, bool SCALE, bool IN_PLACE>
+template <int RTW, int CT, int NKB, bool IN_PLACE>
 __device__ __forceinline__ void dense_silu(Rsrc wA, Rsrc bias, int T0, const char *in, int in_stride, char *out,
-                                           int out_stride, int lane, float oscale, float inv_next, int sc = 127)
+                                           int out_stride, int lane)
 {
     constexpr int RP = RTW >= 4 ? RTW / 2 : 1;     // row tiles per pass
     constexpr int NP = RTW / RP;                   // passes
     constexpr int UNITS = RP * CT * 4;             // epilogue units (4 values) per pass
-    constexpr int WPU = words_per_unit(POUT);
+    constexpr int WPU = words_per_unit(kF32);
     constexpr int UPK = (UNITS + NKB - 1) / NKB;   // epilogue units per k-block
     uint32_t pk[NP > 1 ? NP - 1 : 1][UNITS * WPU];
     f32x16 acc[2][RP][CT];
     auto epi = [&](auto PP, int u) {
         constexpr int pp = decltype(PP)::value;
         const int r = u / (4 * CT), c = (u / 4) % CT, g = u % 4;
-        epi_unit<POUT, SCALE>(acc[pp % 2][r][c], g, oscale, inv_next, &pk[pp][u * WPU]);
+        epi_unit(acc[pp % 2][r][c], g, &pk[pp][u * WPU]);
     };
     sfor<NP>([&](auto P) {
         constexpr int p = decltype(P)::value;
         init_bias<RP, CT>(acc[p % 2], bias, T0 + p * RP, lane);
-        mma_pass<PIN, RP, CT, NKB>(acc[p % 2], wA, T0 + p * RP, in, in_stride, 0, lane, [&](auto KB) {
+        mma_pass<kF32, RP, CT, NKB>(acc[p % 2], wA, T0 + p * RP, in, in_stride, 0, lane, [&](auto KB) {
             constexpr int kb = decltype(KB)::value;
             if constexpr (p > 0) {
                 sfor<UPK>([&](auto J) {
@@ -243,7 +123,7 @@ __device__ __forceinline__ void dense_silu(Rsrc wA, Rsrc bias, int T0, const cha
                     if constexpr (u < UNITS) epi(std::integral_constant<int, p - 1>{}, u);
                 });
             }
-        }, sc);
+        });
         if constexpr (p > 0 && NKB * UPK < UNITS) {
             sfor<UNITS - NKB * UPK>([&](auto J) {
                 epi(std::integral_constant<int, p - 1>{}, NKB * UPK + decltype(J)::value);
@@ -255,7 +135,7 @@ __device__ __forceinline__ void dense_silu(Rsrc wA, Rsrc bias, int T0, const cha
         constexpr int p = decltype(P)::value;
         sfor<RP * CT>([&](auto TC) {
             constexpr int r = decltype(TC)::value / CT, c = decltype(TC)::value % CT;
-            store_tile<POUT>(&pk[p][(r * CT + c) * 4 * WPU], T0 + p * RP + r, c, out, out_stride, lane);
+            store_tile<kF32>(&pk[p][(r * CT + c) * 4 * WPU], T0 + p * RP + r, c, out, out_stride, lane);
         });
     });
     constexpr int pl = NP - 1;
@@ -263,32 +143,32 @@ __device__ __forceinline__ void dense_silu(Rsrc wA, Rsrc bias, int T0, const cha
         constexpr int r = decltype(TC)::value / CT, c = decltype(TC)::value % CT;
         uint32_t w[4 * WPU];
 #pragma unroll
-        for (int g = 0; g < 4; ++g) epi_unit<POUT, SCALE>(acc[pl % 2][r][c], g, oscale, inv_next, &w[g * WPU]);
-        store_tile<POUT>(w, T0 + pl * RP + r, c, out, out_stride, lane);
+        for (int g = 0; g < 4; ++g) epi_unit(acc[pl % 2][r][c], g, &w[g * WPU]);
+        store_tile<kF32>(w, T0 + pl * RP + r, c, out, out_stride, lane);
     });
 }
 
 // Part J of NJ of draining accumulator tiles src[RP][CT] through the epilogue into packed words.
-template <int PO, bool SCALE, int NJ, int J, int RP, int CT>
-__device__ __forceinline__ void drain_step(const f32x16 (&src)[RP][CT], uint32_t *pk, float osc, float inv)
+template <int NJ, int J, int RP, int CT>
+__device__ __forceinline__ void drain_step(const f32x16 (&src)[RP][CT], uint32_t *pk)
 {
     constexpr int UNITS = RP * CT * 4;
     constexpr int UPK = (UNITS + NJ - 1) / NJ;
-    constexpr int WPU = words_per_unit(PO);
+    constexpr int WPU = words_per_unit(kF32);
     sfor<UPK>([&](auto U) {
         constexpr int u = J * UPK + decltype(U)::value;
-        if constexpr (u < UNITS) epi_unit<PO, SCALE>(src[u / (4 * CT)][(u / 4) % CT], u % 4, osc, inv, &pk[u * WPU]);
+        if constexpr (u < UNITS) epi_unit(src[u / (4 * CT)][(u / 4) % CT], u % 4, &pk[u * WPU]);
     });
 }
 
 // Store the packed outputs of one row pass (row tiles Tb .. Tb + RP - 1, all column tiles).
-template <int PO, int RP, int CT>
+template <int RP, int CT>
 __device__ __forceinline__ void store_pass(const uint32_t *pk, int Tb, char *act, int stride, int lane)
 {
-    constexpr int WPU = words_per_unit(PO);
+    constexpr int WPU = words_per_unit(kF32);
     sfor<RP * CT>([&](auto TC) {
         constexpr int r = decltype(TC)::value / CT, c = decltype(TC)::value % CT;
-        store_tile<PO>(&pk[(r * CT + c) * 4 * WPU], Tb + r, c, act, stride, lane);
+        store_tile<kF32>(&pk[(r * CT + c) * 4 * WPU], Tb + r, c, act, stride, lane);
     });
 }
 
@@ -305,7 +185,8 @@ struct Cfg {
     // first half of every layer's output rows, group 1 the second half; while one group's
     // waves run the matrix k-loop, the other group's waves run the SiLU epilogue on the same
     // SIMDs, so vector and matrix work overlap across waves.
-    static constexpr bool GROUPS = (MP != kF32 && H >= 256 && GMC_WIDE_WAVES == 8);
+    static constexpr bool GROUPS = (MP != kF32);
+    static_assert(!GROUPS || H >= 256, "width 128 has kernels of its own");
     static constexpr int W = GROUPS ? 8 : kWaves;
     static constexpr int THREADS = 64 * W;
     static constexpr int NT = H / 32;                       // row tiles of a hidden layer
@@ -316,13 +197,12 @@ struct Cfg {
     static constexpr int NKB5 = H / kb_width(P5);
     static constexpr int RP = RTW >= 4 ? RTW / 2 : 1;       // row tiles per pass
     static constexpr int NP = RTW / RP;                     // row passes per layer
-    // Cross-layer pipelining: pass p of wave w computes row tiles p * NT / 2 + w * RP + r, so
+    // Cross-layer pipelining (FP32): pass p of wave w computes row tiles p * NT / 2 + w * RP + r, so
     // the first passes of all waves fill the first half of the consumer's k-blocks and the
     // second passes the other half; each half must be whole k-blocks.
     static constexpr bool PIPE = !GROUPS && NP == 2 && NKBH % 2 == 0 && NKB5 % 2 == 0;
-    static constexpr int GH = (PIPE || GROUPS) ? NKBH / 2 : 1;
-    static constexpr int G5 = (PIPE || GROUPS) ? NKB5 / 2 : 1;
-    static constexpr int WPK = words_per_unit(PH) > words_per_unit(P5) ? words_per_unit(PH) : words_per_unit(P5);
+    static constexpr int GH = PIPE ? NKBH / 2 : 1;
+    static constexpr int G5 = PIPE ? NKB5 / 2 : 1;
     static constexpr int CT = TM / 32;                      // sample column tiles of a tile
     static constexpr int LDS_ACT = TM * ACT_STRIDE;
     static constexpr int LDS_IN = TM * IN_STRIDE;
@@ -493,13 +373,12 @@ __global__ __launch_bounds__((Cfg<MP, H, TM>::THREADS), 1) void mlp_ode_kernel(M
             // Two-group schedule: the layer-5 lanes apply the integrator's update (Euler step, RK4
             // stage) and write the next input row themselves, so the input row is assembled here
             // only for the first evaluation.
-            constexpr bool fold = C::GROUPS;
             for (int e = 0; e < nevals; ++e) {
                 const int stage = rk4 ? (e & 3) : 0;
                 const int k = rk4 ? (e >> 2) : e;
                 const float t = ((float)k + (stage == 0 ? 0.0f : (stage == 3 ? 1.0f : 0.5f))) * dt;
                 // layer-1 input row of sample tid: [x0..x4, t, ln tau, c, 2y-1, sin th, 0 x 6]
-                if ((!fold || (e == 0 && grp == 0)) && tid < TM) {
+                if ((!C::GROUPS || (e == 0 && grp == 0)) && tid < TM) {
                     float v[16];
                     if (!rk4 || e == 0) {
 #pragma unroll
@@ -525,7 +404,7 @@ __global__ __launch_bounds__((Cfg<MP, H, TM>::THREADS), 1) void mlp_ode_kernel(M
                                       pack_bf16(v[8 * q + 4], v[8 * q + 5]), pack_bf16(v[8 * q + 6], v[8 * q + 7])};
                     }
                 }
-                if (!fold || e == 0) __syncthreads();
+                if (!C::GROUPS || e == 0) __syncthreads();
 
                 if constexpr (C::GROUPS) {
                     // Two-group schedule.  Per hidden layer, three barrier-separated phases:
@@ -552,7 +431,6 @@ __global__ __launch_bounds__((Cfg<MP, H, TM>::THREADS), 1) void mlp_ode_kernel(M
                         constexpr int PO = decltype(POC)::value;
                         using A = std::remove_reference_t<decltype(a)>;
                         constexpr int RX = std::extent_v<A, 0>, CX = std::extent_v<A, 1>;
-#if GMC_DRAIN_PIPE
                         drain_pipe<PO, C::SCALE, RX * CX>(
                             [&](auto I) {
                                 constexpr int i = decltype(I)::value;
@@ -563,20 +441,10 @@ __global__ __launch_bounds__((Cfg<MP, H, TM>::THREADS), 1) void mlp_ode_kernel(M
                                 constexpr int tt = decltype(TT)::value;
                                 store_tile<PO>(wd, (T0 + tt / CX) ^ xt, c0 + tt % CX, act, C::ACT_STRIDE, lane);
                             });
-                        return;
-#endif
-                        sfor<RX * CX>([&](auto TC) {
-                            constexpr int r = decltype(TC)::value / CX, c = decltype(TC)::value % CX;
-                            uint32_t wd[4 * words_per_unit(PO)];
-                            epi_tile<PO, C::SCALE>(a[r][c], osc, inv, wd);
-                            store_tile<PO>(wd, (T0 + r) ^ xt, c0 + c, act, C::ACT_STRIDE, lane);
-                        });
                     };
                     auto drain = [&](auto POC, float osc, float inv, int xt = 0) {
                         const int lane = here();
                         constexpr int PO = decltype(POC)::value;
-                        constexpr int WPU = words_per_unit(PO);
-#if GMC_DRAIN_PIPE
                         drain_pipe<PO, C::SCALE, RG * C::CT>(
                             [&](auto I) {
                                 constexpr int i = decltype(I)::value;
@@ -587,14 +455,6 @@ __global__ __launch_bounds__((Cfg<MP, H, TM>::THREADS), 1) void mlp_ode_kernel(M
                                 constexpr int tt = decltype(TT)::value;
                                 store_tile<PO>(wd, (TB + tt / C::CT) ^ xt, tt % C::CT, act, C::ACT_STRIDE, lane);
                             });
-                        return;
-#endif
-                        sfor<RG * C::CT>([&](auto TC) {
-                            constexpr int r = decltype(TC)::value / C::CT, c = decltype(TC)::value % C::CT;
-                            uint32_t wd[4 * WPU];
-                            epi_tile<PO, C::SCALE>(acc[r][c], osc, inv, wd);
-                            store_tile<PO>(wd, (TB + r) ^ xt, c, act, C::ACT_STRIDE, lane);
-                        });
                     };
                     // layer 1 (10 -> H): both groups multiply their own rows; group 0 writes them now,
                     // group 1 during the first hidden layer's P1.  FP8 models (whose epilogue has
@@ -700,7 +560,7 @@ __global__ __launch_bounds__((Cfg<MP, H, TM>::THREADS), 1) void mlp_ode_kernel(M
                     }
                     if (grp == 0 && (C::CT == 4 || wg < C::CT)) {
                         const int sn = wg * 32 + (lane & 31);
-                        if constexpr (fold && !rk4) {
+                        if constexpr (!rk4) {
                             // x += dt v, then the next input row's x (and t) in BF16
                             char *row = in0 + sn * C::IN_STRIDE;
                             if (lane < 32) {
@@ -716,7 +576,7 @@ __global__ __launch_bounds__((Cfg<MP, H, TM>::THREADS), 1) void mlp_ode_kernel(M
                                 xs[4 * TM + sn] = x4;
                                 *(uint32_t *)(row + 8) = pack_bf16(x4, (float)(e + 1) * dt);
                             }
-                        } else if constexpr (fold) {
+                        } else {
                             // RK4 (the arithmetic of advance): stages 0..2 add v to the stage sum
                             // and give the next stage's input, stage 3 finishes the step; then the
                             // next input row's x (and t) in BF16
@@ -740,11 +600,6 @@ __global__ __launch_bounds__((Cfg<MP, H, TM>::THREADS), 1) void mlp_ode_kernel(M
                                 const float x4 = update(4, out[0][0][0]);
                                 *(uint32_t *)(row + 8) = pack_bf16(x4, t1);
                             }
-                        } else if (lane < 32) {
-#pragma unroll
-                            for (int d = 0; d < 4; ++d) emit(d, sn, out[0][0][d]);
-                        } else {
-                            emit(4, sn, out[0][0][0]);
                         }
                     }
                     __syncthreads();
@@ -758,63 +613,54 @@ __global__ __launch_bounds__((Cfg<MP, H, TM>::THREADS), 1) void mlp_ode_kernel(M
                     // and the remaining k-blocks follow after a barrier.
                     constexpr int RP = C::RP, CT = C::CT;
                     f32x16 X[RP][CT], Y[RP][CT];
-                    uint32_t pk[RP * CT * 4 * C::WPK];
+                    uint32_t pk[RP * CT * 4 * words_per_unit(kF32)];
                     const Rsrc w0 = make_rsrc(p.wA[0], p.wA_bytes[0]), b0 = make_rsrc(p.bias[0], p.bias_bytes[0]);
                     init_bias<RP, CT>(X, b0, TX, lane);
-                    mma_seq<C::P1, RP, CT, C::NKB1, C::NKB1, MapAll>(X, w0, TX, in0, C::IN_STRIDE, 0, lane, [](auto) {});
+                    mma_seq<kF32, RP, CT, C::NKB1, C::NKB1, MapAll>(X, w0, TX, in0, C::IN_STRIDE, 0, lane, [](auto) {});
                     init_bias<RP, CT>(Y, b0, TY, lane);
-                    mma_seq<C::P1, RP, CT, C::NKB1, C::NKB1, MapAll>(Y, w0, TY, in0, C::IN_STRIDE, 0, lane, [&](auto J) {
-                        drain_step<C::PH, C::SCALE, C::NKB1, decltype(J)::value>(X, pk, p.oscale[0], p.inv_in_scale[1]);
+                    mma_seq<kF32, RP, CT, C::NKB1, C::NKB1, MapAll>(Y, w0, TY, in0, C::IN_STRIDE, 0, lane, [&](auto J) {
+                        drain_step<C::NKB1, decltype(J)::value>(X, pk);
                     });
-                    store_pass<C::PH, RP, CT>(pk, TX, act, C::ACT_STRIDE, lane);
+                    store_pass<RP, CT>(pk, TX, act, C::ACT_STRIDE, lane);
                     __syncthreads();
-                    auto hidden = [&](int l, auto OUTP) {
-                        constexpr int PO = decltype(OUTP)::value;
-                        const Rsrc wl = make_rsrc(p.wA[l], p.wA_bytes[l]), bl = make_rsrc(p.bias[l], p.bias_bytes[l]);
-                        const float osc_prev = p.oscale[l - 1], inv_prev = p.inv_in_scale[l];
-                        const float osc = p.oscale[l], inv = (l < 3) ? p.inv_in_scale[l + 1] : 1.0f;
-                        const int sc = (C::PH == kFP8) ? p.mscale[l] : 127;
-                        init_bias<RP, CT>(X, bl, TX, lane);
-                        mma_seq<C::PH, RP, CT, C::NKBH, C::NKBH / 2, MapHalf0<C::GH>, GMC_VPM_A>(
-                            X, wl, TX, act, C::ACT_STRIDE, 0, lane, [&](auto J) {
-                                drain_step<C::PH, C::SCALE, C::NKBH / 2, decltype(J)::value>(Y, pk, osc_prev, inv_prev);
-                            }, sc);
-                        store_pass<C::PH, RP, CT>(pk, TY, act, C::ACT_STRIDE, lane);
-                        __syncthreads();
-                        mma_seq<C::PH, RP, CT, C::NKBH, C::NKBH / 2, MapHalf1<C::GH>>(
-                            X, wl, TX, act, C::ACT_STRIDE, 0, lane, [](auto) {}, sc);
-                        init_bias<RP, CT>(Y, bl, TY, lane);
-                        mma_seq<C::PH, RP, CT, C::NKBH, C::NKBH, MapAll, GMC_VPM_P>(
-                            Y, wl, TY, act, C::ACT_STRIDE, 0, lane, [&](auto J) {
-                                drain_step<PO, C::SCALE, C::NKBH, decltype(J)::value>(X, pk, osc, inv);
-                            }, sc);
-                        __syncthreads();
-                        store_pass<PO, RP, CT>(pk, TX, act, C::ACT_STRIDE, lane);
-                        __syncthreads();
-                    };
-                    constexpr int NSAME = (C::PH == C::P5) ? 3 : 2;
 #pragma unroll 1
-                    for (int l = 1; l <= NSAME; ++l) hidden(l, std::integral_constant<int, C::PH>{});
-                    if constexpr (NSAME == 2) hidden(3, std::integral_constant<int, C::P5>{});
+                    for (int l = 1; l <= 3; ++l) {
+                        const Rsrc wl = make_rsrc(p.wA[l], p.wA_bytes[l]), bl = make_rsrc(p.bias[l], p.bias_bytes[l]);
+                        init_bias<RP, CT>(X, bl, TX, lane);
+                        mma_seq<kF32, RP, CT, C::NKBH, C::NKBH / 2, MapHalf0<C::GH>>(
+                            X, wl, TX, act, C::ACT_STRIDE, 0, lane, [&](auto J) {
+                                drain_step<C::NKBH / 2, decltype(J)::value>(Y, pk);
+                            });
+                        store_pass<RP, CT>(pk, TY, act, C::ACT_STRIDE, lane);
+                        __syncthreads();
+                        mma_seq<kF32, RP, CT, C::NKBH, C::NKBH / 2, MapHalf1<C::GH>>(
+                            X, wl, TX, act, C::ACT_STRIDE, 0, lane, [](auto) {});
+                        init_bias<RP, CT>(Y, bl, TY, lane);
+                        mma_seq<kF32, RP, CT, C::NKBH, C::NKBH, MapAll>(
+                            Y, wl, TY, act, C::ACT_STRIDE, 0, lane, [&](auto J) {
+                                drain_step<C::NKBH, decltype(J)::value>(X, pk);
+                            });
+                        __syncthreads();
+                        store_pass<RP, CT>(pk, TX, act, C::ACT_STRIDE, lane);
+                        __syncthreads();
+                    }
                     // layer 5 (5 x H, rows padded to one tile) over the first-pass k-blocks while
-                    // layer 4's second pass drains; wave w < 4 owns sample column tile w, further
+                    // layer 4's second pass drains; wave w < CT owns sample column tile w, further
                     // waves only drain
                     f32x16 out[1][1];
                     const Rsrc w4 = make_rsrc(p.wA[4], p.wA_bytes[4]);
-                    auto drain4 = [&](auto J) {
-                        drain_step<C::P5, C::SCALE, C::NKB5 / 2, decltype(J)::value>(Y, pk, p.oscale[3], 1.0f);
-                    };
+                    auto drain4 = [&](auto J) { drain_step<C::NKB5 / 2, decltype(J)::value>(Y, pk); };
                     if (C::W == CT || wave < CT) {
                         init_bias<1, 1>(out, make_rsrc(p.bias[4], p.bias_bytes[4]), 0, lane);
-                        mma_seq<C::P5, 1, 1, C::NKB5, C::NKB5 / 2, MapHalf0<C::G5>, GMC_VPM_5>(
+                        mma_seq<kF32, 1, 1, C::NKB5, C::NKB5 / 2, MapHalf0<C::G5>>(
                             out, w4, 0, act, C::ACT_STRIDE, wave, lane, drain4);
                     } else {
                         sfor<C::NKB5 / 2>(drain4);
                     }
-                    store_pass<C::P5, RP, CT>(pk, TY, act, C::ACT_STRIDE, lane);
+                    store_pass<RP, CT>(pk, TY, act, C::ACT_STRIDE, lane);
                     __syncthreads();
                     if (C::W == CT || wave < CT) {
-                        mma_seq<C::P5, 1, 1, C::NKB5, C::NKB5 / 2, MapHalf1<C::G5>>(
+                        mma_seq<kF32, 1, 1, C::NKB5, C::NKB5 / 2, MapHalf1<C::G5>>(
                             out, w4, 0, act, C::ACT_STRIDE, wave, lane, [](auto) {});
                         const int sn = wave * 32 + (lane & 31);
                         if (lane < 32) {
@@ -829,34 +675,23 @@ __global__ __launch_bounds__((Cfg<MP, H, TM>::THREADS), 1) void mlp_ode_kernel(M
                 }
 
                 // layer 1: 10 -> H (reads in0, writes the activation tile: no barrier before writing)
-                dense_silu<C::P1, C::PH, C::RTW, C::CT, C::NKB1, C::SCALE, false>(
-                    make_rsrc(p.wA[0], p.wA_bytes[0]), make_rsrc(p.bias[0], p.bias_bytes[0]), T0, in0, C::IN_STRIDE, act, C::ACT_STRIDE, lane,
-                    p.oscale[0], p.inv_in_scale[1]);
+                dense_silu<C::RTW, C::CT, C::NKB1, false>(
+                    make_rsrc(p.wA[0], p.wA_bytes[0]), make_rsrc(p.bias[0], p.bias_bytes[0]), T0, in0, C::IN_STRIDE, act,
+                    C::ACT_STRIDE, lane);
                 __syncthreads();
-                // hidden layers 2..4: H -> H, in place.  One code instance in a runtime loop (layers
-                // whose output feeds an operand of the same type as their input); an FP8 model's
-                // last hidden layer writes BF16 for the output layer and is a second instance.
-                constexpr int NSAME = (C::PH == C::P5) ? 3 : 2;
+                // hidden layers 2..4: H -> H, in place
 #pragma unroll 1
-                for (int l = 1; l <= NSAME; ++l) {
-                    dense_silu<C::PH, C::PH, C::RTW, C::CT, C::NKBH, C::SCALE, true>(
+                for (int l = 1; l <= 3; ++l) {
+                    dense_silu<C::RTW, C::CT, C::NKBH, true>(
                         make_rsrc(p.wA[l], p.wA_bytes[l]), make_rsrc(p.bias[l], p.bias_bytes[l]), T0,
-                        act, C::ACT_STRIDE, act, C::ACT_STRIDE, lane, p.oscale[l],
-                        l < 3 ? p.inv_in_scale[l + 1] : 1.0f, (C::PH == kFP8) ? p.mscale[l] : 127);
-                    __syncthreads();
-                }
-                if constexpr (NSAME == 2) {
-                    dense_silu<C::PH, C::P5, C::RTW, C::CT, C::NKBH, C::SCALE, true>(
-                        make_rsrc(p.wA[3], p.wA_bytes[3]), make_rsrc(p.bias[3], p.bias_bytes[3]), T0,
-                        act, C::ACT_STRIDE, act, C::ACT_STRIDE, lane, p.oscale[3], 1.0f,
-                        (C::PH == kFP8) ? p.mscale[3] : 127);
+                        act, C::ACT_STRIDE, act, C::ACT_STRIDE, lane);
                     __syncthreads();
                 }
                 // layer 5: H -> 5 (rows padded to 32); wave w handles sample column tile w
                 if (C::W == C::CT || wave < C::CT) {
                     f32x16 out[1][1];
                     init_bias<1, 1>(out, make_rsrc(p.bias[4], p.bias_bytes[4]), 0, lane);
-                    mma_pass<C::P5, 1, 1, C::NKB5>(out, make_rsrc(p.wA[4], p.wA_bytes[4]), 0, act,
+                    mma_pass<kF32, 1, 1, C::NKB5>(out, make_rsrc(p.wA[4], p.wA_bytes[4]), 0, act,
                                                    C::ACT_STRIDE, wave, lane, [](auto) {});
                     const int sn = wave * 32 + (lane & 31);
                     if (lane < 32) {
@@ -872,7 +707,7 @@ __global__ __launch_bounds__((Cfg<MP, H, TM>::THREADS), 1) void mlp_ode_kernel(M
             if ((!C::GROUPS || grp == 0) && tid < TM) {
                 const int64_t i = base + tid;
                 float xk[5];
-                if constexpr (rk4 && !fold) {
+                if constexpr (rk4 && !C::GROUPS) {
                     advance(nevals - 1, xk);
                 } else {
 #pragma unroll
@@ -1106,7 +941,7 @@ __global__ __launch_bounds__((WaveCfg<MP>::THREADS), WaveCfg<MP>::W / 4) void ml
             using I2 = std::integral_constant<int, 2>;
             using KH = std::integral_constant<int, C::NKBH / 2>;
             using KN = std::integral_constant<int, C::NKBH>;
-            constexpr int STEPS = 32 + 4 * GMC_PIPE_D, LEAD = 4;   // iterations of a pair's SiLU
+            constexpr int STEPS = 32 + 4 * kPipeD, LEAD = 4;   // iterations of a pair's SiLU
             // SiLU of the pair `src` (row tiles T0, T0 + 1) with a list of n products in its iterations
             auto silu_pair = [&](f32x16 (&src)[2], auto PO, auto SLOT, auto T0, float osc, float inv, auto N, auto &&run) {
                 constexpr int n = decltype(N)::value, every = (STEPS - LEAD) / (n > 0 ? n : 1);

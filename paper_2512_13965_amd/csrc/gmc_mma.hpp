@@ -11,11 +11,6 @@
 #include "gmc_device.hpp"
 #include "gmc_internal.hpp"
 
-// Weight fragments the half-range k-loop (mma_seq) loads ahead of the k-block it multiplies.
-#ifndef GMC_PFA
-#define GMC_PFA 2
-#endif
-
 namespace gmc {
 namespace {
 
@@ -124,7 +119,7 @@ __device__ __forceinline__ void sfor(F &&f)
 // A fragments are prefetched two k-blocks ahead, B fragments one.
 template <int P, int RP, int CT, int NKB, typename Hook>
 __device__ __forceinline__ void mma_pass(f32x16 (&acc)[RP][CT], Rsrc wA, int T0, const char *act,
-                                         int stride, int col0, int lane, Hook &&hook, int sc = 127)
+                                         int stride, int col0, int lane, Hook &&hook)
 {
     using M = Mma<P>;
     using Frag = typename M::Frag;
@@ -153,7 +148,7 @@ __device__ __forceinline__ void mma_pass(f32x16 (&acc)[RP][CT], Rsrc wA, int T0,
 #pragma unroll
         for (int r = 0; r < RP; ++r)
 #pragma unroll
-            for (int c = 0; c < CT; ++c) M::run(acc[r][c], a[kb % 3][r], b[kb % 2][c], sc);
+            for (int c = 0; c < CT; ++c) M::run(acc[r][c], a[kb % 3][r], b[kb % 2][c], 127);
         hook(KB);
         // keep each k-block in its own scheduling region: otherwise the scheduler merges the
         // passes' k-loops (they are independent), which defeats both the prefetch distance and
@@ -245,11 +240,10 @@ struct MapHalf1 {
 
 // acc[r][c] += W[T0 + r] x act[column tile col0 + c] over the NJ k-blocks Map::kb(0..NJ-1) of
 // a layer with NKB k-blocks (same fragment layout and prefetch scheme as mma_pass).
-template <int P, int RP, int CT, int NKB, int NJ, typename Map, int VPM = 0, int SWAPB = 0, typename Hook>
+template <int P, int RP, int CT, int NKB, int NJ, typename Map, typename Hook>
 __device__ __forceinline__ void mma_seq(f32x16 (&acc)[RP][CT], Rsrc wA, int T0, const char *act,
-                                        int stride, int col0, int lane, Hook &&hook, int sc = 127)
+                                        int stride, int col0, int lane, Hook &&hook)
 {
-    constexpr int MFMA_PER_RUN = (P == kF32) ? 4 : 1;
     using M = Mma<P>;
     using Frag = typename M::Frag;
     constexpr int FB = frag_bytes(P);
@@ -258,9 +252,7 @@ __device__ __forceinline__ void mma_seq(f32x16 (&acc)[RP][CT], Rsrc wA, int T0, 
     const int t0 = __builtin_amdgcn_readfirstlane(T0);
     const int voff = lane * FB;
     const char *sb = act + (col0 * 32 + n) * stride + h * (KBB / 2);
-    // k-blocks the weight loads run ahead (an FP8 k-block is four times the matrix work of a
-    // BF16 one, and its fragments twice the registers)
-    constexpr int PA = (P == kFP8) ? 1 : GMC_PFA;
+    constexpr int PA = 2;                              // k-blocks the weight loads run ahead
     Frag a[PA + 1][RP], b[2][CT];
     auto loadA = [&](int slot, int kb) {
 #pragma unroll
@@ -268,7 +260,7 @@ __device__ __forceinline__ void mma_seq(f32x16 (&acc)[RP][CT], Rsrc wA, int T0, 
     };
     auto loadB = [&](int slot, int kb) {
 #pragma unroll
-        for (int c = 0; c < CT; ++c) b[slot][c] = M::load_s(sb + c * 32 * stride + (kb ^ SWAPB) * KBB);
+        for (int c = 0; c < CT; ++c) b[slot][c] = M::load_s(sb + c * 32 * stride + kb * KBB);
     };
     sfor<PA>([&](auto I) {
         if constexpr (decltype(I)::value < NJ) loadA(decltype(I)::value, Map::kb(decltype(I)::value));
@@ -281,16 +273,8 @@ __device__ __forceinline__ void mma_seq(f32x16 (&acc)[RP][CT], Rsrc wA, int T0, 
 #pragma unroll
         for (int r = 0; r < RP; ++r)
 #pragma unroll
-            for (int c = 0; c < CT; ++c) M::run(acc[r][c], a[j % (PA + 1)][r], b[j % 2][c], sc);
+            for (int c = 0; c < CT; ++c) M::run(acc[r][c], a[j % (PA + 1)][r], b[j % 2][c], 127);
         hook(JJ);
-        if constexpr (VPM > 0) {
-            // interleave the hook's epilogue arithmetic between the MFMAs: one MFMA, then up
-            // to VPM vector instructions, so transcendental latencies hide behind matrix work
-            sfor<RP * CT * MFMA_PER_RUN>([&](auto) {
-                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-                __builtin_amdgcn_sched_group_barrier(0x002, VPM, 0);
-            });
-        }
         __builtin_amdgcn_sched_barrier(0);
     });
 }

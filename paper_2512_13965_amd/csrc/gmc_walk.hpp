@@ -43,7 +43,7 @@ constexpr int kGroupWalks = 16;
 constexpr int kGroupAfter = 6;
 
 // End of a walk (besides the exit faces 0..3): absorbed in the cell, or cut off at kMaxFlights.
-constexpr int kAbsorbed = -1, kCapped = -2, kWalking = -3, kAtFace = -4;
+constexpr int kAbsorbed = -1, kCapped = -2, kAtFace = -4;
 
 // One walk before its first flight: position and direction in the cell [0, wa] x [0, 1] (lengths
 // in units of its height), tau over that height, scattering ratio, random stream.
