@@ -313,7 +313,9 @@ int gmc_problem_remove(gmc_world *w, int32_t pid);
  * sampling, and for a volumetric source the first leg in the birth cell (the analog walk with
  * continuous absorption, or the internal model set by gmc_world_set_source_model), its tally,
  * and the move to the neighbour (a surface source's births enter their cell directly).  Survivors join the bank.  GMC_ENOMEM if count exceeds
- * the free bank slots.  Synchronises `stream`; *n_alive_out (optional) = particles in flight. */
+ * the free bank slots.  Synchronises `stream`; *n_alive_out (optional) = particles in flight.
+ * After GMC_EDEVICE, here and from gmc_transport_step, the particles in flight are those before the
+ * call (what the call had tallied stays tallied). */
 int gmc_world_inject(gmc_world *w, int32_t pid, uint64_t h_begin, int64_t count, void *stream,
                      int64_t *n_alive_out);
 /* One transport step for every particle in flight: canonical conditions (stage 1), one cell

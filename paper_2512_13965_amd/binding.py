@@ -81,7 +81,7 @@ _ready_devices = set()
 
 
 def device_init():
-    """gmc_device_init on the current device (once per device): the analog walk's counters."""
+    """gmc_device_init on the current device (once per device; the analog walk asks for it)."""
     dev = torch.cuda.current_device()
     if dev not in _ready_devices:
         _check(lib().gmc_device_init())
@@ -208,7 +208,7 @@ class Model:
         self.hidden, self.precision = hid.value, prec.value
         nin = ctypes.c_int()
         _check(lib().gmc_model_inputs(h, ctypes.byref(nin)))
-        self.n_in = nin.value          # 10: boundary model, 12: internal model
+        self.n_in = nin.value          # 10, 11: boundary model, 12: internal model
 
     @property
     def handle(self):

@@ -172,7 +172,8 @@ __global__ __launch_bounds__((FilmCfg<MP, H, TM>::THREADS), 1) void film_ode_ker
     }
     // The groups of the two-group schedule run separate code, as in the plain sampler, and form
     // their LDS addresses where they use them: held through the other phases they spill (106
-    // registers at width 512; 28 now).  Width 512, Euler K = 16, against one code, full tiles only:
+    // registers at width 512, Euler, full tiles; 28 now, 43 with RK4, 33 and 42 with 96-sample
+    // tiles, none and 8 with 64, none with 32).  Width 512, Euler K = 16, against one code, full tiles only:
     // 2^18 samples 6.88 -> 6.79 ms, 20,001 765 -> 670 us, 15,000 757 -> 514 us, 1,000 744 -> 340 us.
     auto tiles = [&](auto GRP) {
         constexpr int grp = decltype(GRP)::value;

@@ -93,12 +93,14 @@ struct MlpParams {
     int xy;                   // XY geometry: exit directions decoded into the unit disk
     uint64_t seed, id_base;
     // Device-side tile choice, for launches whose count n_dev is known only on the device and
-    // whose bound n exceeds what 32-sample tiles serve: the launcher runs the smaller-tile
-    // kernels first, 32 then 64 samples; each reads its count, and its first lane writes to
-    // its n_dev_large the count left to the next kernel (0 when the count is at most its
-    // small_max, else the whole count); it exits when that count is not 0, and the next kernel
-    // takes that word as its n_dev.  The caller passes two words of device memory (NULL: no
-    // device-side choice), one per handoff; the launcher sets each kernel's word and small_max.
+    // whose bound n exceeds what the smallest tiles serve: the launcher runs the kernels of small
+    // launches first (32-, then 64-sample tiles; for BF16 and FP8 of width 128 teams of four waves,
+    // then a wave each); each reads its count, and its first lane writes to its n_dev_large the
+    // count left to the next kernel (0 when the count is at most its small_max, else the whole
+    // count); it exits when that count is not 0, and the next kernel takes that word as its n_dev.
+    // The caller passes two words of device memory (NULL: no device-side choice), one per handoff;
+    // the launcher sets each kernel's word and small_max.  The residual network makes no such
+    // choice.
     unsigned long long *n_dev_large;
     int64_t small_max;
     // FP8 hidden layers: E8M0 byte (127 + e) of the matrix core's operand scale 2^e = 2 sw sa
@@ -108,7 +110,8 @@ struct MlpParams {
 
 // One fused sampler launch over p.n samples (the launch's bound: p.n_dev, when set, holds the
 // count) for the network p.net (plain MLP or residual network) on a device of cu compute units:
-// the launcher picks the tile size and a grid of at most cu persistent workgroups.
+// the launcher picks the kernel, the tile size and a grid of at most cu persistent workgroups (two to
+// a compute unit for the small launches of width 128, mlp_team_kernel).
 hipError_t launch_mlp_ode(int prec, int hidden, const MlpParams &p, int cu, hipStream_t s);
 bool mlp_supported(int prec, int hidden);
 hipError_t launch_film_ode(int prec, int hidden, const MlpParams &p, int cu, hipStream_t s);
@@ -129,9 +132,9 @@ struct WalkParams {
 };
 
 hipError_t launch_walk(const WalkParams &p, int grid, hipStream_t s);
-// Blocks of 256 lanes per compute unit of the walk kernels, all resident at once.  8 (64 registers
-// a lane) / 6 / 5 / 4: 2^20 mixed walks 172 / 157 / 157 / 154 us, at tau = 100 706 / 661 / 723 /
-// 740 us.
+// Blocks of 256 lanes per compute unit of the walk kernels, all resident at once.  8 / 6 / 5 / 4: 2^20
+// walks of mixed cells 118 / 109 / 117 / 111 us, at tau = 100 632 / 609 / 655 / 685 us; in XY geometry
+// 176 / 150 / 153 / 148 and 922 / 951 / 978 / 1,015 us; 2^23 at tau = 1 255 / 233 / 221 / 217 us.
 constexpr int kWalkBlocksPerCu = 6;
 // Grid of the walk for n particles: at least one particle to a wave (few walks are spread over
 // all waves, since a wave with few walks shares its lanes out among them).

@@ -10,7 +10,7 @@
 //   apply   (stages 3-4)  FP64 rescale of the path to physical units, weight attenuation and
 //            flux / absorption tallies (FP64 atomics), rotation back to the global frame, move
 //            to the neighbour cell or leave / cut off, and compaction of the survivors into the
-//            other bank with one atomic per wave (ballot + mbcnt).
+//            other bank with one atomic per workgroup's tile of particles.
 // Volumetric births draw a source particle and take its first leg inside the birth cell with the
 // analog walk or the internal (volumetric-source) model; surface-source births enter their
 // boundary cell directly.
