@@ -21,7 +21,8 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-mcode-object-v
 # Per-source device flags.  The samplers' MFMA accumulators stay in ordinary vector registers:
 # the four-wave kernels (FP32, and the residual network of width 128) otherwise keep them in
 # accumulation registers and move every value out with one extra vector instruction in the
-# epilogue (the residual network of width 128: 8 % of the launch); the two-group kernels already keep them there and compile to the same code.
+# epilogue (the residual network of width 128: 8 % of the launch); the two-group kernels already
+# keep them there and compile to the same code.
 SOURCE_FLAGS = {"gmc_mlp.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"],
                 "gmc_film.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"]}
 

@@ -282,7 +282,8 @@ __device__ __forceinline__ void append(AppendLds<THREADS> &al, bool alive, const
     uint32_t mine = 0;
     for (uint64_t m = mask; m;) {
         const int l0 = __ffsll((unsigned long long)m) - 1;
-        const uint64_t same = __ballot(alive && pid == __shfl(pid, l0));
+        const int p0 = __shfl(pid, l0);
+        const uint64_t same = __ballot(alive && pid == p0);
         if (lane == l0) mine = (uint32_t)__popcll(same);
         m &= ~same;
     }
